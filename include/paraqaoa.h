@@ -94,7 +94,8 @@ typedef void* qaoa_stream_t;
  *   QAOA_FLAG_GRADIENT_CHECKPOINTS keeps the state after every HBM pass of
  *     the forward sweep (for subgraphs of more than 13 qubits: max_p (G - 1)
  *     stored states, G = the subgraph's qubit groups; with the default group
- *     split 2 for 14..20 qubits, 3 for 21..28, 4 above), so that the adjoint
+ *     split 2 for 14..20 qubits, 3 for 21..28, 4 above, one less where the
+ *     library takes wide tiles, see qaoa_tune_group_split), so that the adjoint
  *     sweep reads psi where it needs it and writes only lambda;
  *   QAOA_FLAG_GRADIENT_INPLACE keeps one psi, which the adjoint sweep
  *     rebuilds by undoing each pass (less memory, 8 more bytes per stored
@@ -371,7 +372,11 @@ qaoa_status_t qaoa_state_offset(qaoa_batch_t h, int32_t b, size_t* out_offset);
  * created). Subgraphs with n > 13 qubits are simulated in group 0 (qubits
  * 0..10 and the top qubit, 4096-amplitude tiles) and strided groups of at most
  * 8 of the qubits 11..n-2, one HBM pass per group and layer (Sec. 2.2's mixer
- * is a product over qubits, so any grouping gives the same state).
+ * is a product over qubits, so any grouping gives the same state). Without a
+ * split named here, batches large enough take 16384-amplitude tiles (13 low
+ * qubits and the top one, strided groups of at most 12) for subgraphs where
+ * that saves a group: 21..26, 29 and 30 qubits, in gradient batches up to 25
+ * qubits and 29, 30, and only where the weight sum is at most 1.5 n.
  * sizes[0..count) are the strided group sizes in qubit order for subgraphs
  * with n qubits (each 1..8, at most 3 groups, adding up to n - 12); count = 0
  * restores the default (fewest groups, sizes as even as possible). Batches

@@ -10,8 +10,10 @@ bits are real qubits and how long the contiguous rows of a strided tile are
 candidate splits (fewest groups, every ordered composition of n - 12 into
 parts of at most 8) on a batch of random graphs with n qubits, one optimiser
 evaluation (forward pass + adjoint sweep) or one forward evaluation per
-repetition, and keeps the fastest. The table is saved as JSON and applied
-with `apply()` before batches are created.
+repetition, and keeps the fastest. A named split also keeps a subgraph on
+4096-amplitude tiles; the split None is the library's own choice, which takes
+wider tiles where those save a group, and is timed beside the named ones. The
+table is saved as JSON and applied with `apply()` before batches are created.
 
 Run: python -m paper_2603_26232_amd.autotune --n 21 22 ... --out FILE
 """
@@ -57,7 +59,7 @@ def time_split(n, split, p=3, gradient=True, amps=1 << 24, reps=5, seed=0):
     B = max(1, amps >> n)
     edges = []
     for b in range(B):
-        g = synth.erdos_renyi(n, 0.15, seed + b)
+        g = synth.erdos_renyi(n, 0.1, seed + b)
         edges.append((g.u, g.v, g.w))
     gamma, beta = synth.uniform_angles(seed + 999, p, batch=B)
     _abi.qaoa_tune_group_split(n, split)
@@ -95,7 +97,7 @@ def tune(ns, p=3, gradient=True, log=print):
         if len(cands) <= 1:
             continue
         res = []
-        for sp in cands:
+        for sp in cands + [None]:
             ms, per = time_split(n, sp, p=p, gradient=gradient)
             res.append((per, sp, ms))
             log(f"autotune: n={n} split {sp}: {ms:.3f} ms per evaluation ({per:.4f} ms per 2^20 amplitudes)")

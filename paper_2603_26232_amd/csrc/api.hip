@@ -208,6 +208,7 @@ struct Plan {
     // program and one launch per pass
     struct Class {
         int G;
+        bool wide;
         int chain[MAX_GROUPS];
         std::vector<int2> work;
         uint64_t o_work;
@@ -221,13 +222,36 @@ struct Plan {
 constexpr uint64_t CACHE_BYTES = 256ull << 20;
 constexpr uint64_t CACHE_FIT_BYTES = 224ull << 20;
 
+// Wide tiles need enough workgroups for the 256 CUs: with 64 in a batch they are
+// as fast as the 4096-amplitude tiles (21 qubits, p = 3: forward 63 us against
+// 64, gradient 134 against 123), with 128 faster (73 against 92, 142 against
+// 157 us).
+constexpr int64_t WIDE_MIN_TILES = 128;
+
 // layout-chain code of group g (see launch_fwd_pass): 3 for group 0; for a
-// high group 2 (8 qubits), 4 (5..7), 1 (4), 5 (1..3)
+// high group 2 (8 qubits), 4 (5..7), 1 (4), 5 (1..3); on wide tiles the
+// group's size
 int chain_of(const SubDesc& d, int g)
 {
     if (g == 0) return 3;
     const int nb = d.gsize[g];
+    if (d.wide) return nb;
     return nb == 8 ? 2 : (nb >= 5 ? 4 : (nb == 4 ? 1 : 5));
+}
+
+// Tile of position i in a class's work list. Workgroups go round robin over
+// the 8 XCDs, so tiles 8 positions apart run on one XCD at about the same
+// time. Wide strided groups of 10, 11 and 12 qubits have rows of 128, 64 and 32
+// bytes: 4, 8 and 8 neighbouring tiles are placed so that the XCD's L2 joins
+// their accesses to the lines (and DRAM pages) they share.
+int tile_order(const SubDesc& d, int i, int np)
+{
+    if (!d.wide) return i;
+    int nb = 0;
+    for (int g = 1; g < d.ngroups; ++g) nb = std::max(nb, d.gsize[g]);
+    const int m = nb < 10 ? 1 : nb == 10 ? 4 : 8;
+    if (m == 1 || np % (8 * m)) return i;
+    return i / (8 * m) * (8 * m) + i % 8 * m + i / 8 % m;
 }
 
 uint64_t align_up(uint64_t x, uint64_t a) { return (x + a - 1) / a * a; }
@@ -244,16 +268,40 @@ int groups_for(int n)
 std::mutex g_split_mu;
 std::vector<int> g_split[QAOA_MAX_QUBITS + 1];
 
-std::vector<int> group_split(int n)
+std::vector<int> tuned_split(int n)
 {
-    {
-        std::lock_guard<std::mutex> lk(g_split_mu);
-        if (!g_split[n].empty()) return g_split[n];
-    }
+    std::lock_guard<std::mutex> lk(g_split_mu);
+    return g_split[n];
+}
+
+std::vector<int> even_split(int rest, int parts)
+{
     std::vector<int> v;
-    const int G1 = groups_for(n) - 1, rest = n - TILE_BITS;
-    for (int g = 1; g <= G1; ++g) v.push_back(rest / G1 + (g <= rest % G1 ? 1 : 0));
+    for (int g = 1; g <= parts; ++g) v.push_back(rest / parts + (g <= rest % parts ? 1 : 0));
     return v;
+}
+
+// Wide tiles are taken where they save a qubit group, and so one pass over the
+// state per layer: 21..26 qubits (2 groups instead of 3) and 29, 30 (3 instead
+// of 4). Measured over 2^28 amplitudes at p = 3, 4096-amplitude against wide
+// tiles: forward 2.67 -> 1.59 ms at 21 qubits, 2.70 -> 1.66 at 24, 2.81 -> 1.95
+// at 25 (64-byte rows), 2.79 -> 2.47 at 26 (32-byte rows); gradient 5.94 -> 4.37,
+// 6.06 -> 4.68, 6.26 -> 5.10 and 6.21 -> 6.30 ms.
+int wide_groups_for(int n) { return 1 + (n - WIDE_BITS + WIDE_GROUP_MAX - 1) / WIDE_GROUP_MAX; }
+bool wide_saves(int n) { return n > SMALL_MAX_N + 2 && wide_groups_for(n) < groups_for(n); }
+
+// Exceptions. 26 qubits: the 32-byte rows take back the gradient's gain, and a
+// single state (256 MB) streams from the last-level cache faster than that
+// (0.64 against 0.71 ms). Gradients of denser graphs: at generic angles dE/dgamma
+// is small beside the C(z)-weighted terms that cancel in it (10^-5 and less of
+// them at 21 qubits and half of all edges), so another order of the roundings
+// moves its leading digits without being more or less exact; those subgraphs
+// keep the tiles, and the bits, that they have.
+bool wide_allowed(const SubDesc& d, bool grad, int64_t wsum, int n26)
+{
+    if (d.skip || !wide_saves(d.n) || !tuned_split(d.n).empty()) return false;
+    if (d.n == 26 && (grad || n26 < 2)) return false;
+    return !grad || 2 * wsum <= 3 * d.n;
 }
 
 qaoa_status_t make_plan(int32_t B, const int32_t* nq, const int64_t* eoff, const int32_t* ew, int32_t max_p,
@@ -301,20 +349,6 @@ qaoa_status_t make_plan(int32_t B, const int32_t* nq, const int64_t* eoff, const
                         QAOA_MAX_WEIGHT_SUM);
         SubDesc& d = P.subs[b];
         d.n = n;
-        // group 0: qubits 0..10 and the top qubit (the complement of a reduced
-        // index, tile bit 11); strided groups: qubits 11..n-2 of the reduced index
-        d.gstart[0] = 0;
-        d.gsize[0] = n <= SMALL_MAX_N ? n : TILE_BITS;
-        d.ngroups = 1;
-        if (n > SMALL_MAX_N) {
-            int q = HALF_BITS;
-            for (int sz : group_split(n)) {
-                d.gstart[d.ngroups] = q;
-                d.gsize[d.ngroups] = sz;
-                q += sz;
-                ++d.ngroups;
-            }
-        }
         d.lut_len = (int32_t)wsum + 1;
         d.tabw = wsum <= 255 ? 1 : 2;
         d.skip = (flags & QAOA_FLAG_SKIP_EDGELESS) && eoff[b + 1] == eoff[b];
@@ -327,6 +361,38 @@ qaoa_status_t make_plan(int32_t B, const int32_t* nq, const int64_t* eoff, const
     if (tiles > (1ll << 30)) return fail(QAOA_ERR_OUT_OF_RANGE, "batch too large (%lld tiles)", (long long)tiles);
     P.total_tiles = (int32_t)tiles;
     P.total_edges = eoff[B];
+    // Qubit groups. Group 0: the low qubits and the top one (the complement of
+    // a reduced index, the tile's highest bit); strided groups: the rest.
+    {
+        int64_t wide_tiles = 0;
+        int n26 = 0;
+        std::vector<char> wide(B, 0);
+        for (const SubDesc& d : P.subs) n26 += d.n == 26 && !d.skip;
+        for (int b = 0; b < B; ++b) {
+            const SubDesc& d = P.subs[b];
+            // (the matrix-core modes are defined on 4096-amplitude tiles)
+            wide[b] = P.prec == 0 && wide_allowed(d, grad, d.lut_len - 1, n26);
+            if (wide[b]) wide_tiles += 1ll << (d.n - 1 - WIDE_BITS);
+        }
+        for (int b = 0; b < B; ++b) {
+            SubDesc& d = P.subs[b];
+            d.wide = wide[b] && wide_tiles >= WIDE_MIN_TILES;
+            d.gstart[0] = 0;
+            d.gsize[0] = d.n <= SMALL_MAX_N ? d.n : d.wide ? WIDE_BITS : TILE_BITS;
+            d.ngroups = 1;
+            if (d.n <= SMALL_MAX_N) continue;
+            std::vector<int> split = tuned_split(d.n);
+            if (d.wide) split = even_split(d.n - WIDE_BITS, wide_groups_for(d.n) - 1);
+            else if (split.empty()) split = even_split(d.n - TILE_BITS, groups_for(d.n) - 1);
+            int q = d.gsize[0] - 1;
+            for (int sz : split) {
+                d.gstart[d.ngroups] = q;
+                d.gsize[d.ngroups] = sz;
+                q += sz;
+                ++d.ngroups;
+            }
+        }
+    }
     if (grad) {
         // Gradient memory: checkpoints unless asked otherwise, except when the
         // single-slot states and tables fit the 256 MB Infinity Cache and the
@@ -360,18 +426,20 @@ qaoa_status_t make_plan(int32_t B, const int32_t* nq, const int64_t* eoff, const
             if (d.skip) continue;
             int ci = -1;
             for (size_t k = 0; k < P.classes.size(); ++k) {
-                bool same = P.classes[k].G == d.ngroups;
+                bool same = P.classes[k].G == d.ngroups && P.classes[k].wide == (d.wide != 0);
                 for (int g = 0; same && g < d.ngroups; ++g) same = P.classes[k].chain[g] == chain_of(d, g);
                 if (same) ci = (int)k;
             }
             if (ci < 0) {
                 Plan::Class c{};
                 c.G = d.ngroups;
+                c.wide = d.wide != 0;
                 for (int g = 0; g < d.ngroups; ++g) c.chain[g] = chain_of(d, g);
                 P.classes.push_back(c);
                 ci = (int)P.classes.size() - 1;
             }
-            for (int t = 0; t < d.ntiles; ++t) P.classes[ci].work.push_back(make_int2(b, t));
+            const int np = partials_of(&d);
+            for (int i = 0; i < np; ++i) P.classes[ci].work.push_back(make_int2(b, tile_order(d, i, np)));
             P.classes[ci].tab_bytes += (double)d.ntiles * TILE * d.tabw;
         }
     }
@@ -494,9 +562,9 @@ const char* pass_name(const PassOps& o, bool backward)
 
 // algorithmic HBM bytes of one pass over a class: states read and written
 // once, the cut table (1 or 2 B per amplitude) where the pass needs C(z)
-double pass_bytes(const PassOps& o, bool backward, int nwork, double tab_bytes)
+double pass_bytes(const PassOps& o, bool backward, int nwork, double tab_bytes, bool wide)
 {
-    const double amps = (double)nwork * TILE;
+    const double amps = (double)nwork * (wide ? WIDE_TILE : TILE);
     double per;
     bool tab;
     if (!backward) {
@@ -645,7 +713,7 @@ static qaoa_status_t for_each_class(qaoa_batch_t h, int32_t p, hipStream_t st, F
     qaoa_status_t s = QAOA_OK;
     if (nc > 0) s = body(0, st);
     for (int k = 1; k < nc && s == QAOA_OK && ferr == hipSuccess; ++k)
-        s = body(k, pick((double)P.classes[k].work.size() * (double)(p * (P.classes[k].G - 1) + 1)));
+        s = body(k, pick((double)P.classes[k].work.size() * (P.classes[k].wide ? WIDE_TILE / TILE : 1) * (double)(p * (P.classes[k].G - 1) + 1)));
     if (P.nsmall && s == QAOA_OK && ferr == hipSuccess) s = body(-1, pick((double)P.nsmall * p));
     // join every side stream that was forked, also after an error
     for (int j = 0; j < NSIDE; ++j) {
@@ -809,9 +877,12 @@ extern "C" qaoa_status_t qaoa_apply_layers(qaoa_batch_t h, int32_t p, const doub
             PassOps o = passes[i];
             o.init = i == 0;
             o.epi_e = i + 1 == passes.size();
-            ProfScope ps(pass_name(o, false), cs, pass_bytes(o, false, nw, c.tab_bytes));
-            HIP_TRY(launch_fwd_pass(h->ws, h->d_subs, work, nw, c.chain[o.group], o, h->part, P.lut_max, P.prec,
-                                    cs));
+            ProfScope ps(pass_name(o, false), cs, pass_bytes(o, false, nw, c.tab_bytes, c.wide));
+            if (c.wide)
+                HIP_TRY(launch_fwd_wide(h->ws, h->d_subs, work, nw, c.chain[o.group], o, h->part, P.lut_max, cs));
+            else
+                HIP_TRY(launch_fwd_pass(h->ws, h->d_subs, work, nw, c.chain[o.group], o, h->part, P.lut_max, P.prec,
+                                        cs));
         }
         return QAOA_OK;
     });
@@ -878,9 +949,16 @@ static qaoa_status_t enqueue_class_grad(qaoa_batch_t h, int k, int32_t p, hipStr
             o.init = i == 0;
             o.psi_in = ck && i > 0 ? i - 1 : 0;
             o.psi_out = ck ? i : 0;
-            ProfScope ps(pass_name(o, false), st, pass_bytes(o, false, nw, c.tab_bytes));
-            HIP_TRY(launch_fwd_pass(h->ws, h->d_subs, work, nw, c.chain[o.group], o, h->part, P.lut_max, 0, st));
+            ProfScope ps(pass_name(o, false), st, pass_bytes(o, false, nw, c.tab_bytes, c.wide));
+            if (c.wide)
+                HIP_TRY(launch_fwd_wide(h->ws, h->d_subs, work, nw, c.chain[o.group], o, h->part, P.lut_max, st));
+            else
+                HIP_TRY(launch_fwd_pass(h->ws, h->d_subs, work, nw, c.chain[o.group], o, h->part, P.lut_max, 0, st));
         }
+        auto backward = [&](const PassOps& o) {
+            return c.wide ? launch_bwd_wide(h->ws, h->d_subs, work, nw, c.chain[o.group], o, h->part, P.lut_max, st)
+                          : launch_bwd_pass(h->ws, h->d_subs, work, nw, c.chain[o.group], o, h->part, P.lut_max, st);
+        };
         std::vector<Op> rev(ops.rbegin(), ops.rend());
         std::vector<PassOps> bwd = group_passes(rev);
         // the last forward pass (RX of the last group, layer p-1) and the
@@ -889,16 +967,16 @@ static qaoa_status_t enqueue_class_grad(qaoa_batch_t h, int k, int32_t p, hipStr
         f.fused = 1;
         f.psi_in = ck ? F - 2 : 0;
         {
-            ProfScope ps(pass_name(f, true), st, pass_bytes(f, true, nw, c.tab_bytes));
-            HIP_TRY(launch_bwd_pass(h->ws, h->d_subs, work, nw, c.chain[f.group], f, h->part, P.lut_max, st));
+            ProfScope ps(pass_name(f, true), st, pass_bytes(f, true, nw, c.tab_bytes, c.wide));
+            HIP_TRY(backward(f));
         }
         for (int i = 1; i < (int)bwd.size(); ++i) {
             PassOps o = bwd[i];
             o.last = i + 1 == (int)bwd.size();
             o.nopsi = ck || i + 2 == (int)bwd.size();  // the last pass synthesises psi
             o.psi_in = ck ? F - 1 - i : 0;
-            ProfScope ps(pass_name(o, true), st, pass_bytes(o, true, nw, c.tab_bytes));
-            HIP_TRY(launch_bwd_pass(h->ws, h->d_subs, work, nw, c.chain[o.group], o, h->part, P.lut_max, st));
+            ProfScope ps(pass_name(o, true), st, pass_bytes(o, true, nw, c.tab_bytes, c.wide));
+            HIP_TRY(backward(o));
         }
     }
     return QAOA_OK;

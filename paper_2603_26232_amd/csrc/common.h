@@ -17,6 +17,12 @@ constexpr int TILE = 1 << TILE_BITS;
 constexpr int THREADS = 256;
 constexpr int REGS = TILE / THREADS;  // 16
 constexpr int LDS_TILE = TILE + TILE / 16;  // one pad slot per 16 amplitudes
+// Wide tiles (wide.hip): 2^14 amplitudes, 512 threads with 32 amplitudes each
+constexpr int WIDE_BITS = 14;
+constexpr int WIDE_TILE = 1 << WIDE_BITS;
+constexpr int WIDE_THREADS = 512;
+constexpr int WIDE_REGS = WIDE_TILE / WIDE_THREADS;  // 32
+constexpr int WIDE_GROUP_MAX = 12;  // active qubits of a wide strided group (rows of 4 amplitudes)
 constexpr int MAX_GROUPS = 4;  // qubit groups per subgraph (n <= 30)
 constexpr int MAX_P = 32;      // QAOA depth limit
 constexpr int MAX_K = 64;      // top-k limit
@@ -33,19 +39,22 @@ constexpr int B_GROUP_MAX = 8;   // active qubits of a strided (high) group
 // Per-subgraph descriptor, resident in the workspace.
 struct SubDesc {
     int32_t n;        // qubits
-    int32_t ngroups;  // 1 for n <= 13 (whole-state kernel), else 1 + ceil((n-12)/8)
+    int32_t ngroups;  // 1 for n <= 13 (whole-state kernel), else 1 + ceil((n-12)/8) (wide tiles: 1 + ceil((n-14)/12))
     int32_t gstart[MAX_GROUPS];  // first qubit of group g (group 0 starts at 0)
-    int32_t gsize[MAX_GROUPS];   // qubits in group g (group 0: n when n <= 13, else 12)
+    int32_t gsize[MAX_GROUPS];   // qubits in group g (group 0: n when n <= 13, else 12, or 14 with wide tiles)
     int32_t lut_len;  // sum of weights + 1 (phase table length per layer)
-    int32_t ntiles;   // max(1, 2^(n-12))
+    int32_t ntiles;   // 4096-amplitude tiles, max(1, 2^(n-13))
     int32_t tile_base;  // first global tile index
     int32_t nedges;
     int32_t skip;  // edgeless and not simulated (closed form)
     int32_t tabw;  // bytes per cut-table entry: 1 (weight sum <= 255) or 2
     uint32_t freem;  // vertices without an edge of positive weight (bit j = local vertex j)
-    int32_t pad_;
+    int32_t wide;  // its passes run on wide tiles: npart = ntiles / 4 of them, tables in their order
     uint64_t psi, lam, tab, tabB, lut, coef, edges;  // byte offsets into the workspace
 };
+
+// Partial sums that a subgraph's passes write: one per tile they run on.
+__host__ __device__ inline int partials_of(const SubDesc* d) { return d->wide ? d->ntiles >> (WIDE_BITS - TILE_BITS) : d->ntiles; }
 
 // Which part of the circuit one tile pass applies (layers are 0-based,
 // -1 = absent). Forward: RX(pre), phase(ph), RX(post). Backward: unmix(pre)
@@ -175,6 +184,12 @@ hipError_t launch_bwd_pass(uint8_t* ws, const SubDesc* subs, const int2* work, i
                            PassOps ops, Partials part, int lut_max, hipStream_t s);
 hipError_t launch_small(uint8_t* ws, const SubDesc* subs, const int32_t* list, int nlist, int p,
                         int grad, Partials part, int lut_max, hipStream_t s);
+// ---- launchers (wide.hip) ----
+// chain: 3: group 0; 7..12: a strided group of that many qubits
+hipError_t launch_fwd_wide(uint8_t* ws, const SubDesc* subs, const int2* work, int nwork, int chain,
+                           PassOps ops, Partials part, int lut_max, hipStream_t s);
+hipError_t launch_bwd_wide(uint8_t* ws, const SubDesc* subs, const int2* work, int nwork, int chain,
+                           PassOps ops, Partials part, int lut_max, hipStream_t s);
 // ---- launchers (optim.hip) ----
 hipError_t launch_angle_prep(uint8_t* ws, const SubDesc* subs, int B, int p, const double* gamma,
                              const double* beta, hipStream_t s);

@@ -83,7 +83,7 @@ __global__ __launch_bounds__(THREADS) void k_reduce(const SubDesc* subs, int p, 
     __shared__ double red[THREADS / 64];
     const int b = blockIdx.x, q = blockIdx.y;
     const SubDesc* sd = subs + b;
-    const int T = part.total_tiles, tb = sd->tile_base, nt = sd->ntiles, G = sd->ngroups;
+    const int T = part.total_tiles, tb = sd->tile_base, nt = partials_of(sd), G = sd->ngroups;
     double acc = 0.0;
     if (q == 0) {
         for (int i = threadIdx.x; i < nt; i += THREADS) acc += part.e[tb + i];
@@ -129,7 +129,7 @@ __global__ __launch_bounds__(THREADS) void k_reduce_adam(uint8_t* ws, const SubD
     const SubDesc* sd = subs + b;
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
     const int32_t t = *step + it + 1;
-    const int T = part.total_tiles, tb = sd->tile_base, nt = sd->ntiles, G = sd->ngroups;
+    const int T = part.total_tiles, tb = sd->tile_base, nt = partials_of(sd), G = sd->ngroups;
     // sums (k_reduce's terms and order: per thread in tile order, groups
     // inner; the wave tree; the waves in order): 0 = dE/dgamma_l,
     // 1 = dE/dbeta_l, 2 = <C>

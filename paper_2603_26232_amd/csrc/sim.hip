@@ -35,7 +35,7 @@
 // permutation is never executed but carried as an XOR mask on tile positions
 // into cut-table reads and store addresses. Gradient inner products taken on
 // scaled states are rescaled by the known |f|^2 powers.
-#include "common.h"
+#include "tile.h"
 
 // Occupancy targets of the tile passes (waves per SIMD): the register budget
 // the compiler may use is 512 / target VGPRs per lane.
@@ -50,40 +50,6 @@
 #endif
 
 namespace pq {
-
-// ---------------------------------------------------------------------------
-// tile geometry
-// ---------------------------------------------------------------------------
-struct Geo {
-    uint32_t zb;   // fixed index bits of this tile
-    int c;         // passive low tile bits (contiguous amplitudes)
-    int g0;        // first qubit of the group
-    int nb;        // qubits in the group (active tile bits = [c, 12))
-    uint32_t mir;  // group 0: 2^(n-1) - 1 (the complement of a reduced index)
-};
-
-// tile position q -> z offset (bit deposit; zb supplies the fixed bits)
-__device__ inline uint32_t gmap(const Geo& g, uint32_t q)
-{
-    return (q & ((1u << g.c) - 1u)) | ((q >> g.c) << g.g0);
-}
-
-// Group 0 tiles pair a block of 2048 reduced indices with its mirror block:
-// tile bits 0..10 are qubits 0..10 and tile bit 11 selects the block or its
-// complement (index XOR 2^(n-1) - 1). In the reduced state the top qubit's
-// X maps an index to its complement, so it acts on tile bit 11 like any other
-// qubit on its bit. The map is XOR-linear, as the deposit of the other groups.
-__device__ inline uint32_t gmap0(const Geo& g, uint32_t q)
-{
-    return (q & ((1u << HALF_BITS) - 1u)) ^ ((q >> HALF_BITS) & 1u ? g.mir : 0u);
-}
-
-template <bool G0>
-__device__ inline uint32_t gmapT(const Geo& g, uint32_t q)
-{
-    if constexpr (G0) return gmap0(g, q);
-    else return gmap(g, q);
-}
 
 // Register layouts of a 4096-amplitude tile over 256 lanes x 16 registers.
 // LLIN: lanes = tile bits 0..7, registers = bits 8..11 (coalesced rows)
@@ -178,16 +144,6 @@ __device__ inline void xchg(float2* lds, uint32_t tid, float2 (&v)[REGS])
     __builtin_amdgcn_sched_barrier(0);
 }
 
-// Reduced pair rotation (I - i t X) on (a, b) = (psi(z), psi(z ^ bit)):
-// (a, b) -> (a - i t b, b - i t a). t = 0 is exactly the identity.
-__device__ inline void rx_tan(float2& a, float2& b, float t)
-{
-    const float2 na = make_float2(a.x + t * b.y, a.y - t * b.x);
-    const float2 nb = make_float2(b.x + t * a.y, b.y - t * a.x);
-    a = na;
-    b = nb;
-}
-
 template <int K>
 __device__ inline void rx_bit(float2 (&v)[REGS], float t)
 {
@@ -224,35 +180,10 @@ __device__ inline float xb_bit(const float2 (&ps)[REGS], const float2 (&la)[REGS
     return a0 + a1;
 }
 
-__device__ inline float2 cmul(float2 a, float2 b)
-{
-    return make_float2(a.x * b.x - a.y * b.y, a.x * b.y + a.y * b.x);
-}
-
 __device__ inline void scale_regs(float2 (&v)[REGS], float2 f)
 {
 #pragma unroll
     for (int r = 0; r < REGS; ++r) v[r] = cmul(v[r], f);
-}
-
-// Per-layer rotation parameters (built in FP64 by the angle-prep kernel):
-// e^{-i beta X} = f (I - i t X) X^flip per qubit.
-struct RxC {
-    float t;
-    int flip;
-    float fsq;      // |f|^2
-    float2 Ff, Fi;  // f^(group size), forward and inverse
-};
-
-__device__ inline RxC load_rx(const RxCoef* cf, int l, int g)
-{
-    RxC r;
-    r.t = cf[l].t;
-    r.flip = cf[l].mode;
-    r.fsq = cf[l].fsq;
-    r.Ff = cf[l].Ff[g];
-    r.Fi = cf[l].Fi[g];
-    return r;
 }
 
 // FULL: every register bit of every layout in the chain is an active qubit
@@ -560,17 +491,6 @@ __device__ inline CutTab tile_tab(const uint8_t* ws, const SubDesc* sd, int g, u
     return CutTab{(g == 0 ? ws + sd->tab : ws + sd->tabB) + (size_t)t * TILE * w, w};
 }
 
-// OFF32: addresses as 32-bit byte offsets from the state's (uniform) base
-// (a stored state of n <= 30 qubits spans at most 2^29 amplitudes = 4 GiB).
-// The map is XOR-linear, so a register's offset is the lane's offset XOR a
-// per-register value that is uniform across the workgroup: one vector XOR
-// per access instead of an XOR and a 64-bit address add.
-__device__ inline const float2& at_off(const float2* st, uint32_t off)
-{
-    return *(const float2*)((const uint8_t*)st + off);
-}
-__device__ inline float2& at_off(float2* st, uint32_t off) { return *(float2*)((uint8_t*)st + off); }
-
 template <int L, bool G0, bool OFF32 = false>
 __device__ inline void load_state(float2 (&v)[REGS], const float2* st, const Geo& geo, uint32_t tid)
 {
@@ -606,36 +526,6 @@ __device__ inline void store_state(const float2 (&v)[REGS], float2* st, const Ge
     }
 }
 
-// deterministic block sum (wave64 butterfly, then the 4 wave totals in order)
-// three deterministic block sums with one barrier pair
-__device__ inline void block_sum3(double& a, double& b, double& c, double* red)
-{
-    for (int off = 32; off > 0; off >>= 1) {
-        a += __shfl_xor(a, off);
-        b += __shfl_xor(b, off);
-        c += __shfl_xor(c, off);
-    }
-    const uint32_t tid = threadIdx.x;
-    const int nw = (int)(blockDim.x >> 6);
-    if ((tid & 63u) == 0) {
-        red[tid >> 6] = a;
-        red[nw + (tid >> 6)] = b;
-        red[2 * nw + (tid >> 6)] = c;
-    }
-    __syncthreads();
-    if (tid == 0) {
-        double x = 0.0, y = 0.0, z = 0.0;
-        for (int i = 0; i < nw; ++i) {
-            x += red[i];
-            y += red[nw + i];
-            z += red[2 * nw + i];
-        }
-        a = x;
-        b = y;
-        c = z;
-    }
-}
-
 __device__ inline uint32_t cut_of(uint32_t z, const int32_t* E, int ne)
 {
     uint32_t c = 0;
@@ -644,27 +534,6 @@ __device__ inline uint32_t cut_of(uint32_t z, const int32_t* E, int ne)
         c += (((z >> u) ^ (z >> v)) & 1u) ? (uint32_t)w : 0u;
     }
     return c;
-}
-
-__device__ inline Geo make_geo(const SubDesc* sd, int g, uint32_t t)
-{
-    Geo r;
-    r.mir = 0;
-    if (g == 0) {
-        r.c = 0;
-        r.g0 = 0;
-        r.nb = TILE_BITS;
-        r.zb = t << HALF_BITS;
-        r.mir = (1u << (sd->n - 1)) - 1u;
-    } else {
-        r.nb = sd->gsize[g];
-        r.g0 = sd->gstart[g];
-        r.c = TILE_BITS - r.nb;
-        const int L = r.g0 - r.c;  // fixed bits between the passive block and the group
-        const uint32_t tlo = t & ((1u << L) - 1u), thi = t >> L;
-        r.zb = (tlo << r.c) | (thi << (r.g0 + r.nb));
-    }
-    return r;
 }
 
 // ---------------------------------------------------------------------------
@@ -683,8 +552,14 @@ __global__ __launch_bounds__(THREADS) void k_cut_tables(uint8_t* ws, const SubDe
     uint8_t* tab = ws + sd->tab;
     const uint32_t dim = 1u << (n - 1);
     const uint32_t span = dim < (uint32_t)TILE ? dim : (uint32_t)TILE;
-    const Geo geoA = make_geo(sd, 0, t);
-    const Geo geoB = make_geo(sd, G >= 2 ? G - 1 : 0, t);
+    // wide tiles: this block covers a quarter of tile t / 4, whose entries lie
+    // in the order (lane, register) of their layout LL1
+    const bool wide = sd->wide != 0;
+    const int TB = wide ? WIDE_BITS : TILE_BITS;
+    const uint32_t tw = wide ? t >> (WIDE_BITS - TILE_BITS) : t;
+    const uint32_t first = wide ? (t << TILE_BITS) & ((uint32_t)WIDE_TILE - 1u) : 0u;
+    const Geo geoA = make_geo(sd, 0, tw, TB);
+    const Geo geoB = make_geo(sd, G >= 2 ? G - 1 : 0, tw, TB);
     uint8_t* tabB = ws + sd->tabB;
     const bool w1 = sd->tabw == 1;
     // four consecutive entries per thread, written as whole 32-bit words
@@ -695,8 +570,14 @@ __global__ __launch_bounds__(THREADS) void k_cut_tables(uint8_t* ws, const SubDe
             uint32_t z[4], zB[4], c[4] = {0, 0, 0, 0}, cb[4] = {0, 0, 0, 0};
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
-                z[i] = G >= 2 ? geoA.zb ^ gmap0(geoA, q0 + i) : q0 + i;
-                zB[i] = geoB.zb | gmap(geoB, q0 + i);
+                uint32_t q = q0 + i;
+                if (wide) {
+                    q = wide_entry(first + q);
+                    z[i] = geoA.zb ^ gmap0<WIDE_BITS>(geoA, q);
+                } else {
+                    z[i] = G >= 2 ? geoA.zb ^ gmap0(geoA, q) : q;
+                }
+                zB[i] = geoB.zb | gmap(geoB, q);
             }
             for (int e = 0; e < ne; ++e) {
                 const int32_t u = E[3 * e], v = E[3 * e + 1];

@@ -1,0 +1,641 @@
+// Tile passes on wide tiles: 2^14 amplitudes per workgroup instead of 2^12,
+// for the subgraphs where that saves whole passes over the state.
+//
+// What a pass computes, the pass kinds, the reduced state, the mirror-paired
+// group 0, the factored rotation with its flip mask and the adjoint sweep are
+// those of sim.hip. What differs is the tile: 512 lanes hold 32 amplitudes
+// each, so group 0 rotates 13 low qubits and the top one, and a strided group
+// up to 12 qubits. Subgraphs of 21..26 qubits then need two groups instead of
+// three and those of 29 and 30 three instead of four: a layer costs one pass
+// over the state instead of two (two instead of three).
+//
+// Register layouts (tile position q, 14 bits; lane id = 9 bits):
+//   LLIN  registers = bits 9..13, lanes = bits 0..8 (coalesced rows)
+//   LL1   registers = bits 4..8,  lanes = bits 0..3 and 9..13
+// Bits 0..3 are rotated in LL1 across the lanes of a row of 16: the lane
+// number is the XOR of masks 1, 2, 7, 15 for the bits that are set, so that a
+// bit's partner lane is one DPP step away (quad_perm, row_half_mirror,
+// row_mirror). That costs one instruction per amplitude and bit more than a
+// register bit, and saves a third layout and its LDS exchange.
+// The forward passes exchange the real and the imaginary parts one after the
+// other through 66 KB of LDS, so that two workgroups share a CU; the backward
+// passes hold two states in registers (two waves per SIMD), so one workgroup
+// owns the CU's LDS and exchanges whole amplitudes.
+//
+// Measured on 1.68e8 amplitudes (ten 25-qubit states, one launch; algorithmic
+// bytes): group 0 middle forward 557 us (5.1 TB/s), 11-qubit middle forward
+// 790 us (3.6 TB/s: a copy of 64-byte rows reaches 3.6), group 0 middle
+// backward 1.50 ms (2.8 TB/s), 11-qubit middle backward 1.48 ms (2.8 TB/s).
+// The forward passes are bound by memory. The backward ones issue 6,370 (group
+// 0) and 4,810 vector instructions per wave, 0.57 of the time at the vector
+// units' rate, and their loads and stores do not overlap that: at 256 registers
+// a lane, one workgroup fills the CU. On 4096-amplitude tiles the two passes
+// that each of these replaces take 5.9 + 4.5 and 4.9 + 4.5 ns per 1000
+// amplitudes, against 8.9 and 8.8.
+//
+// Phases, <C> and the gamma terms always happen in LL1, and the cut tables of
+// these tiles are stored in that layout's order (lane, register), so a lane
+// reads its 32 entries as two (1-byte entries) or four 16-byte loads.
+#include "tile.h"
+
+namespace pq {
+
+namespace {
+
+constexpr int WT = WIDE_THREADS, WR = WIDE_REGS;
+enum { LLIN = 0, LL1 = 1 };
+constexpr uint32_t EX_SLOTS = WIDE_TILE + WIDE_TILE / 32;  // one pad slot per 32 amplitudes
+
+template <int L>
+__device__ inline uint32_t thread_part(uint32_t tid)
+{
+    return L == LLIN ? tid : wide_nibble(tid & 15u) | ((tid >> 4) << 9);
+}
+template <int L>
+__host__ __device__ constexpr uint32_t reg_part(uint32_t r)
+{
+    return L == LLIN ? (r << 9) : (r << 4);
+}
+__host__ __device__ constexpr uint32_t slot(uint32_t q) { return q + (q >> 5); }  // additive over disjoint bits
+
+// Layout change of one state through a buffer of single floats. In LL1 a wave
+// reads and writes only its own eighth of the buffer (tile bits 11..13), so
+// after a change to LL1 no barrier is needed before the next one writes.
+template <int LF, int LT>
+__device__ inline void xchg(float* ex, uint32_t tid, float2 (&v)[WR])
+{
+    float* p = ex + slot(thread_part<LF>(tid));
+    const float* s = ex + slot(thread_part<LT>(tid));
+#pragma unroll
+    for (int r = 0; r < WR; ++r) p[slot(reg_part<LF>(r))] = v[r].x;
+    __syncthreads();
+#pragma unroll
+    for (int r = 0; r < WR; ++r) v[r].x = s[slot(reg_part<LT>(r))];
+    __syncthreads();
+#pragma unroll
+    for (int r = 0; r < WR; ++r) p[slot(reg_part<LF>(r))] = v[r].y;
+    __syncthreads();
+#pragma unroll
+    for (int r = 0; r < WR; ++r) v[r].y = s[slot(reg_part<LT>(r))];
+    if constexpr (LT == LLIN) __syncthreads();
+    __builtin_amdgcn_sched_barrier(0);
+}
+
+// The same for whole amplitudes (backward passes).
+template <int LF, int LT>
+__device__ inline void xchg2(float2* ex, uint32_t tid, float2 (&v)[WR])
+{
+    float2* p = ex + slot(thread_part<LF>(tid));
+    const float2* s = ex + slot(thread_part<LT>(tid));
+#pragma unroll
+    for (int r = 0; r < WR; ++r) p[slot(reg_part<LF>(r))] = v[r];
+    __syncthreads();
+#pragma unroll
+    for (int r = 0; r < WR; ++r) v[r] = s[slot(reg_part<LT>(r))];
+    __syncthreads();
+    __builtin_amdgcn_sched_barrier(0);
+}
+
+// Operations across lanes on tile bit K (0..3) in LL1, on DPP operands: the
+// compiler does not fold a DPP move into a fused multiply-add, which would
+// cost a move per operand. Each block starts with the two wait states that a
+// DPP read needs after the last vector write of its source, and reads nothing
+// by DPP that it has written within the two instructions before.
+#define PQ_DPP0 "quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf"
+#define PQ_DPP1 "quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf"
+#define PQ_DPP2 "row_half_mirror row_mask:0xf bank_mask:0xf"
+#define PQ_DPP3 "row_mirror row_mask:0xf bank_mask:0xf"
+
+// x += t * (partner's y), y -= t * (partner's old x), four amplitudes
+#define PQ_RX_LANE(D)                                                                                            \
+    asm("s_nop 1\n\t"                                                                                            \
+        "v_mov_b32 %8, %0\n\t"                                                                                   \
+        "v_mov_b32 %9, %2\n\t"                                                                                   \
+        "v_mov_b32 %10, %4\n\t"                                                                                  \
+        "v_mov_b32 %11, %6\n\t"                                                                                  \
+        "v_fmac_f32_dpp %0, %1, %12 " D "\n\t"                                                                   \
+        "v_fmac_f32_dpp %2, %3, %12 " D "\n\t"                                                                   \
+        "v_fmac_f32_dpp %4, %5, %12 " D "\n\t"                                                                   \
+        "v_fmac_f32_dpp %6, %7, %12 " D "\n\t"                                                                   \
+        "v_fmac_f32_dpp %1, %8, %13 " D "\n\t"                                                                   \
+        "v_fmac_f32_dpp %3, %9, %13 " D "\n\t"                                                                   \
+        "v_fmac_f32_dpp %5, %10, %13 " D "\n\t"                                                                  \
+        "v_fmac_f32_dpp %7, %11, %13 " D                                                                          \
+        : "+v"(v[r].x), "+v"(v[r].y), "+v"(v[r + 1].x), "+v"(v[r + 1].y), "+v"(v[r + 2].x), "+v"(v[r + 2].y),     \
+          "+v"(v[r + 3].x), "+v"(v[r + 3].y), "=&v"(s0), "=&v"(s1), "=&v"(s2), "=&v"(s3)                          \
+        : "v"(t), "v"(-t))
+
+// rotation of tile bit K across lanes
+template <int K>
+__device__ inline void rx_lane(float2 (&v)[WR], float t)
+{
+#pragma unroll
+    for (int r = 0; r < WR; r += 4) {
+        float s0, s1, s2, s3;
+        if constexpr (K == 0) PQ_RX_LANE(PQ_DPP0);
+        else if constexpr (K == 1) PQ_RX_LANE(PQ_DPP1);
+        else if constexpr (K == 2) PQ_RX_LANE(PQ_DPP2);
+        else PQ_RX_LANE(PQ_DPP3);
+    }
+}
+
+// a += la.x * (partner's ps.y), b += la.y * (partner's ps.x), four amplitudes
+#define PQ_XB_LANE(D)                                                                                            \
+    asm("s_nop 1\n\t"                                                                                            \
+        "v_fmac_f32_dpp %0, %3, %10 " D "\n\t"                                                                   \
+        "v_fmac_f32_dpp %1, %2, %11 " D "\n\t"                                                                   \
+        "v_fmac_f32_dpp %0, %5, %12 " D "\n\t"                                                                   \
+        "v_fmac_f32_dpp %1, %4, %13 " D "\n\t"                                                                   \
+        "v_fmac_f32_dpp %0, %7, %14 " D "\n\t"                                                                   \
+        "v_fmac_f32_dpp %1, %6, %15 " D "\n\t"                                                                   \
+        "v_fmac_f32_dpp %0, %9, %16 " D "\n\t"                                                                   \
+        "v_fmac_f32_dpp %1, %8, %17 " D                                                                           \
+        : "+v"(a), "+v"(b)                                                                                       \
+        : "v"(ps[r].x), "v"(ps[r].y), "v"(ps[r + 1].x), "v"(ps[r + 1].y), "v"(ps[r + 2].x), "v"(ps[r + 2].y),     \
+          "v"(ps[r + 3].x), "v"(ps[r + 3].y), "v"(la[r].x), "v"(la[r].y), "v"(la[r + 1].x), "v"(la[r + 1].y),     \
+          "v"(la[r + 2].x), "v"(la[r + 2].y), "v"(la[r + 3].x), "v"(la[r + 3].y))
+
+// sum over the lane's amplitudes of Im conj(lam(z)) psi(z ^ bit K)
+template <int K>
+__device__ inline float xb_lane(const float2 (&ps)[WR], const float2 (&la)[WR])
+{
+    float a = 0.f, b = 0.f;
+#pragma unroll
+    for (int r = 0; r < WR; r += 4) {
+        if constexpr (K == 0) PQ_XB_LANE(PQ_DPP0);
+        else if constexpr (K == 1) PQ_XB_LANE(PQ_DPP1);
+        else if constexpr (K == 2) PQ_XB_LANE(PQ_DPP2);
+        else PQ_XB_LANE(PQ_DPP3);
+    }
+    return a - b;
+}
+
+template <int K>
+__device__ inline void rx_bit(float2 (&v)[WR], float t)
+{
+#pragma unroll
+    for (int r = 0; r < WR; ++r)
+        if (!(r & (1 << K))) rx_tan(v[r], v[r | (1 << K)], t);
+}
+
+// NB: qubits of the group (0: group 0); C: its lowest active tile bit
+template <int NB>
+constexpr int low_bit()
+{
+    return NB == 0 ? 0 : WIDE_BITS - NB;
+}
+
+// is tile bit q an active qubit of the group?
+template <int NB>
+__host__ __device__ constexpr bool active(int q)
+{
+    return q >= (NB == 0 ? 0 : WIDE_BITS - NB);
+}
+// active bits that layout L rotates: 9..13 in LLIN, 0..8 in LL1
+template <int L, int NB>
+__host__ __device__ constexpr int active_count()
+{
+    int n = 0;
+    for (int q = L == LLIN ? 9 : 0; q < (L == LLIN ? 14 : 9); ++q) n += active<NB>(q);
+    return n;
+}
+
+template <int L, int NB>
+__device__ inline void rx_round(float2 (&v)[WR], float t)
+{
+    constexpr int Q = L == LLIN ? 9 : 4;
+    if constexpr (active<NB>(Q)) rx_bit<0>(v, t);
+    if constexpr (active<NB>(Q + 1)) rx_bit<1>(v, t);
+    if constexpr (active<NB>(Q + 2)) rx_bit<2>(v, t);
+    if constexpr (active<NB>(Q + 3)) rx_bit<3>(v, t);
+    if constexpr (active<NB>(Q + 4)) rx_bit<4>(v, t);
+    if constexpr (L == LL1) {
+        if constexpr (active<NB>(3)) rx_lane<3>(v, t);
+        if constexpr (active<NB>(2)) rx_lane<2>(v, t);
+        if constexpr (active<NB>(1)) rx_lane<1>(v, t);
+        if constexpr (active<NB>(0)) rx_lane<0>(v, t);
+    }
+}
+
+// sum over one register bit of Im conj(lam(z)) psi(z ^ bit), both directions
+template <int K>
+__device__ inline float xb_bit(const float2 (&ps)[WR], const float2 (&la)[WR])
+{
+    float a0 = 0.f, a1 = 0.f;
+#pragma unroll
+    for (int r = 0; r < WR; ++r) {
+        if (r & (1 << K)) continue;
+        const int r1 = r | (1 << K);
+        a0 = fmaf(la[r].x, ps[r1].y, a0);
+        a0 = fmaf(-la[r].y, ps[r1].x, a0);
+        a1 = fmaf(la[r1].x, ps[r].y, a1);
+        a1 = fmaf(-la[r1].y, ps[r].x, a1);
+    }
+    return a0 + a1;
+}
+
+template <int L, int NB>
+__device__ inline float xb_round(const float2 (&ps)[WR], const float2 (&la)[WR])
+{
+    constexpr int Q = L == LLIN ? 9 : 4;
+    float a = 0.f;
+    if constexpr (active<NB>(Q)) a += xb_bit<0>(ps, la);
+    if constexpr (active<NB>(Q + 1)) a += xb_bit<1>(ps, la);
+    if constexpr (active<NB>(Q + 2)) a += xb_bit<2>(ps, la);
+    if constexpr (active<NB>(Q + 3)) a += xb_bit<3>(ps, la);
+    if constexpr (active<NB>(Q + 4)) a += xb_bit<4>(ps, la);
+    if constexpr (L == LL1) {
+        if constexpr (active<NB>(3)) a += xb_lane<3>(ps, la);
+        if constexpr (active<NB>(2)) a += xb_lane<2>(ps, la);
+        if constexpr (active<NB>(1)) a += xb_lane<1>(ps, la);
+        if constexpr (active<NB>(0)) a += xb_lane<0>(ps, la);
+    }
+    return a;
+}
+
+// One RX segment, LLIN -> LL1 (UP) or back.
+template <int NB, bool UP>
+__device__ inline void seg_rot(float2 (&v)[WR], float* ex, float t, uint32_t tid)
+{
+    constexpr int A = UP ? LLIN : LL1, B = UP ? LL1 : LLIN;
+    rx_round<A, NB>(v, t);
+    xchg<A, B>(ex, tid, v);
+    rx_round<B, NB>(v, t);
+}
+
+// the same, LLIN -> LL1, with whole-amplitude exchanges
+template <int NB>
+__device__ inline void seg_rot2(float2 (&v)[WR], float2* ex, float t, uint32_t tid)
+{
+    rx_round<LLIN, NB>(v, t);
+    xchg2<LLIN, LL1>(ex, tid, v);
+    rx_round<LL1, NB>(v, t);
+}
+
+// Inverse rotation of psi and lambda with the beta terms of one layout: the
+// inner products are taken before the rotations, on states scaled by
+// |f|^-done, so they are multiplied back by fsq^done.
+template <int L, int NB>
+__device__ inline void bwd_round(float2 (&ps)[WR], float2 (&la)[WR], const RxC& rc, float& wdone, double& acc)
+{
+    acc += (double)(wdone * xb_round<L, NB>(ps, la));
+    __builtin_amdgcn_sched_barrier(0);
+    rx_round<L, NB>(ps, -rc.t);
+    rx_round<L, NB>(la, -rc.t);
+#pragma unroll
+    for (int k = 0; k < active_count<L, NB>(); ++k) wdone *= rc.fsq;
+    __builtin_amdgcn_sched_barrier(0);
+}
+
+template <int NB, bool UP>
+__device__ inline void seg_bwd(float2 (&ps)[WR], float2 (&la)[WR], float2* ex, const RxC& rc, uint32_t tid,
+                               double& acc)
+{
+    constexpr int A = UP ? LLIN : LL1, B = UP ? LL1 : LLIN;
+    float wdone = 1.f;
+    bwd_round<A, NB>(ps, la, rc, wdone, acc);
+    xchg2<A, B>(ex, tid, ps);
+    xchg2<A, B>(ex, tid, la);
+    bwd_round<B, NB>(ps, la, rc, wdone, acc);
+}
+
+__device__ inline void scale_regs(float2 (&v)[WR], float2 f)
+{
+#pragma unroll
+    for (int r = 0; r < WR; ++r) v[r] = cmul(v[r], f);
+}
+
+// tile t of the group: make_geo with the group's size known
+template <int NB>
+__device__ inline Geo wide_geo(const SubDesc* sd, int g, uint32_t t)
+{
+    Geo r;
+    r.c = low_bit<NB>();
+    r.nb = NB == 0 ? WIDE_BITS : NB;
+    r.g0 = NB == 0 ? 0 : sd->gstart[g];
+    r.mir = NB == 0 ? (1u << (sd->n - 1)) - 1u : 0u;
+    if constexpr (NB == 0) {
+        r.zb = t << (WIDE_BITS - 1);
+    } else {
+        const int L = r.g0 - r.c;  // fixed bits between the passive block and the group
+        r.zb = ((t & ((1u << L) - 1u)) << r.c) | ((t >> L) << (r.g0 + NB));
+    }
+    return r;
+}
+
+template <int L, bool G0>
+__device__ inline void load_state(float2 (&v)[WR], const float2* st, const Geo& geo, uint32_t tid)
+{
+    uint32_t base = (geo.zb ^ gmapT<G0, WIDE_BITS>(geo, thread_part<L>(tid))) << 3;
+    asm volatile("" : "+v"(base));  // keeps the shift out of the per-register XOR
+#pragma unroll
+    for (int r = 0; r < WR; ++r) v[r] = at_off(st, base ^ (gmapT<G0, WIDE_BITS>(geo, reg_part<L>(r)) << 3));
+    __builtin_amdgcn_sched_barrier(0);
+}
+
+// store slot q to amplitude q ^ m
+template <int L, bool G0>
+__device__ inline void store_state(const float2 (&v)[WR], float2* st, const Geo& geo, uint32_t tid, uint32_t m)
+{
+    __builtin_amdgcn_sched_barrier(0);
+    uint32_t base =
+        (geo.zb ^ gmapT<G0, WIDE_BITS>(geo, thread_part<L>(tid)) ^ gmapT<G0, WIDE_BITS>(geo, m)) << 3;
+    asm volatile("" : "+v"(base));
+#pragma unroll
+    for (int r = 0; r < WR; ++r) at_off(st, base ^ (gmapT<G0, WIDE_BITS>(geo, reg_part<L>(r)) << 3)) = v[r];
+}
+
+// The lane's 32 cut values in LL1, two 16-bit values per word, for slots that
+// hold amplitude q ^ m, m = M (the group's bits) where flip is set, else 0: the
+// lane part of M moves the 32-entry row, its register part permutes the words.
+struct Cuts {
+    uint32_t w[WR / 2];
+    __device__ uint32_t at(int r) const { return (r & 1) ? w[r >> 1] >> 16 : w[r >> 1] & 0xFFFFu; }
+};
+
+template <uint32_t M>
+__device__ inline void load_cuts(Cuts& c, const uint8_t* tab, int width, uint32_t tid, bool flip)
+{
+    constexpr uint32_t ROW = wide_lanes(M & 15u) | (((M >> 9) & 31u) << 4), R = (M >> 4) & 31u;
+    const uint32_t row = flip ? tid ^ ROW : tid;
+    if (width == 1) {
+        const uint4* p = (const uint4*)(tab + (size_t)row * WR);
+        const uint4 a = p[0], b = p[1];
+        const uint32_t s[8] = {a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w};
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {  // bytes 0, 1 and 2, 3 to 16 bits
+            c.w[2 * i] = __builtin_amdgcn_perm(0u, s[i], 0x0C010C00u);
+            c.w[2 * i + 1] = __builtin_amdgcn_perm(0u, s[i], 0x0C030C02u);
+        }
+    } else {
+        const uint4* p = (const uint4*)(tab + (size_t)row * WR * 2);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const uint4 a = p[i];
+            c.w[4 * i] = a.x;
+            c.w[4 * i + 1] = a.y;
+            c.w[4 * i + 2] = a.z;
+            c.w[4 * i + 3] = a.w;
+        }
+    }
+    if (flip) {
+        uint32_t x[WR / 2];
+#pragma unroll
+        for (int i = 0; i < WR / 2; ++i) x[i] = c.w[i ^ (R >> 1)];
+#pragma unroll
+        for (int i = 0; i < WR / 2; ++i) c.w[i] = (R & 1u) ? (x[i] >> 16) | (x[i] << 16) : x[i];
+    }
+}
+
+__device__ inline const uint8_t* tile_tab(const uint8_t* ws, const SubDesc* sd, int g, uint32_t t)
+{
+    return (g == 0 ? ws + sd->tab : ws + sd->tabB) + (size_t)t * WIDE_TILE * sd->tabw;
+}
+
+// tile bits of the group's qubits (the ones a flip permutes)
+__host__ __device__ constexpr uint32_t group_bits(int c) { return ((uint32_t)WIDE_TILE - 1u) & ~((1u << c) - 1u); }
+
+enum { F_FIRST = 0, F_SINGLE = 1, F_MID = 2, F_LAST = 3 };
+enum { B_FUSED = 0, B_SINGLE = 1, B_MID = 2, B_LAST = 3 };
+
+}  // namespace
+
+// Forward pass. FIRST synthesises the phased |+> in LL1 and walks to LLIN;
+// MID walks to LL1, phases and walks back; SINGLE and LAST end in LL1.
+template <int NB, int KIND>
+__global__ __launch_bounds__(WT) __attribute__((amdgpu_waves_per_eu(4))) void k_fwd_wide(uint8_t* ws,
+                                                                                      const SubDesc* subs,
+                                                                                      const int2* work, PassOps ops,
+                                                                                      Partials part)
+{
+    extern __shared__ float wsm[];
+    float* ex = wsm;
+    float2* lut = (float2*)(wsm + EX_SLOTS);
+    __shared__ double red[WT / 64];
+    constexpr bool HAS_PRE = KIND != F_FIRST, HAS_PH = KIND == F_FIRST || KIND == F_MID;
+    const uint32_t tid = threadIdx.x;
+    const int2 wk = work[blockIdx.x];
+    const SubDesc* sd = subs + wk.x;
+    const uint32_t t = (uint32_t)wk.y;
+    constexpr bool G0 = NB == 0;
+    const int g = G0 ? 0 : ops.group;
+    const Geo geo = wide_geo<NB>(sd, g, t);
+    const float2* src = (const float2*)(ws + sd->psi + (uint64_t)ops.psi_in * state_bytes(sd->n));
+    float2* st = (float2*)(ws + sd->psi + (uint64_t)ops.psi_out * state_bytes(sd->n));
+    const RxCoef* cf = (const RxCoef*)(ws + sd->coef);
+    constexpr uint32_t gb = group_bits(low_bit<NB>());
+    RxC pre{}, post{};
+    if constexpr (HAS_PRE) pre = load_rx(cf, ops.pre, g);
+    if constexpr (HAS_PH) post = load_rx(cf, ops.post, g);
+    const uint32_t m_pre = (HAS_PRE && pre.flip) ? gb : 0u;
+    const uint32_t m_end = m_pre ^ ((HAS_PH && post.flip) ? gb : 0u);
+    float2 v[WR];
+    if constexpr (HAS_PRE) load_state<LLIN, G0>(v, src, geo, tid);
+    Cuts cr;
+    if constexpr (KIND != F_SINGLE)
+        load_cuts<gb>(cr, tile_tab(ws, sd, g, t), sd->tabw, tid, m_pre != 0u);  // LAST: m_pre = m_end
+    if constexpr (HAS_PH) {
+        // phase table with the factors of the segments before and after it
+        // (FIRST: and the amplitude of |+>) folded in
+        const int len = sd->lut_len;
+        const float2* L = (const float2*)(ws + sd->lut) + (size_t)ops.ph * len;
+        const float amp = (float)(1.0 / sqrt((double)(1ull << (sd->n - 1))));
+        const float2 F = HAS_PRE ? cmul(pre.Ff, post.Ff) : make_float2(amp * post.Ff.x, amp * post.Ff.y);
+        for (int i = tid; i < len; i += WT) lut[i] = cmul(L[i], F);
+        if constexpr (!HAS_PRE) __syncthreads();  // (MID: the exchange's barriers come before the table is read)
+    }
+    if constexpr (HAS_PRE) {
+        seg_rot<NB, true>(v, ex, pre.t, tid);
+        if constexpr (!HAS_PH) scale_regs(v, pre.Ff);
+    }
+    if constexpr (HAS_PH) {
+#pragma unroll
+        for (int r = 0; r < WR; ++r) {
+            const float2 f = lut[cr.at(r)];
+            v[r] = HAS_PRE ? cmul(v[r], f) : f;
+        }
+        seg_rot<NB, false>(v, ex, post.t, tid);
+        store_state<LLIN, G0>(v, st, geo, tid, m_end);
+    } else {
+        double acc = 0.0;
+        if constexpr (KIND == F_LAST) {
+#pragma unroll
+            for (int r = 0; r < WR; ++r)
+                acc += ((double)v[r].x * v[r].x + (double)v[r].y * v[r].y) * (double)cr.at(r);
+        }
+        store_state<LL1, G0>(v, st, geo, tid, m_end);
+        if constexpr (KIND == F_LAST) {
+            acc = block_sum(acc, red);
+            if (tid == 0) part.e[sd->tile_base + t] = acc;
+        }
+    }
+}
+
+// Backward pass (kinds as in sim.hip). SPSI: psi is stored too.
+template <int NB, int KIND, bool SPSI>
+__global__ __launch_bounds__(WT) __attribute__((amdgpu_waves_per_eu(2))) void k_bwd_wide(uint8_t* ws,
+                                                                                      const SubDesc* subs,
+                                                                                      const int2* work, PassOps ops,
+                                                                                      Partials part)
+{
+    extern __shared__ float2 wsm2[];
+    float2* ex = wsm2;
+    float2* lut = wsm2 + EX_SLOTS;
+    __shared__ double red[3 * WT / 64];
+    const uint32_t tid = threadIdx.x;
+    const int2 wk = work[blockIdx.x];
+    const SubDesc* sd = subs + wk.x;
+    const uint32_t t = (uint32_t)wk.y;
+    constexpr bool G0 = NB == 0;
+    const int g = G0 ? 0 : ops.group;
+    const Geo geo = wide_geo<NB>(sd, g, t);
+    float2* sp = (float2*)(ws + sd->psi + (uint64_t)ops.psi_in * state_bytes(sd->n));
+    float2* sl = (float2*)(ws + sd->lam);
+    const RxCoef* cf = (const RxCoef*)(ws + sd->coef);
+    const int T = part.total_tiles;
+    const int tile = sd->tile_base + (int)t;
+    constexpr uint32_t gb = group_bits(low_bit<NB>());
+    const RxC pre = load_rx(cf, ops.pre, g);
+    RxC post{};
+    if constexpr (KIND == B_MID) post = load_rx(cf, ops.post, g);
+    const uint32_t m_pre = pre.flip ? gb : 0u;
+    const uint32_t m_end = m_pre ^ ((KIND == B_MID && post.flip) ? gb : 0u);
+    float2 ps[WR], la[WR];
+    if constexpr (KIND != B_LAST) load_state<LLIN, G0>(ps, sp, geo, tid);
+    if constexpr (KIND != B_FUSED) load_state<LLIN, G0>(la, sl, geo, tid);
+    Cuts cr;
+    if constexpr (KIND != B_SINGLE) load_cuts<gb>(cr, tile_tab(ws, sd, g, t), sd->tabw, tid, m_pre != 0u);
+    if constexpr (KIND == B_MID || KIND == B_LAST) {
+        // MID: the conjugate phase table with the inverse factors of the
+        // segments before and after it. LAST: the phase table of layer 1 with
+        // the amplitude of |+> and the conjugate of the inverse factor of
+        // RX(pre) (every sum of that pass is bilinear in conj(lambda) and psi)
+        const int len = sd->lut_len;
+        const float2* L = (const float2*)(ws + sd->lut) + (size_t)ops.ph * len;
+        const float amp = (float)(1.0 / sqrt((double)(1ull << (sd->n - 1))));
+        const float2 F = KIND == B_MID ? cmul(pre.Fi, post.Fi) : make_float2(amp * pre.Fi.x, -amp * pre.Fi.y);
+        for (int i = tid; i < len; i += WT) {
+            const float2 e = L[i];
+            lut[i] = cmul(make_float2(e.x, KIND == B_MID ? -e.y : e.y), F);
+        }
+    }
+    double acc_pre = 0.0, acc_ph = 0.0, acc_post = 0.0, acc_e = 0.0;
+    if constexpr (KIND == B_LAST) {
+        seg_rot2<NB>(la, ex, -pre.t, tid);
+        float a = 0.f;
+#pragma unroll
+        for (int r = 0; r < WR; ++r) {
+            const uint32_t c = cr.at(r);
+            ps[r] = lut[c];
+            a = fmaf((float)c, fmaf(la[r].x, ps[r].y, -la[r].y * ps[r].x), a);
+        }
+        acc_ph = (double)a;
+        // beta terms in both layouts
+        acc_pre += (double)xb_round<LL1, NB>(ps, la);
+        xchg2<LL1, LLIN>(ex, tid, ps);
+        xchg2<LL1, LLIN>(ex, tid, la);
+        acc_pre += (double)xb_round<LLIN, NB>(ps, la);
+    } else if constexpr (KIND == B_FUSED) {
+        seg_rot2<NB>(ps, ex, pre.t, tid);
+        scale_regs(ps, pre.Ff);
+#pragma unroll
+        for (int r = 0; r < WR; ++r) {
+            const uint32_t ci = cr.at(r);
+            const float c = (float)ci;
+            acc_e += ((double)ps[r].x * ps[r].x + (double)ps[r].y * ps[r].y) * (double)ci;
+            la[r] = make_float2(c * ps[r].x, c * ps[r].y);
+        }
+        seg_bwd<NB, false>(ps, la, ex, pre, tid, acc_pre);
+        scale_regs(la, pre.Fi);
+        store_state<LLIN, G0>(la, sl, geo, tid, 0u);
+    } else {
+        seg_bwd<NB, true>(ps, la, ex, pre, tid, acc_pre);
+        if constexpr (KIND == B_SINGLE) {
+            if constexpr (SPSI) {
+                scale_regs(ps, pre.Fi);
+                store_state<LL1, G0>(ps, sp, geo, tid, m_end);
+            }
+            scale_regs(la, pre.Fi);
+            store_state<LL1, G0>(la, sl, geo, tid, m_end);
+        } else {
+            float a = 0.f;
+#pragma unroll
+            for (int r = 0; r < WR; ++r)
+                a = fmaf((float)cr.at(r), fmaf(la[r].x, ps[r].y, -la[r].y * ps[r].x), a);
+            acc_ph = (double)a * (double)(pre.Fi.x * pre.Fi.x + pre.Fi.y * pre.Fi.y);
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int r = 0; r < WR; ++r) {
+                const float2 f = lut[cr.at(r)];
+                ps[r] = cmul(ps[r], f);
+                la[r] = cmul(la[r], f);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+            seg_bwd<NB, false>(ps, la, ex, post, tid, acc_post);
+            acc_post /= (double)post.Fi.x * post.Fi.x + (double)post.Fi.y * post.Fi.y;
+            if constexpr (SPSI) store_state<LLIN, G0>(ps, sp, geo, tid, m_end);
+            store_state<LLIN, G0>(la, sl, geo, tid, m_end);
+        }
+    }
+    double s0 = KIND == B_FUSED ? acc_e : acc_ph, s1 = acc_pre, s2 = acc_post;
+    block_sum3(s0, s1, s2, red);
+    if (tid == 0) {
+        if constexpr (KIND == B_FUSED) part.e[tile] = s0;
+        if constexpr (KIND == B_MID || KIND == B_LAST) part.gg[(size_t)ops.ph * T + tile] = s0;
+        part.gb[((size_t)ops.pre * MAX_GROUPS + g) * T + tile] = s1;
+        if constexpr (KIND == B_MID) part.gb[((size_t)ops.post * MAX_GROUPS + g) * T + tile] = s2;
+    }
+}
+
+// ---------------------------------------------------------------------------
+// launchers. Chain codes: 3 = group 0, 7..12 = a strided group of that many
+// qubits (the even splits of 21..26, 29 and 30 qubits).
+// ---------------------------------------------------------------------------
+#define PQ_WIDE(KERNEL, ...)                                                                                        \
+    do {                                                                                                            \
+        switch (chain) {                                                                                            \
+        case 3: hipLaunchKernelGGL((KERNEL<0, __VA_ARGS__>), g, b, lds, s, ws, subs, work, ops, part); break;       \
+        case 7: hipLaunchKernelGGL((KERNEL<7, __VA_ARGS__>), g, b, lds, s, ws, subs, work, ops, part); break;       \
+        case 8: hipLaunchKernelGGL((KERNEL<8, __VA_ARGS__>), g, b, lds, s, ws, subs, work, ops, part); break;       \
+        case 9: hipLaunchKernelGGL((KERNEL<9, __VA_ARGS__>), g, b, lds, s, ws, subs, work, ops, part); break;       \
+        case 10: hipLaunchKernelGGL((KERNEL<10, __VA_ARGS__>), g, b, lds, s, ws, subs, work, ops, part); break;     \
+        case 11: hipLaunchKernelGGL((KERNEL<11, __VA_ARGS__>), g, b, lds, s, ws, subs, work, ops, part); break;     \
+        case 12: hipLaunchKernelGGL((KERNEL<12, __VA_ARGS__>), g, b, lds, s, ws, subs, work, ops, part); break;     \
+        default: return hipErrorInvalidValue;                                                                       \
+        }                                                                                                           \
+    } while (0)
+
+hipError_t launch_fwd_wide(uint8_t* ws, const SubDesc* subs, const int2* work, int nwork, int chain, PassOps ops,
+                           Partials part, int lut_max, hipStream_t s)
+{
+    if (nwork <= 0) return hipSuccess;
+    const size_t lds = EX_SLOTS * sizeof(float) + (size_t)lut_max * sizeof(float2);
+    const dim3 g(nwork), b(WT);
+    if (ops.init) {
+        if (chain != 3) return hipErrorInvalidValue;
+        hipLaunchKernelGGL((k_fwd_wide<0, F_FIRST>), g, b, lds, s, ws, subs, work, ops, part);
+    } else if (ops.epi_e) PQ_WIDE(k_fwd_wide, F_LAST);
+    else if (ops.ph >= 0) PQ_WIDE(k_fwd_wide, F_MID);
+    else PQ_WIDE(k_fwd_wide, F_SINGLE);
+    return hipGetLastError();
+}
+
+hipError_t launch_bwd_wide(uint8_t* ws, const SubDesc* subs, const int2* work, int nwork, int chain, PassOps ops,
+                           Partials part, int lut_max, hipStream_t s)
+{
+    if (nwork <= 0) return hipSuccess;
+    const size_t lds = EX_SLOTS * sizeof(float2) + (size_t)lut_max * sizeof(float2);
+    const dim3 g(nwork), b(WT);
+    if (ops.last) {
+        // the last pass mirrors the first forward pass (group 0 of layer 1)
+        if (ops.group != 0 || chain != 3) return hipErrorInvalidValue;
+        hipLaunchKernelGGL((k_bwd_wide<0, B_LAST, false>), g, b, lds, s, ws, subs, work, ops, part);
+    } else if (ops.fused) PQ_WIDE(k_bwd_wide, B_FUSED, false);
+    else if (ops.ph >= 0 && ops.nopsi) PQ_WIDE(k_bwd_wide, B_MID, false);
+    else if (ops.ph >= 0) PQ_WIDE(k_bwd_wide, B_MID, true);
+    else if (ops.nopsi) PQ_WIDE(k_bwd_wide, B_SINGLE, false);
+    else PQ_WIDE(k_bwd_wide, B_SINGLE, true);
+    return hipGetLastError();
+}
+
+}  // namespace pq
