@@ -1,0 +1,56 @@
+// Phase-table entries and rotation parameters of a set of angles: FP64
+// products, sine and cosine, rounded to FP32.
+#pragma once
+
+#include "common.h"
+
+namespace pq {
+
+__device__ inline void cpow_d(double re, double im, int e, double& ore, double& oim)
+{
+    double r = 1.0, i = 0.0;
+    for (int k = 0; k < e; ++k) {
+        const double nr = r * re - i * im, ni = r * im + i * re;
+        r = nr;
+        i = ni;
+    }
+    ore = r;
+    oim = i;
+}
+
+// e^{-i gamma c}
+__device__ inline float2 lut_entry(int c, double gm)
+{
+    double sv, cv;
+    sincos(gm * (double)c, &sv, &cv);
+    return make_float2((float)cv, (float)(-sv));
+}
+
+// rotation parameters of one layer
+__device__ inline RxCoef rx_coef(const SubDesc* sd, double bt)
+{
+    double s, c;
+    sincos(bt, &s, &c);
+    RxCoef rc;
+    rc.cs = make_float2((float)c, (float)s);
+    // e^{-i beta X} = c (I - i tan(beta) X)            when |cos| >= |sin|
+    //               = -i s X (I + i cot(beta) X)       otherwise
+    // i.e. f (I - i t X) X^flip with (f, t) = (c, tan) or (-i s, -cot)
+    const bool tanm = fabs(c) >= fabs(s);
+    rc.mode = tanm ? 0 : 1;
+    rc.t = (float)(tanm ? s / c : -c / s);
+    rc.fsq = (float)(tanm ? c * c : s * s);
+    // per-qubit factors: forward c or -i s, inverse c or +i s
+    const double fr = tanm ? c : 0.0, fi_f = tanm ? 0.0 : -s, fi_i = tanm ? 0.0 : s;
+    for (int g = 0; g < MAX_GROUPS; ++g) {
+        const int nq = g < sd->ngroups ? sd->gsize[g] : 0;
+        double r, i;
+        cpow_d(fr, fi_f, nq, r, i);
+        rc.Ff[g] = make_float2((float)r, (float)i);
+        cpow_d(fr, fi_i, nq, r, i);
+        rc.Fi[g] = make_float2((float)r, (float)i);
+    }
+    return rc;
+}
+
+}  // namespace pq

@@ -201,6 +201,8 @@ struct Plan {
              o_pgb = 0,
              o_pgg = 0, o_keys = 0, total = 0;
     int nsmall = 0;
+    int small_n = 0, small_len = 0;  // largest qubit count and phase table of the small ones
+    bool only_small = false;         // every subgraph is run by the small-subgraph kernel
     // host images of the metadata regions
     std::vector<int2> work_all;
     std::vector<int32_t> small;
@@ -445,7 +447,14 @@ qaoa_status_t make_plan(int32_t B, const int32_t* nq, const int64_t* eoff, const
     }
     for (int b = 0; b < B; ++b)
         if (P.subs[b].ngroups == 1 && !P.subs[b].skip) P.small.push_back(b);
+    // the longest first
+    std::stable_sort(P.small.begin(), P.small.end(), [&](int a, int c) { return P.subs[a].n > P.subs[c].n; });
     P.nsmall = (int)P.small.size();
+    P.only_small = P.nsmall == B;
+    for (int b : P.small) {
+        P.small_n = std::max(P.small_n, (int)P.subs[b].n);
+        P.small_len = std::max(P.small_len, (int)P.subs[b].lut_len);
+    }
 
     // regions
     uint64_t o = 0;
@@ -726,6 +735,14 @@ static qaoa_status_t for_each_class(qaoa_batch_t h, int32_t p, hipStream_t st, F
     return s;
 }
 
+// the small-subgraph kernel over the batch's small subgraphs
+static hipError_t small_subgraphs(qaoa_batch_t h, bool grad, const SmallArgs& a, hipStream_t st)
+{
+    const Plan& P = h->P;
+    return launch_small(h->ws, h->d_subs, (const int32_t*)(h->ws + P.o_small), P.nsmall, P.small_n, P.small_len, grad,
+                        a, h->part, st);
+}
+
 extern "C" const char* qaoa_status_string(qaoa_status_t s)
 {
     switch (s) {
@@ -858,15 +875,14 @@ extern "C" qaoa_status_t qaoa_apply_layers(qaoa_batch_t h, int32_t p, const doub
     if (s != QAOA_OK) return s;
     hipStream_t st = (hipStream_t)stream;
     Plan& P = h->P;
-    {
+    if (!P.classes.empty()) {
         ProfScope ps("angle_prep", st, angle_bytes(P, p));
         HIP_TRY(launch_angle_prep(h->ws, h->d_subs, P.B, p, d_gamma, d_beta, st));
     }
     s = for_each_class(h, p, st, [&](int k, hipStream_t cs) -> qaoa_status_t {
         if (k < 0) {
             ProfScope ps("small", cs, small_bytes(P, p, false));
-            HIP_TRY(launch_small(h->ws, h->d_subs, (const int32_t*)(h->ws + P.o_small), P.nsmall, p, 0, h->part,
-                                 P.lut_max, cs));
+            HIP_TRY(small_subgraphs(h, false, SmallArgs{p, P.B, 0, 0, 0, d_gamma, d_beta}, cs));
             return QAOA_OK;
         }
         const auto& c = P.classes[k];
@@ -922,14 +938,14 @@ extern "C" qaoa_status_t qaoa_topk(qaoa_batch_t h, int32_t k, uint32_t* d_idx, f
 }
 
 // one class's tile passes of a gradient evaluation (forward sweep, fused
-// turn, adjoint sweep), or the small-subgraph kernel (k < 0)
-static qaoa_status_t enqueue_class_grad(qaoa_batch_t h, int k, int32_t p, hipStream_t st)
+// turn, adjoint sweep), or the small-subgraph kernel (k < 0) with its arguments
+static qaoa_status_t enqueue_class_grad(qaoa_batch_t h, int k, int32_t p, const SmallArgs& a, hipStream_t st)
 {
     Plan& P = h->P;
     if (k < 0) {
+        if (a.iters > 0) return QAOA_OK;  // the optimiser has run them
         ProfScope ps("small", st, small_bytes(P, p, true));
-        HIP_TRY(launch_small(h->ws, h->d_subs, (const int32_t*)(h->ws + P.o_small), P.nsmall, p, 1, h->part,
-                             P.lut_max, st));
+        HIP_TRY(small_subgraphs(h, true, a, st));
         return QAOA_OK;
     }
     {
@@ -984,9 +1000,9 @@ static qaoa_status_t enqueue_class_grad(qaoa_batch_t h, int k, int32_t p, hipStr
 
 // the small-subgraph kernel and every tile pass of one gradient evaluation
 // (forward sweep, fused turn, adjoint sweep), after the angle tables are set
-static qaoa_status_t enqueue_grad_passes(qaoa_batch_t h, int32_t p, hipStream_t st)
+static qaoa_status_t enqueue_grad_passes(qaoa_batch_t h, int32_t p, const SmallArgs& a, hipStream_t st)
 {
-    return for_each_class(h, p, st, [&](int k, hipStream_t cs) { return enqueue_class_grad(h, k, p, cs); });
+    return for_each_class(h, p, st, [&](int k, hipStream_t cs) { return enqueue_class_grad(h, k, p, a, cs); });
 }
 
 extern "C" qaoa_status_t qaoa_expectation_grad(qaoa_batch_t h, int32_t p, const double* d_gamma,
@@ -1000,13 +1016,19 @@ extern "C" qaoa_status_t qaoa_expectation_grad(qaoa_batch_t h, int32_t p, const 
     if (!d_E || !d_dgamma || !d_dbeta) return fail(QAOA_ERR_INVALID_ARG, "output pointers are NULL");
     hipStream_t st = (hipStream_t)stream;
     Plan& P = h->P;
-    {
+    if (!P.classes.empty()) {
         ProfScope ps("angle_prep", st, angle_bytes(P, p));
         HIP_TRY(launch_angle_prep(h->ws, h->d_subs, P.B, p, d_gamma, d_beta, st));
     }
-    s = enqueue_grad_passes(h, p, st);
+    SmallArgs a{p, P.B, 0, 0, 0, d_gamma, d_beta};
+    if (P.only_small) {  // one tile per subgraph: nothing to reduce
+        a.E = d_E;
+        a.dgamma = d_dgamma;
+        a.dbeta = d_dbeta;
+    }
+    s = enqueue_grad_passes(h, p, a, st);
     if (s != QAOA_OK) return s;
-    {
+    if (!P.only_small) {
         ProfScope ps("reduce", st, 8.0 * P.total_tiles * (1.0 + p * (MAX_GROUPS + 1.0)));
         HIP_TRY(launch_reduce(h->d_subs, P.B, p, 1, h->part, d_E, d_dgamma, d_dbeta, st));
     }
@@ -1036,12 +1058,28 @@ extern "C" qaoa_status_t qaoa_optimize(qaoa_batch_t h, int32_t p, int32_t iters,
     hipStream_t st = (hipStream_t)stream;
     Plan& P = h->P;
     const size_t BP = (size_t)P.B * p;
-    {
+    // the small subgraphs' steps all run in one launch; the tiled ones' step by
+    // step
+    SmallArgs a{p, P.B, iters};
+    a.E = d_E;
+    a.theta = d_theta;
+    a.m = d_m;
+    a.v = d_v;
+    a.step = d_step;
+    a.lr = lr;
+    a.b1 = beta1;
+    a.b2 = beta2;
+    a.eps = eps;
+    if (P.nsmall) {
+        ProfScope ps("small", st, iters * small_bytes(P, p, true));
+        HIP_TRY(small_subgraphs(h, true, a, st));
+    }
+    if (!P.only_small) {
         ProfScope ps("angle_prep", st, angle_bytes(P, p));
         HIP_TRY(launch_angle_prep(h->ws, h->d_subs, P.B, p, d_theta, d_theta + BP, st));
     }
-    for (int it = 0; it < iters; ++it) {
-        s = enqueue_grad_passes(h, p, st);
+    for (int it = 0; it < iters && !P.only_small; ++it) {
+        s = enqueue_grad_passes(h, p, a, st);
         if (s != QAOA_OK) return s;
         ProfScope ps("reduce_adam", st,
                      8.0 * P.total_tiles * (1.0 + p * (MAX_GROUPS + 1.0)) + 7.0 * 8.0 * 2.0 * BP + angle_bytes(P, p));

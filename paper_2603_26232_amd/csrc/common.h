@@ -182,8 +182,21 @@ hipError_t launch_fwd_pass(uint8_t* ws, const SubDesc* subs, const int2* work, i
                            PassOps ops, Partials part, int lut_max, int prec, hipStream_t s);
 hipError_t launch_bwd_pass(uint8_t* ws, const SubDesc* subs, const int2* work, int nwork, int chain,
                            PassOps ops, Partials part, int lut_max, hipStream_t s);
-hipError_t launch_small(uint8_t* ws, const SubDesc* subs, const int32_t* list, int nlist, int p,
-                        int grad, Partials part, int lut_max, hipStream_t s);
+// ---- launchers (small.hip) ----
+// Arguments of the whole-state kernel: angles [B*p]; outputs that may be NULL;
+// with iters > 0 theta, m, v [2*B*p] and the Adam constants (then gamma and
+// beta are not read). The lut fields are the launcher's.
+struct SmallArgs {
+    int32_t p, B, iters, lut_cap;
+    uint32_t lut_at;
+    const double *gamma, *beta;
+    double *E, *dgamma, *dbeta;
+    double *theta, *m, *v;
+    const int32_t* step;
+    double lr, b1, b2, eps;
+};
+hipError_t launch_small(uint8_t* ws, const SubDesc* subs, const int32_t* list, int nlist, int max_n, int max_len,
+                        bool grad, SmallArgs A, Partials part, hipStream_t s);
 // ---- launchers (wide.hip) ----
 // chain: 3: group 0; 7..12: a strided group of that many qubits
 hipError_t launch_fwd_wide(uint8_t* ws, const SubDesc* subs, const int2* work, int nwork, int chain,

@@ -3,7 +3,7 @@
 // set of angles, the fixed-order reduction of the per-tile gradient and <C>
 // partials that the tile passes write, and the fused optimiser step
 // (reduction + Adam + the next step's tables).
-#include "common.h"
+#include "angles.h"
 
 namespace pq {
 
@@ -12,53 +12,18 @@ namespace pq {
 // FP64 sine/cosine, rounded to complex64; the rotation parameters of the
 // layer in FP64, rounded to float.
 // ---------------------------------------------------------------------------
-__device__ inline void cpow_d(double re, double im, int e, double& ore, double& oim)
-{
-    double r = 1.0, i = 0.0;
-    for (int k = 0; k < e; ++k) {
-        const double nr = r * re - i * im, ni = r * im + i * re;
-        r = nr;
-        i = ni;
-    }
-    ore = r;
-    oim = i;
-}
-
 // entry c of layer l's phase table: e^{-i gamma c} (c = 0 .. weight sum).
 // This and prep_coef are compiled once (not inlined), so the standalone table
 // kernel and the fused optimiser kernel produce the same bits.
 __device__ __noinline__ void prep_lut_entry(uint8_t* ws, const SubDesc* sd, int l, int c, double gm)
 {
-    double sv, cv;
-    sincos(gm * (double)c, &sv, &cv);
-    ((float2*)(ws + sd->lut))[(size_t)l * sd->lut_len + c] = make_float2((float)cv, (float)(-sv));
+    ((float2*)(ws + sd->lut))[(size_t)l * sd->lut_len + c] = lut_entry(c, gm);
 }
 
 // rotation parameters of layer l (one thread)
 __device__ __noinline__ void prep_coef(uint8_t* ws, const SubDesc* sd, int l, double bt)
 {
-    double s, c;
-    sincos(bt, &s, &c);
-    RxCoef rc;
-    rc.cs = make_float2((float)c, (float)s);
-    // e^{-i beta X} = c (I - i tan(beta) X)            when |cos| >= |sin|
-    //               = -i s X (I + i cot(beta) X)       otherwise
-    // i.e. f (I - i t X) X^flip with (f, t) = (c, tan) or (-i s, -cot)
-    const bool tanm = fabs(c) >= fabs(s);
-    rc.mode = tanm ? 0 : 1;
-    rc.t = (float)(tanm ? s / c : -c / s);
-    rc.fsq = (float)(tanm ? c * c : s * s);
-    // per-qubit factors: forward c or -i s, inverse c or +i s
-    const double fr = tanm ? c : 0.0, fi_f = tanm ? 0.0 : -s, fi_i = tanm ? 0.0 : s;
-    for (int g = 0; g < MAX_GROUPS; ++g) {
-        const int nq = g < sd->ngroups ? sd->gsize[g] : 0;
-        double r, i;
-        cpow_d(fr, fi_f, nq, r, i);
-        rc.Ff[g] = make_float2((float)r, (float)i);
-        cpow_d(fr, fi_i, nq, r, i);
-        rc.Fi[g] = make_float2((float)r, (float)i);
-    }
-    ((RxCoef*)(ws + sd->coef))[l] = rc;
+    ((RxCoef*)(ws + sd->coef))[l] = rx_coef(sd, bt);
 }
 
 __global__ __launch_bounds__(THREADS) void k_angle_prep(uint8_t* ws, const SubDesc* subs, int p,
@@ -66,6 +31,7 @@ __global__ __launch_bounds__(THREADS) void k_angle_prep(uint8_t* ws, const SubDe
 {
     const int b = blockIdx.x / p, l = blockIdx.x % p;
     const SubDesc* sd = subs + b;
+    if (sd->ngroups == 1 || sd->skip) return;  // the small kernel builds its own tables
     const double gm = gamma[(size_t)b * p + l];
     for (int c = threadIdx.x; c < sd->lut_len; c += THREADS) prep_lut_entry(ws, sd, l, c, gm);
     if (threadIdx.x == 0) prep_coef(ws, sd, l, beta[(size_t)b * p + l]);
@@ -127,6 +93,7 @@ __global__ __launch_bounds__(THREADS) void k_reduce_adam(uint8_t* ws, const SubD
     __shared__ double s_gamma, s_beta;
     const int b = blockIdx.x / p, l = blockIdx.x % p;
     const SubDesc* sd = subs + b;
+    if (sd->ngroups == 1 && !sd->skip) return;  // the small kernel runs its own steps
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
     const int32_t t = *step + it + 1;
     const int T = part.total_tiles, tb = sd->tile_base, nt = partials_of(sd), G = sd->ngroups;

@@ -891,121 +891,6 @@ __global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu((KIND =
 }
 
 // ---------------------------------------------------------------------------
-// Subgraphs with n <= 13: one workgroup runs the whole circuit (and, with
-// grad, the whole adjoint sweep) in LDS, one qubit at a time, with the
-// plain (cos, sin) form of each rotation.
-// ---------------------------------------------------------------------------
-__device__ inline void rx_pair(float2& a, float2& b, float c, float s)
-{
-    const float2 na = make_float2(c * a.x + s * b.y, c * a.y - s * b.x);
-    const float2 nb = make_float2(c * b.x + s * a.y, c * b.y - s * a.x);
-    a = na;
-    b = nb;
-}
-
-__global__ __launch_bounds__(THREADS) void k_small(uint8_t* ws, const SubDesc* subs, const int32_t* list,
-                                                   int p, int grad, Partials part)
-{
-    extern __shared__ float2 smem[];
-    __shared__ double red[THREADS / 64];
-    const uint32_t tid = threadIdx.x;
-    const SubDesc* sd = subs + list[blockIdx.x];
-    const int n = sd->n;
-    // the reduced state: qubits 0..n-2 act on the index bits, the top qubit's
-    // X on an index pairs it with its complement (dim - 1 - index); for n = 1
-    // that pair is the single amplitude itself
-    const uint32_t dim = 1u << (n - 1), half = dim >> 1, comp = dim - 1;
-    float2* ps = smem;
-    float2* la = smem + TILE;
-    float2* lut = smem + (grad ? 2 * TILE : TILE);
-    const CutTab tab{ws + sd->tab, sd->tabw};
-    const RxCoef* cf = (const RxCoef*)(ws + sd->coef);
-    const float2* luts = (const float2*)(ws + sd->lut);
-    const int lut_len = sd->lut_len;
-    const int T = part.total_tiles;
-    const int tile = sd->tile_base;
-
-    const float a0 = (float)(1.0 / sqrt((double)dim));
-    for (uint32_t z = tid; z < dim; z += THREADS) ps[z] = make_float2(a0, 0.f);
-    for (int l = 0; l < p; ++l) {
-        __syncthreads();
-        for (int i = tid; i < lut_len; i += THREADS) lut[i] = luts[(size_t)l * lut_len + i];
-        __syncthreads();
-        for (uint32_t z = tid; z < dim; z += THREADS) ps[z] = cmul(ps[z], lut[tab.at(z)]);
-        const float2 cs = cf[l].cs;
-        for (int j = 0; j < n - 1; ++j) {
-            __syncthreads();
-            for (uint32_t i = tid; i < half; i += THREADS) {
-                const uint32_t z = ((i >> j) << (j + 1)) | (i & ((1u << j) - 1u));
-                rx_pair(ps[z], ps[z | (1u << j)], cs.x, cs.y);
-            }
-        }
-        __syncthreads();
-        for (uint32_t i = tid; i < half; i += THREADS) rx_pair(ps[i], ps[i ^ comp], cs.x, cs.y);
-        if (dim == 1 && tid == 0) ps[0] = cmul(ps[0], make_float2(cs.x, -cs.y));
-    }
-    __syncthreads();
-    double acc = 0.0;
-    for (uint32_t z = tid; z < dim; z += THREADS)
-        acc += ((double)ps[z].x * ps[z].x + (double)ps[z].y * ps[z].y) * (double)tab.at(z);
-    acc = block_sum(acc, red);
-    if (tid == 0) part.e[tile] = acc;
-    if (!grad) {
-        float2* st = (float2*)(ws + sd->psi);
-        for (uint32_t z = tid; z < dim; z += THREADS) st[z] = ps[z];
-        return;
-    }
-    for (uint32_t z = tid; z < dim; z += THREADS) {
-        const float c = (float)tab.at(z);
-        la[z] = make_float2(c * ps[z].x, c * ps[z].y);
-    }
-    for (int l = p - 1; l >= 0; --l) {
-        const float2 cs = cf[l].cs;
-        double xb = 0.0;
-        // the top qubit (complement pairs) first, then qubits n-2..0
-        for (int j = n - 1; j >= 0; --j) {
-            __syncthreads();
-            float a = 0.f;
-            if (j == n - 1 && dim == 1) {
-                if (tid == 0) {
-                    a += la[0].x * ps[0].y - la[0].y * ps[0].x;
-                    ps[0] = cmul(ps[0], make_float2(cs.x, cs.y));
-                    la[0] = cmul(la[0], make_float2(cs.x, cs.y));
-                }
-            } else {
-                for (uint32_t i = tid; i < half; i += THREADS) {
-                    const uint32_t z = j == n - 1 ? i : ((i >> j) << (j + 1)) | (i & ((1u << j) - 1u));
-                    const uint32_t z1 = j == n - 1 ? i ^ comp : z | (1u << j);
-                    a += la[z].x * ps[z1].y - la[z].y * ps[z1].x;
-                    a += la[z1].x * ps[z].y - la[z1].y * ps[z].x;
-                    rx_pair(ps[z], ps[z1], cs.x, -cs.y);
-                    rx_pair(la[z], la[z1], cs.x, -cs.y);
-                }
-            }
-            xb += (double)a;
-        }
-        __syncthreads();
-        xb = block_sum(xb, red);
-        if (tid == 0) part.gb[((size_t)l * MAX_GROUPS + 0) * T + tile] = xb;
-        double gg = 0.0;
-        for (uint32_t z = tid; z < dim; z += THREADS)
-            gg += (double)((float)tab.at(z) * (la[z].x * ps[z].y - la[z].y * ps[z].x));
-        gg = block_sum(gg, red);
-        if (tid == 0) part.gg[(size_t)l * T + tile] = gg;
-        if (l > 0) {
-            for (int i = tid; i < lut_len; i += THREADS) lut[i] = luts[(size_t)l * lut_len + i];
-            __syncthreads();
-            for (uint32_t z = tid; z < dim; z += THREADS) {
-                float2 f = lut[tab.at(z)];
-                f.y = -f.y;
-                ps[z] = cmul(ps[z], f);
-                la[z] = cmul(la[z], f);
-            }
-        }
-    }
-}
-
-// ---------------------------------------------------------------------------
 // launchers
 // ---------------------------------------------------------------------------
 hipError_t launch_cut_tables(uint8_t* ws, const SubDesc* subs, const int2* work, int nwork, hipStream_t s)
@@ -1089,15 +974,6 @@ hipError_t launch_bwd_pass(uint8_t* ws, const SubDesc* subs, const int2* work, i
     else if (ops.ph >= 0) PQ_LAUNCH_CH(k_bwd_pass, B_MID);
     else if (ops.nopsi) PQ_LAUNCH_CH2(k_bwd_pass, B_SINGLE, false);
     else PQ_LAUNCH_CH(k_bwd_pass, B_SINGLE);
-    return hipGetLastError();
-}
-
-hipError_t launch_small(uint8_t* ws, const SubDesc* subs, const int32_t* list, int nlist, int p, int grad,
-                        Partials part, int lut_max, hipStream_t s)
-{
-    if (nlist <= 0) return hipSuccess;
-    const size_t lds = (size_t)((grad ? 2 : 1) * TILE + lut_max) * sizeof(float2);
-    hipLaunchKernelGGL(k_small, dim3(nlist), dim3(THREADS), lds, s, ws, subs, list, p, grad, part);
     return hipGetLastError();
 }
 

@@ -1,0 +1,533 @@
+// Subgraphs of at most 13 qubits: one workgroup runs the whole circuit, the
+// whole gradient, or the whole angle optimisation of its subgraph with the
+// state in registers (paper Sec. 2.2; the reduced state has 2^(n-1) <= 4096
+// amplitudes).
+//
+// What bounds it is latency: a subgraph's state fits one CU many times over,
+// and every layer is a chain of n rotations. So a layer has no pass over LDS
+// per qubit: 64 lanes x R registers hold the state, register bits rotate in
+// registers, index bits 0..3 across the lanes of a row by DPP (lane.h), bits 4
+// and 5 by swapping lane halves of register pairs (v_permlane16/32_swap). Up
+// to 10 qubits fit one wave (R = 2^(n-7)) and never wait at a barrier; 11 and 12
+// take four waves (R = 2^(n-9)) and 13 eight (R = 8), whose number is two or
+// three more index bits: they trade places with register bits through LDS once
+// per layer, one barrier forward. The top qubit's X maps an index to its complement; its partner
+// amplitude is read in that same exchange (one wave: by a lane permutation).
+//
+// Rotations are in the factored form e^{-i beta X} = f (I - i t X) X^flip. The
+// n flips of a layer cancel here: together they complement the index and the
+// top qubit's flip complements it back. f^n sits in the phase table, which the
+// workgroup builds itself from the angles (FP64 products, sine and cosine).
+// Gradient terms are FP32 sums per lane and index bit, FP64 beyond.
+//
+// Measured at p = 3, one subgraph, against one rotation per pass over LDS by 256
+// lanes: forward 46.8 -> 9.1 us at 13 qubits (28.0 -> 8.4 at 12), an optimiser
+// step 120 -> 19.4 us at 13, 69 -> 14 at 12, 31 -> 11 at 10, 19 -> 4.3 at 4; 512
+// subgraphs of 13 qubits 138 -> 32.5 us a step.
+//
+// The optimiser runs all its steps in one launch: subgraphs are independent,
+// so theta, the moments and the tables never leave the CU between steps.
+#include "angles.h"
+#include "lane.h"
+
+namespace pq {
+
+namespace {
+
+constexpr int ST = 512;  // threads at most
+constexpr int STEPS = 64;  // steps whose bias corrections are computed at a time
+
+template <int X>
+constexpr int log2c()
+{
+    return X == 8 ? 3 : X == 4 ? 2 : X == 2 ? 1 : 0;
+}
+
+// W waves: index of (register, wave, lane) in the exchange buffer
+template <int W>
+__device__ inline uint32_t xslot(uint32_t r, uint32_t w, uint32_t lane)
+{
+    return (r * W + w) * 64 + lane;
+}
+
+// Orders LDS accesses of the workgroup: a barrier between waves; within one
+// wave the LDS keeps issue order, so only the compiler has to.
+template <int W>
+__device__ inline void sync()
+{
+    if constexpr (W > 1) __syncthreads();
+    else asm volatile("" ::: "memory");
+}
+
+// (I - i t X) on registers that differ in bit K
+template <int K, int R>
+__device__ inline void rx_reg(float2 (&v)[R], float t)
+{
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        if (r & (1 << K)) continue;
+        const float2 a = v[r], b = v[r | (1 << K)];
+        v[r] = make_float2(fmaf(t, b.y, a.x), fmaf(-t, b.x, a.y));
+        v[r | (1 << K)] = make_float2(fmaf(t, a.y, b.x), fmaf(-t, a.x, b.y));
+    }
+}
+template <int K, int R>
+__device__ inline float xb_reg(const float2 (&ps)[R], const float2 (&la)[R])
+{
+    float a = 0.f, b = 0.f;
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        a = fmaf(la[r].x, ps[r ^ (1 << K)].y, a);
+        b = fmaf(la[r].y, ps[r ^ (1 << K)].x, b);
+    }
+    return a - b;
+}
+
+// exchanges lane bit 4 (H = 16) or 5 (H = 32) with register bit 0
+template <int H, int R>
+__device__ inline void swap_lanes(float2 (&v)[R])
+{
+#pragma unroll
+    for (int r = 0; r < R; r += 2) {
+        swap_halves<H>(v[r].x, v[r + 1].x);
+        swap_halves<H>(v[r].y, v[r + 1].y);
+    }
+}
+
+// the other lane's amplitudes (single registers: no pair to swap)
+template <int R>
+__device__ inline void lanes_xor(float2 (&o)[R], const float2 (&v)[R], int mask)
+{
+#pragma unroll
+    for (int r = 0; r < R; ++r) o[r] = make_float2(__shfl_xor(v[r].x, mask), __shfl_xor(v[r].y, mask));
+}
+template <int R>
+__device__ inline void rx_with(float2 (&v)[R], const float2 (&o)[R], float t)
+{
+#pragma unroll
+    for (int r = 0; r < R; ++r) v[r] = make_float2(fmaf(t, o[r].y, v[r].x), fmaf(-t, o[r].x, v[r].y));
+}
+template <int R>
+__device__ inline float xb_with(const float2 (&o)[R], const float2 (&la)[R])
+{
+    float a = 0.f, b = 0.f;
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        a = fmaf(la[r].x, o[r].y, a);
+        b = fmaf(la[r].y, o[r].x, b);
+    }
+    return a - b;
+}
+
+// Forward rotation of every index bit in the wave: lane bits nl (6, or n - 1
+// below 7 qubits) and register bits.
+template <int R>
+__device__ inline void rotate(float2 (&v)[R], float t, int nl)
+{
+    constexpr int K = log2c<R>();
+    if (nl > 0) rx_lane<0>(v, t);
+    if (nl > 1) rx_lane<1>(v, t);
+    if (nl > 2) rx_lane<2>(v, t);
+    if (nl > 3) rx_lane<3>(v, t);
+    if constexpr (R >= 2) {
+        swap_lanes<16>(v);
+        rx_reg<0>(v, t);
+        swap_lanes<16>(v);
+        swap_lanes<32>(v);
+        rx_reg<0>(v, t);
+        swap_lanes<32>(v);
+    } else {
+        float2 o[R];
+        if (nl > 4) {
+            lanes_xor(o, v, 16);
+            rx_with(v, o, t);
+        }
+        if (nl > 5) {
+            lanes_xor(o, v, 32);
+            rx_with(v, o, t);
+        }
+    }
+    if constexpr (K > 0) rx_reg<0>(v, t);
+    if constexpr (K > 1) rx_reg<1>(v, t);
+    if constexpr (K > 2) rx_reg<2>(v, t);
+}
+
+__device__ inline float2 cmulf(float2 a, float2 b)
+{
+    return make_float2(a.x * b.x - a.y * b.y, a.x * b.y + a.y * b.x);
+}
+
+// One bit of the adjoint sweep: the beta term on states scaled by |f|^-done,
+// w = |f|^(2 done), then the inverse rotation of both.
+struct Back {
+    float t, fsq, w;
+    double acc;
+    __device__ void add(float a)
+    {
+        acc += (double)(w * a);
+        w *= fsq;
+    }
+};
+template <int K, int R>
+__device__ inline void back_lane(float2 (&ps)[R], float2 (&la)[R], Back& s)
+{
+    s.add(xb_lane<K>(ps, la));
+    rx_lane<K>(ps, s.t);
+    rx_lane<K>(la, s.t);
+}
+template <int K, int R>
+__device__ inline void back_reg(float2 (&ps)[R], float2 (&la)[R], Back& s)
+{
+    s.add(xb_reg<K>(ps, la));
+    rx_reg<K>(ps, s.t);
+    rx_reg<K>(la, s.t);
+}
+template <int H, int R>
+__device__ inline void back_half(float2 (&ps)[R], float2 (&la)[R], Back& s)
+{
+    if constexpr (R >= 2) {
+        swap_lanes<H>(ps);
+        swap_lanes<H>(la);
+        back_reg<0>(ps, la, s);
+        swap_lanes<H>(ps);
+        swap_lanes<H>(la);
+    } else {
+        float2 po[R], lo[R];
+        lanes_xor(po, ps, H);
+        lanes_xor(lo, la, H);
+        s.add(xb_with(po, la));
+        rx_with(ps, po, s.t);
+        rx_with(la, lo, s.t);
+    }
+}
+template <int R>
+__device__ inline void back(float2 (&ps)[R], float2 (&la)[R], int nl, Back& s)
+{
+    constexpr int K = log2c<R>();
+    if (nl > 0) back_lane<0>(ps, la, s);
+    if (nl > 1) back_lane<1>(ps, la, s);
+    if (nl > 2) back_lane<2>(ps, la, s);
+    if (nl > 3) back_lane<3>(ps, la, s);
+    if (nl > 4) back_half<16>(ps, la, s);
+    if (nl > 5) back_half<32>(ps, la, s);
+    if constexpr (K > 0) back_reg<0>(ps, la, s);
+    if constexpr (K > 1) back_reg<1>(ps, la, s);
+    if constexpr (K > 2) back_reg<2>(ps, la, s);
+}
+
+// LDS of a workgroup (beside the exchange buffers and phase tables)
+struct SmallShared {
+    float2 rx[MAX_P];             // (t, |f|^2) per layer
+    float2 F[MAX_P];              // f^n per layer
+    double angle[2 * MAX_P];      // gamma, beta (optimiser)
+    double sg[MAX_P][8], sb[MAX_P][8], se[8];  // per wave: gamma and beta terms per layer, <C>
+    double k1[STEPS], k2[STEPS];  // Adam's bias corrections of the next steps
+};
+
+// W waves of R registers per lane; GRAD: gradient (and optimiser) or forward.
+template <int W, int R, bool GRAD>
+__device__ __forceinline__ void run(uint8_t* ws, const SubDesc* sd, int b, const SmallArgs& A, Partials part,
+                                    float2* dyn, SmallShared& S)
+{
+    const uint32_t tid = threadIdx.x, lane = tid & 63u, wv = tid >> 6;
+    if (wv >= W) return;  // (a barrier counts the waves that are still there)
+    constexpr uint32_t T = 64 * W;
+    const int n = sd->n, p = A.p, len = sd->lut_len;
+    const uint32_t dim = 1u << (n - 1);
+    const int nl = n - 1 < 6 ? n - 1 : 6;
+    float2* buf = dyn;                                    // W > 1: two exchange buffers
+    float2* lut = dyn + A.lut_at;                         // phase tables
+    const bool all = p * len <= A.lut_cap;                // every layer's table at once
+    // the lane of the complement (index bits 0..5 flipped) of this one
+    const uint32_t rest = (dim - 1u) & 63u;
+    const int lflip = (int)(row_lanes(rest & 15u) | (rest & 48u));
+    // index of register r: W = 2^KW waves alternate between two layouts, in
+    // which index bits 6.. are the wave and the next KW the low register bits,
+    // or the other way round
+    constexpr int KW = log2c<W>();
+    constexpr uint32_t WM = W - 1;
+    const uint32_t lp = row_bits(lane & 15u) | (lane & 48u);
+    auto index = [&](int r, int alt) -> uint32_t {
+        if constexpr (W == 1) return lp | ((uint32_t)r << 6);
+        else return alt ? lp | (((uint32_t)r & WM) << 6) | (wv << (6 + KW)) | ((uint32_t)(r >> KW) << (6 + 2 * KW))
+                        : lp | (wv << 6) | ((uint32_t)r << (6 + KW));
+    };
+    uint16_t c0[R], c1[W > 1 ? R : 1];
+    const uint8_t* tab = ws + sd->tab;
+    const bool w1 = sd->tabw == 1;
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        const uint32_t z = index(r, 0);
+        const uint32_t zz = z < dim ? z : 0u;
+        c0[r] = w1 ? (uint16_t)tab[zz] : ((const uint16_t*)tab)[zz];
+        if constexpr (W > 1) {
+            const uint32_t y = index(r, 1);
+            c1[r] = w1 ? (uint16_t)tab[y] : ((const uint16_t*)tab)[y];
+        }
+    }
+    auto cut = [&](int r, int alt) -> uint32_t {
+        if constexpr (W > 1) return alt ? c1[r] : c0[r];
+        else return c0[r];
+    };
+    const double* gm = A.gamma + (size_t)b * p;
+    const double* bt = A.beta + (size_t)b * p;
+    double* th = A.theta;
+    // optimiser: lane q < 2p of the workgroup holds one angle and its moments
+    double my_th = 0.0, my_m = 0.0, my_v = 0.0;
+    size_t my_idx = 0;
+    const bool opt = GRAD && A.iters > 0, mine = opt && (int)tid < 2 * p;
+    if (mine) {
+        const int q = (int)tid;
+        my_idx = (q < p ? 0 : (size_t)A.B * p) + (size_t)b * p + (q < p ? q : q - p);
+        my_th = th[my_idx];
+        my_m = A.m[my_idx];
+        my_v = A.v[my_idx];
+        S.angle[q] = my_th;
+    }
+    const int32_t t0 = opt ? *A.step : 0;
+    if (opt) sync<W>();
+    const float amp = (float)(1.0 / sqrt((double)dim));
+    float2 v[R], la[GRAD ? R : 1];
+    int alt = 0;
+    for (int it = 0; it < (opt ? A.iters : 1); ++it) {
+        auto gamma_of = [&](int l) { return opt ? S.angle[l] : gm[l]; };
+        auto beta_of = [&](int l) { return opt ? S.angle[p + l] : bt[l]; };
+        // phase tables (where those of all layers do not fit in LDS, they wait in
+        // the workspace) and rotation parameters, one sine and cosine each
+        float2* tables = all ? lut : (float2*)(ws + sd->lut);
+        for (int i = (int)tid; i < p * len + p; i += T) {
+            const int l = i / len;
+            const bool phase = l < p;
+            double sn, cs;
+            sincos(phase ? gamma_of(l) * (double)(i % len) : beta_of(i - p * len), &sn, &cs);
+            if (phase) {
+                tables[i] = make_float2((float)cs, (float)-sn);
+            } else {
+                // e^{-i beta X} = f (I - i t X) X^flip as in rx_coef
+                const bool tanm = fabs(cs) >= fabs(sn);
+                S.rx[i - p * len] = make_float2((float)(tanm ? sn / cs : -cs / sn),
+                                                (float)(tanm ? cs * cs : sn * sn));
+                double fr, fi;
+                cpow_d(tanm ? cs : 0.0, tanm ? 0.0 : -sn, n, fr, fi);
+                S.F[i - p * len] = make_float2((float)fr, (float)fi);
+            }
+        }
+        if (opt && it % STEPS == 0)
+            for (int i = (int)tid; i < STEPS; i += T) {
+                const double t = (double)(t0 + it + i + 1);
+                S.k1[i] = 1.0 - pow(A.b1, t);
+                S.k2[i] = 1.0 - pow(A.b2, t);
+            }
+        __syncthreads();
+        for (int i = (int)tid; i < p * len; i += T) tables[i] = cmulf(tables[i], S.F[i / len]);
+        __syncthreads();
+        // layer l's table, with f^n
+        auto table = [&](int l) -> const float2* {
+            if (all) return lut + l * len;
+            sync<W>();
+            for (int i = (int)tid; i < len; i += T) lut[i] = tables[l * len + i];
+            sync<W>();
+            return lut;
+        };
+        alt = 0;
+        for (int l = 0; l < p; ++l) {
+            const float2* L = table(l);
+            const float t = S.rx[l].x;
+#pragma unroll
+            for (int r = 0; r < R; ++r) {
+                const float2 f = L[cut(r, alt)];
+                if (l == 0) v[r] = index(r, 0) < dim ? make_float2(amp * f.x, amp * f.y) : make_float2(0.f, 0.f);
+                else v[r] = cmulf(v[r], f);
+            }
+            rotate(v, t, nl);
+            if constexpr (W > 1) {
+                // (two buffers in turn: one barrier per layer)
+                float2* x = buf + (l & 1) * (R * W * 64);
+#pragma unroll
+                for (int r = 0; r < R; ++r) x[xslot<W>(r, wv, lane)] = v[r];
+                __syncthreads();
+#pragma unroll
+                for (int r = 0; r < R; ++r) {
+                    const uint32_t q = r ^ (R - 1);
+                    const float2 a = x[xslot<W>((r & ~WM) | wv, r & WM, lane)];
+                    const float2 o = x[xslot<W>((q & ~WM) | (wv ^ WM), q & WM, lane ^ lflip)];
+                    v[r] = make_float2(fmaf(t, o.y, a.x), fmaf(-t, o.x, a.y));
+                }
+                rx_reg<0>(v, t);
+                rx_reg<1>(v, t);
+                if constexpr (KW > 2) rx_reg<2>(v, t);
+                alt ^= 1;
+            } else {
+                float2 o[R], u[R];
+                lanes_xor(o, v, lflip);
+#pragma unroll
+                for (int r = 0; r < R; ++r) u[r] = o[r ^ (R - 1)];
+                rx_with(v, u, t);
+            }
+        }
+        double e = 0.0;
+#pragma unroll
+        for (int r = 0; r < R; ++r)
+            e += ((double)v[r].x * v[r].x + (double)v[r].y * v[r].y) * (double)cut(r, alt);
+        e = wave_total(e);
+        if (lane == 0) S.se[wv] = e;
+        if constexpr (GRAD) {
+#pragma unroll
+            for (int r = 0; r < R; ++r) {
+                const float c = (float)cut(r, alt);
+                la[r] = make_float2(c * v[r].x, c * v[r].y);
+            }
+            for (int l = p - 1; l >= 0; --l) {
+                Back s{-S.rx[l].x, S.rx[l].y, 1.f, 0.0};
+                back(v, la, nl, s);
+                if constexpr (W > 1) {
+                    float2 *x = buf, *y = buf + R * W * 64;
+                    __syncthreads();  // the buffers' last readers are done
+#pragma unroll
+                    for (int r = 0; r < R; ++r) {
+                        x[xslot<W>(r, wv, lane)] = v[r];
+                        y[xslot<W>(r, wv, lane)] = la[r];
+                    }
+                    __syncthreads();
+                    float xa = 0.f, xb = 0.f;
+#pragma unroll
+                    for (int r = 0; r < R; ++r) {
+                        const uint32_t i = xslot<W>((r & ~WM) | wv, r & WM, lane);
+                        const uint32_t q = r ^ (R - 1);
+                        const uint32_t j = xslot<W>((q & ~WM) | (wv ^ WM), q & WM, lane ^ lflip);
+                        const float2 a = x[i], po = x[j], c = y[i], lo = y[j];
+                        xa = fmaf(c.x, po.y, xa);
+                        xb = fmaf(c.y, po.x, xb);
+                        v[r] = make_float2(fmaf(s.t, po.y, a.x), fmaf(-s.t, po.x, a.y));
+                        la[r] = make_float2(fmaf(s.t, lo.y, c.x), fmaf(-s.t, lo.x, c.y));
+                    }
+                    s.add(xa - xb);
+                    alt ^= 1;
+                } else {
+                    float2 u[R], po[R], lo[R];
+                    lanes_xor(u, v, lflip);
+#pragma unroll
+                    for (int r = 0; r < R; ++r) po[r] = u[r ^ (R - 1)];
+                    lanes_xor(u, la, lflip);
+#pragma unroll
+                    for (int r = 0; r < R; ++r) lo[r] = u[r ^ (R - 1)];
+                    s.add(xb_with(po, la));
+                    rx_with(v, po, s.t);
+                    rx_with(la, lo, s.t);
+                }
+                if constexpr (W > 1) {
+                    back_reg<0>(v, la, s);
+                    back_reg<1>(v, la, s);
+                    if constexpr (KW > 2) back_reg<2>(v, la, s);
+                }
+                float g = 0.f;
+#pragma unroll
+                for (int r = 0; r < R; ++r)
+                    g = fmaf((float)cut(r, alt), fmaf(la[r].x, v[r].y, -la[r].y * v[r].x), g);
+                const float2 F = S.F[l];
+                const double gg = wave_total((double)g * ((double)F.x * F.x + (double)F.y * F.y));
+                const double xb = wave_total(s.acc);
+                if (lane == 0) {
+                    S.sg[l][wv] = gg;
+                    S.sb[l][wv] = xb;
+                }
+                if (l > 0) {
+                    const float2* L = table(l);
+#pragma unroll
+                    for (int r = 0; r < R; ++r) {  // conj(f^n) undoes f^n and the phase of this layer
+                        float2 f = L[cut(r, alt)];
+                        f.y = -f.y;
+                        v[r] = cmulf(v[r], f);
+                        la[r] = cmulf(la[r], f);
+                    }
+                }
+            }
+        }
+        sync<W>();  // the waves' sums are written
+        auto total = [&](const double* x) {
+            double a = 0.0;
+            for (int w = 0; w < W; ++w) a += x[w];
+            return a;
+        };
+        const bool last = it + 1 == (opt ? A.iters : 1);
+        if (last || (opt && A.E)) {
+            if (tid == T - 1) {
+                const double x = total(S.se);
+                part.e[sd->tile_base] = x;
+                if (A.E) A.E[b] = x;
+            }
+        }
+        if constexpr (GRAD) {
+            if (!opt && (int)tid < p) {
+                const double g = total(S.sg[tid]), x = total(S.sb[tid]);
+                part.gg[(size_t)tid * part.total_tiles + sd->tile_base] = g;
+                part.gb[((size_t)tid * MAX_GROUPS) * part.total_tiles + sd->tile_base] = x;
+                if (A.dgamma) {
+                    A.dgamma[(size_t)b * p + tid] = 2.0 * g;
+                    A.dbeta[(size_t)b * p + tid] = 2.0 * x;
+                }
+            }
+            if (opt) {
+                if (mine) {
+                    const int q = (int)tid;
+                    const double a = q < p ? total(S.sg[q]) : total(S.sb[q - p]);
+                    adam_update(my_th, my_m, my_v, 2.0 * a, S.k1[it % STEPS], S.k2[it % STEPS], A.lr, A.b1, A.b2, A.eps, 1.0);
+                    S.angle[q] = my_th;
+                }
+                sync<W>();
+            }
+        }
+    }
+    if (mine) {
+        th[my_idx] = my_th;
+        A.m[my_idx] = my_m;
+        A.v[my_idx] = my_v;
+    }
+    if constexpr (!GRAD) {
+        float2* st = (float2*)(ws + sd->psi);
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            const uint32_t z = index(r, alt);
+            if (z < dim) st[z] = v[r];
+        }
+    }
+}
+
+}  // namespace
+
+template <bool GRAD>
+__global__ __launch_bounds__(ST) __attribute__((amdgpu_waves_per_eu(4))) void k_small(uint8_t* ws, const SubDesc* subs, const int32_t* list, SmallArgs A,
+                                              Partials part)
+{
+    extern __shared__ float2 dyn[];
+    __shared__ SmallShared S;
+    const int b = list[blockIdx.x];
+    const SubDesc* sd = subs + b;
+    switch (sd->n) {
+    case 13: run<8, 8, GRAD>(ws, sd, b, A, part, dyn, S); break;
+    case 12: run<4, 8, GRAD>(ws, sd, b, A, part, dyn, S); break;
+    case 11: run<4, 4, GRAD>(ws, sd, b, A, part, dyn, S); break;
+    case 10: run<1, 8, GRAD>(ws, sd, b, A, part, dyn, S); break;
+    case 9: run<1, 4, GRAD>(ws, sd, b, A, part, dyn, S); break;
+    case 8: run<1, 2, GRAD>(ws, sd, b, A, part, dyn, S); break;
+    default: run<1, 1, GRAD>(ws, sd, b, A, part, dyn, S); break;
+    }
+}
+
+// max_n, max_len: the list's largest qubit count and phase table. The tables
+// of all layers are kept where they fit 4096 entries, else one at a time.
+hipError_t launch_small(uint8_t* ws, const SubDesc* subs, const int32_t* list, int nlist, int max_n, int max_len,
+                        bool grad, SmallArgs A, Partials part, hipStream_t s)
+{
+    if (nlist <= 0) return hipSuccess;
+    A.lut_at = max_n >= 11 ? 2u << (max_n - 1) : 0u;
+    A.lut_cap = A.p * max_len < 4096 ? A.p * max_len : 4096;
+    if (A.lut_cap < max_len) A.lut_cap = max_len;
+    const size_t lds = (size_t)(A.lut_at + A.lut_cap) * sizeof(float2);
+    const int threads = max_n <= 10 ? 64 : max_n <= 12 ? 256 : ST;
+    if (grad) hipLaunchKernelGGL(k_small<true>, dim3(nlist), dim3(threads), lds, s, ws, subs, list, A, part);
+    else hipLaunchKernelGGL(k_small<false>, dim3(nlist), dim3(threads), lds, s, ws, subs, list, A, part);
+    return hipGetLastError();
+}
+
+}  // namespace pq

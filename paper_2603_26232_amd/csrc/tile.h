@@ -2,7 +2,7 @@
 // amplitude tiles, wide.hip: 16384-amplitude tiles).
 #pragma once
 
-#include "common.h"
+#include "lane.h"
 
 namespace pq {
 
@@ -63,24 +63,11 @@ __device__ inline Geo make_geo(const SubDesc* sd, int g, uint32_t t, int TB = TI
     return r;
 }
 
-// Wide tiles, layout LL1: the lanes of a row of 16 hold tile bits 0..3, lane
-// number = XOR of the masks 1, 2, 7, 15 of the bits that are set.
-__host__ __device__ constexpr uint32_t wide_lanes(uint32_t bits)
-{
-    return (bits & 1u ? 1u : 0u) ^ (bits & 2u ? 2u : 0u) ^ (bits & 4u ? 7u : 0u) ^ (bits & 8u ? 15u : 0u);
-}
-// the inverse: tile bits 0..3 of a lane
-__host__ __device__ constexpr uint32_t wide_nibble(uint32_t lane)
-{
-    const uint32_t a = lane & 8u ? lane ^ 15u : lane;  // without bit 3's mask
-    const uint32_t b = a & 4u ? a ^ 7u : a;
-    return (lane & 8u) | (a & 4u) | (b & 3u);
-}
 // tile position of entry e of a wide tile's cut table (order: lane, register)
 __device__ inline uint32_t wide_entry(uint32_t e)
 {
     const uint32_t lane = e / WIDE_REGS, r = e % WIDE_REGS;
-    return wide_nibble(lane & 15u) | (r << 4) | ((lane >> 4) << 9);
+    return row_bits(lane & 15u) | (r << 4) | ((lane >> 4) << 9);
 }
 
 // Reduced pair rotation (I - i t X) on (a, b) = (psi(z), psi(z ^ bit)):

@@ -12,11 +12,9 @@
 // Register layouts (tile position q, 14 bits; lane id = 9 bits):
 //   LLIN  registers = bits 9..13, lanes = bits 0..8 (coalesced rows)
 //   LL1   registers = bits 4..8,  lanes = bits 0..3 and 9..13
-// Bits 0..3 are rotated in LL1 across the lanes of a row of 16: the lane
-// number is the XOR of masks 1, 2, 7, 15 for the bits that are set, so that a
-// bit's partner lane is one DPP step away (quad_perm, row_half_mirror,
-// row_mirror). That costs one instruction per amplitude and bit more than a
-// register bit, and saves a third layout and its LDS exchange.
+// Bits 0..3 are rotated in LL1 across the lanes of a row of 16 (lane.h). That
+// costs one instruction per amplitude and bit more than a register bit, and
+// saves a third layout and its LDS exchange.
 // The forward passes exchange the real and the imaginary parts one after the
 // other through 66 KB of LDS, so that two workgroups share a CU; the backward
 // passes hold two states in registers (two waves per SIMD), so one workgroup
@@ -49,7 +47,7 @@ constexpr uint32_t EX_SLOTS = WIDE_TILE + WIDE_TILE / 32;  // one pad slot per 3
 template <int L>
 __device__ inline uint32_t thread_part(uint32_t tid)
 {
-    return L == LLIN ? tid : wide_nibble(tid & 15u) | ((tid >> 4) << 9);
+    return L == LLIN ? tid : row_bits(tid & 15u) | ((tid >> 4) << 9);
 }
 template <int L>
 __host__ __device__ constexpr uint32_t reg_part(uint32_t r)
@@ -94,80 +92,6 @@ __device__ inline void xchg2(float2* ex, uint32_t tid, float2 (&v)[WR])
     for (int r = 0; r < WR; ++r) v[r] = s[slot(reg_part<LT>(r))];
     __syncthreads();
     __builtin_amdgcn_sched_barrier(0);
-}
-
-// Operations across lanes on tile bit K (0..3) in LL1, on DPP operands: the
-// compiler does not fold a DPP move into a fused multiply-add, which would
-// cost a move per operand. Each block starts with the two wait states that a
-// DPP read needs after the last vector write of its source, and reads nothing
-// by DPP that it has written within the two instructions before.
-#define PQ_DPP0 "quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf"
-#define PQ_DPP1 "quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf"
-#define PQ_DPP2 "row_half_mirror row_mask:0xf bank_mask:0xf"
-#define PQ_DPP3 "row_mirror row_mask:0xf bank_mask:0xf"
-
-// x += t * (partner's y), y -= t * (partner's old x), four amplitudes
-#define PQ_RX_LANE(D)                                                                                            \
-    asm("s_nop 1\n\t"                                                                                            \
-        "v_mov_b32 %8, %0\n\t"                                                                                   \
-        "v_mov_b32 %9, %2\n\t"                                                                                   \
-        "v_mov_b32 %10, %4\n\t"                                                                                  \
-        "v_mov_b32 %11, %6\n\t"                                                                                  \
-        "v_fmac_f32_dpp %0, %1, %12 " D "\n\t"                                                                   \
-        "v_fmac_f32_dpp %2, %3, %12 " D "\n\t"                                                                   \
-        "v_fmac_f32_dpp %4, %5, %12 " D "\n\t"                                                                   \
-        "v_fmac_f32_dpp %6, %7, %12 " D "\n\t"                                                                   \
-        "v_fmac_f32_dpp %1, %8, %13 " D "\n\t"                                                                   \
-        "v_fmac_f32_dpp %3, %9, %13 " D "\n\t"                                                                   \
-        "v_fmac_f32_dpp %5, %10, %13 " D "\n\t"                                                                  \
-        "v_fmac_f32_dpp %7, %11, %13 " D                                                                          \
-        : "+v"(v[r].x), "+v"(v[r].y), "+v"(v[r + 1].x), "+v"(v[r + 1].y), "+v"(v[r + 2].x), "+v"(v[r + 2].y),     \
-          "+v"(v[r + 3].x), "+v"(v[r + 3].y), "=&v"(s0), "=&v"(s1), "=&v"(s2), "=&v"(s3)                          \
-        : "v"(t), "v"(-t))
-
-// rotation of tile bit K across lanes
-template <int K>
-__device__ inline void rx_lane(float2 (&v)[WR], float t)
-{
-#pragma unroll
-    for (int r = 0; r < WR; r += 4) {
-        float s0, s1, s2, s3;
-        if constexpr (K == 0) PQ_RX_LANE(PQ_DPP0);
-        else if constexpr (K == 1) PQ_RX_LANE(PQ_DPP1);
-        else if constexpr (K == 2) PQ_RX_LANE(PQ_DPP2);
-        else PQ_RX_LANE(PQ_DPP3);
-    }
-}
-
-// a += la.x * (partner's ps.y), b += la.y * (partner's ps.x), four amplitudes
-#define PQ_XB_LANE(D)                                                                                            \
-    asm("s_nop 1\n\t"                                                                                            \
-        "v_fmac_f32_dpp %0, %3, %10 " D "\n\t"                                                                   \
-        "v_fmac_f32_dpp %1, %2, %11 " D "\n\t"                                                                   \
-        "v_fmac_f32_dpp %0, %5, %12 " D "\n\t"                                                                   \
-        "v_fmac_f32_dpp %1, %4, %13 " D "\n\t"                                                                   \
-        "v_fmac_f32_dpp %0, %7, %14 " D "\n\t"                                                                   \
-        "v_fmac_f32_dpp %1, %6, %15 " D "\n\t"                                                                   \
-        "v_fmac_f32_dpp %0, %9, %16 " D "\n\t"                                                                   \
-        "v_fmac_f32_dpp %1, %8, %17 " D                                                                           \
-        : "+v"(a), "+v"(b)                                                                                       \
-        : "v"(ps[r].x), "v"(ps[r].y), "v"(ps[r + 1].x), "v"(ps[r + 1].y), "v"(ps[r + 2].x), "v"(ps[r + 2].y),     \
-          "v"(ps[r + 3].x), "v"(ps[r + 3].y), "v"(la[r].x), "v"(la[r].y), "v"(la[r + 1].x), "v"(la[r + 1].y),     \
-          "v"(la[r + 2].x), "v"(la[r + 2].y), "v"(la[r + 3].x), "v"(la[r + 3].y))
-
-// sum over the lane's amplitudes of Im conj(lam(z)) psi(z ^ bit K)
-template <int K>
-__device__ inline float xb_lane(const float2 (&ps)[WR], const float2 (&la)[WR])
-{
-    float a = 0.f, b = 0.f;
-#pragma unroll
-    for (int r = 0; r < WR; r += 4) {
-        if constexpr (K == 0) PQ_XB_LANE(PQ_DPP0);
-        else if constexpr (K == 1) PQ_XB_LANE(PQ_DPP1);
-        else if constexpr (K == 2) PQ_XB_LANE(PQ_DPP2);
-        else PQ_XB_LANE(PQ_DPP3);
-    }
-    return a - b;
 }
 
 template <int K>
@@ -356,7 +280,7 @@ struct Cuts {
 template <uint32_t M>
 __device__ inline void load_cuts(Cuts& c, const uint8_t* tab, int width, uint32_t tid, bool flip)
 {
-    constexpr uint32_t ROW = wide_lanes(M & 15u) | (((M >> 9) & 31u) << 4), R = (M >> 4) & 31u;
+    constexpr uint32_t ROW = row_lanes(M & 15u) | (((M >> 9) & 31u) << 4), R = (M >> 4) & 31u;
     const uint32_t row = flip ? tid ^ ROW : tid;
     if (width == 1) {
         const uint4* p = (const uint4*)(tab + (size_t)row * WR);
