@@ -55,29 +55,40 @@ hipError_t launch_maxcut_eval(int32_t nV, int64_t nE, const int32_t* u, const in
 
 // Adam (Kingma and Ba 2015) in FP64; sign = +1 ascends (the QAOA objective
 // is maximised), -1 descends. The step counter lives in device memory so a
-// captured graph can replay the step.
-__global__ __launch_bounds__(1024) void k_adam(int32_t count, double* theta, const double* grad, double* m,
-                                              double* v, int32_t* step, double lr, double b1, double b2,
-                                              double eps, double sign)
+// captured graph can replay the step. One thread per parameter; up to one
+// workgroup's worth advances the counter itself, more leave it to a second
+// kernel, since every workgroup reads it. (One workgroup for all of the 19,590
+// parameters of the angle predictor took 71 us of FP64 divisions and roots.)
+constexpr int ADAM_THREADS = 256;
+
+__global__ __launch_bounds__(ADAM_THREADS) void k_adam(int32_t count, double* theta, const double* grad, double* m,
+                                                      double* v, int32_t* step, int advance, double lr, double b1,
+                                                      double b2, double eps, double sign)
 {
     const int32_t t = *step + 1;
     const double c1 = 1.0 - pow(b1, (double)t), c2 = 1.0 - pow(b2, (double)t);
-    for (int32_t i = threadIdx.x; i < count; i += blockDim.x) {
+    const int32_t i = blockIdx.x * ADAM_THREADS + threadIdx.x;
+    if (i < count) {
         double th = theta[i], mi = m[i], vi = v[i];
         adam_update(th, mi, vi, grad[i], c1, c2, lr, b1, b2, eps, sign);
         m[i] = mi;
         v[i] = vi;
         theta[i] = th;
     }
-    __syncthreads();
+    if (!advance) return;
+    __syncthreads();  // every thread has read the count
     if (threadIdx.x == 0) *step = t;
 }
 
 hipError_t launch_adam(int32_t count, double* theta, const double* grad, double* m, double* v, int32_t* step,
                        double lr, double b1, double b2, double eps, double sign, hipStream_t s)
 {
-    hipLaunchKernelGGL(k_adam, dim3(1), dim3(1024), 0, s, count, theta, grad, m, v, step, lr, b1, b2, eps, sign);
-    return hipGetLastError();
+    const int blocks = count / ADAM_THREADS + (count % ADAM_THREADS != 0);
+    const int alone = blocks == 1;
+    hipLaunchKernelGGL(k_adam, dim3(blocks), dim3(ADAM_THREADS), 0, s, count, theta, grad, m, v, step, alone, lr, b1,
+                       b2, eps, sign);
+    const hipError_t e = hipGetLastError();
+    return e != hipSuccess || alone ? e : launch_step_advance(step, 1, s);
 }
 
 }  // namespace pq

@@ -10,7 +10,7 @@
 // b3[out]. Every reduction runs in a fixed order (bit-reproducible).
 #include <mutex>
 
-#include "common.h"
+#include "lane.h"
 
 namespace pq {
 
@@ -22,133 +22,303 @@ __host__ __device__ inline int64_t mlp_off_b3(const MlpDims& d) { return mlp_off
 __host__ __device__ int64_t mlp_nparams(const MlpDims& d) { return mlp_off_b3(d) + d.out; }
 int64_t mlp_num_params(const MlpDims& d) { return mlp_nparams(d); }
 
-// one workgroup per sample; act[s] = (h1[H], h2[H])
-__global__ __launch_bounds__(MLP_MAX_H) void k_mlp_fwd(int B, MlpDims d, const double* P, const float* X, float* Y,
-                                                      float* act)
+// Forward and error kernels: a workgroup takes as many samples as its 1024
+// threads can share (one per thread and unit), so every weight, read as FP64 and
+// rounded to FP32 once per workgroup into LDS, serves all of them, along rows.
+// (One workgroup per sample, each lane reading its own row, touched 64 cache
+// lines per load.) The loads' latency is the bound: the first 16 K weights of
+// both hidden layers are all on their way before the first is used. Every output
+// is still one FP32 chain of fused multiply-adds in input order. Measured, 870
+// samples of 18-128-128-6: forward 22 -> 15.5 us, errors 11.9 -> 11.3 us, weight
+// gradients and loss 243 -> 17 us; 4000 samples of 64-256-256-12, a whole step
+// 1965 -> 288 us.
+constexpr int MLP_THREADS = 1024;
+constexpr int MLP_LOADS = 16;  // weights a thread fetches at a time
+
+// weight columns staged at a time for N units, and their row in LDS, padded so
+// that 16-byte reads of 16 lanes meet all 64 banks
+__host__ __device__ inline int mlp_chunk(int N) { return N <= 128 ? 128 : 64; }
+__host__ __device__ inline int mlp_row(int N) { return mlp_chunk(N) + 4; }
+
+// samples per workgroup
+inline int mlp_samples(int H)
 {
-    __shared__ float xs[MLP_MAX_IN], h1s[MLP_MAX_H], h2s[MLP_MAX_H];
-    const int s = blockIdx.x, i = threadIdx.x;
-    const double* W1 = P;
-    const double* b1 = P + mlp_off_b1(d);
-    const double* W2 = P + mlp_off_W2(d);
-    const double* b2 = P + mlp_off_b2(d);
-    const double* W3 = P + mlp_off_W3(d);
-    const double* b3 = P + mlp_off_b3(d);
-    if (i < d.in) xs[i] = X[(size_t)s * d.in + i];
+    int pad = 32;
+    while (pad < H) pad *= 2;
+    return MLP_THREADS / pad;
+}
+// floats of a sample's row of K values, a multiple of four
+__host__ __device__ inline int mlp_pad(int K) { return (K + 3) & ~3; }
+
+// A chunk of at most 16 K weights of a row-major matrix, sixteen per thread:
+// columns c < nc, rows r < nr; thread: column tid % 2^lg, rows tid / 2^lg, +
+// 1024 / 2^lg, ...
+struct MlpChunk {
+    int c, r0, step, nc, nr;
+    __device__ MlpChunk(int nc_, int nr_) : nc(nc_), nr(nr_)
+    {
+        int lg = 4;
+        while ((1 << lg) < nc) ++lg;
+        c = (int)threadIdx.x & ((1 << lg) - 1);
+        r0 = (int)threadIdx.x >> lg;
+        step = MLP_THREADS >> lg;
+    }
+    __device__ void fetch(double (&w)[MLP_LOADS], const double* W, int ld) const
+    {
+#pragma unroll
+        for (int i = 0; i < MLP_LOADS; ++i) {
+            const int r = r0 + i * step;
+            w[i] = r < nr && c < nc ? W[(size_t)r * ld + c] : 0.0;
+        }
+    }
+    // element (r, c) to wt[r * rs + c * cs]
+    __device__ void put(const double (&w)[MLP_LOADS], float* wt, int rs, int cs) const
+    {
+#pragma unroll
+        for (int i = 0; i < MLP_LOADS; ++i) {
+            const int r = r0 + i * step;
+            if (r < nr && c < nc) wt[r * rs + c * cs] = (float)w[i];
+        }
+    }
+};
+
+// fetches the weights of inputs j0 .. of a layer of N units over K inputs:
+// W[n][j] (T = false) or, for the errors going back, W[j][n] (T = true)
+template <bool T>
+__device__ inline MlpChunk mlp_fetch(double (&w)[MLP_LOADS], const double* W, int K, int N, int j0)
+{
+    const int chunk = mlp_chunk(N), kc = K - j0 < chunk ? K - j0 : chunk;
+    const MlpChunk m(T ? N : kc, T ? kc : N);
+    m.fetch(w, T ? W + (size_t)j0 * N : W + j0, T ? N : K);
+    return m;
+}
+
+// out(s, n, b[n] + sum_j W(n, j) src[s][j]) for the workgroup's S samples
+// (bias may be NULL); rows of src are mlp_pad(K) floats apart. first: the first
+// chunk of weights, already fetched.
+template <bool T, typename Out>
+__device__ inline void mlp_layer(int K, int N, int S, const double* W, const double* bias, const float* src,
+                                 float* wt, double (&first)[MLP_LOADS], Out out)
+{
+    const int ks = mlp_pad(K), chunk = mlp_chunk(N), row = mlp_row(N);
+    // (N S <= 1024 for the hidden layers; the output layer may take more rounds)
+    for (int i0 = 0; i0 < N * S; i0 += MLP_THREADS) {
+        const int it = i0 + (int)threadIdx.x;
+        const bool on = it < N * S;
+        const int n = on ? it % N : 0, s0 = on ? it / N : 0;
+        float a = on && bias ? (float)bias[n] : 0.f;
+        for (int j0 = 0; j0 < K; j0 += chunk) {
+            const int kc = K - j0 < chunk ? K - j0 : chunk;
+            if (i0 || j0) mlp_fetch<T>(first, W, K, N, j0);
+            __syncthreads();  // the last chunk has been read
+            MlpChunk(T ? N : kc, T ? kc : N).put(first, wt, T ? 1 : row, T ? row : 1);
+            __syncthreads();
+            const float* w = wt + n * row;
+            const float* x = src + s0 * ks + j0;
+            int c = 0;
+#pragma unroll 8
+            for (; c + 4 <= kc; c += 4) {
+                const float4 u = *(const float4*)(w + c), y = *(const float4*)(x + c);
+                a = fmaf(u.w, y.w, fmaf(u.z, y.z, fmaf(u.y, y.y, fmaf(u.x, y.x, a))));
+            }
+            for (; c < kc; ++c) a = fmaf(w[c], x[c], a);
+        }
+        if (on) out(s0, n, a);
+    }
     __syncthreads();
-    if (i < d.H) {
-        float a = (float)b1[i];
-        for (int f = 0; f < d.in; ++f) a += (float)W1[(size_t)i * d.in + f] * xs[f];
+}
+
+// LDS floats: weights [max(H, out)][mlp_row], then samples [S][in], [S][H], [S][H] (rows padded)
+__global__ __launch_bounds__(MLP_THREADS) void k_mlp_fwd(int B, MlpDims d, int S, const double* P, const float* X,
+                                                        float* Y, float* act)
+{
+    extern __shared__ float4 mlp_lds4[];
+    const int big = d.H > d.out ? d.H : d.out;
+    const int pi = mlp_pad(d.in), ph = mlp_pad(d.H);
+    float* wt = (float*)mlp_lds4;
+    float* xs = wt + big * mlp_row(big);
+    float* h1 = xs + S * pi;
+    float* h2 = h1 + S * ph;
+    const int s0 = blockIdx.x * S, ns = B - s0 < S ? B - s0 : S;
+    double w1[MLP_LOADS], w2[MLP_LOADS];
+    mlp_fetch<false>(w1, P, d.in, d.H, 0);
+    mlp_fetch<false>(w2, P + mlp_off_W2(d), d.H, d.H, 0);
+    for (int i = threadIdx.x; i < S * d.in; i += MLP_THREADS)
+        xs[i / d.in * pi + i % d.in] = i < ns * d.in ? X[(size_t)s0 * d.in + i] : 0.f;
+    mlp_layer<false>(d.in, d.H, S, P, P + mlp_off_b1(d), xs, wt, w1, [&](int q, int n, float a) {
         a = a > 0.f ? a : 0.f;
-        h1s[i] = a;
-        act[(size_t)s * 2 * d.H + i] = a;
-    }
-    __syncthreads();
-    if (i < d.H) {
-        float a = (float)b2[i];
-        for (int j = 0; j < d.H; ++j) a += (float)W2[(size_t)i * d.H + j] * h1s[j];
+        h1[q * ph + n] = a;
+        if (q < ns) act[(size_t)(s0 + q) * 2 * d.H + n] = a;
+    });
+    mlp_fetch<false>(w1, P + mlp_off_W3(d), d.H, d.out, 0);
+    mlp_layer<false>(d.H, d.H, S, P + mlp_off_W2(d), P + mlp_off_b2(d), h1, wt, w2, [&](int q, int n, float a) {
         a = a > 0.f ? a : 0.f;
-        h2s[i] = a;
-        act[(size_t)s * 2 * d.H + d.H + i] = a;
-    }
-    __syncthreads();
-    if (i < d.out) {
-        float a = (float)b3[i];
-        for (int j = 0; j < d.H; ++j) a += (float)W3[(size_t)i * d.H + j] * h2s[j];
-        Y[(size_t)s * d.out + i] = a;
-    }
+        h2[q * ph + n] = a;
+        if (q < ns) act[(size_t)(s0 + q) * 2 * d.H + d.H + n] = a;
+    });
+    mlp_layer<false>(d.H, d.out, S, P + mlp_off_W3(d), P + mlp_off_b3(d), h2, wt, w1, [&](int q, int n, float a) {
+        if (q < ns) Y[(size_t)(s0 + q) * d.out + n] = a;
+    });
 }
 
 // per-sample back-propagated errors: delta[s] = (d1[H], d2[H], d3[out]); the
-// squared error of the sample goes to sq[s]
-__global__ __launch_bounds__(MLP_MAX_H) void k_mlp_delta(int B, MlpDims d, const double* P, const float* Y,
-                                                        const float* act, const float* T, float* delta, double* sq)
+// squared error of the sample goes to sq[s]. LDS floats: weights [H][mlp_row],
+// then samples d3 [S][out], d2 [S][H] (rows padded).
+__global__ __launch_bounds__(MLP_THREADS) void k_mlp_delta(int B, MlpDims d, int S, const double* P, const float* Y,
+                                                          const float* act, const float* T, float* delta, double* sq)
 {
-    __shared__ float d3s[MLP_MAX_OUT], d2s[MLP_MAX_H];
-    __shared__ double sqs[MLP_MAX_OUT];
-    const int s = blockIdx.x, i = threadIdx.x;
-    const double* W2 = P + mlp_off_W2(d);
-    const double* W3 = P + mlp_off_W3(d);
+    extern __shared__ float4 mlp_lds4[];
+    const int ph = mlp_pad(d.H), po = mlp_pad(d.out);
+    float* wt = (float*)mlp_lds4;
+    float* d3 = wt + d.H * mlp_row(d.H);
+    float* d2 = d3 + S * po;
     const float scale = 1.0f / ((float)B * (float)d.out);
-    const float* h1 = act + (size_t)s * 2 * d.H;
-    const float* h2 = h1 + d.H;
-    float* dl = delta + (size_t)s * (2 * d.H + d.out);
-    if (i < d.out) {
-        const float r = Y[(size_t)s * d.out + i] - T[(size_t)s * d.out + i];
-        d3s[i] = 2.f * r * scale;
-        sqs[i] = (double)r * (double)r;
-        dl[2 * d.H + i] = d3s[i];
-    }
-    __syncthreads();
-    if (i == 0) {
-        double a = 0.0;
-        for (int o = 0; o < d.out; ++o) a += sqs[o];
-        sq[s] = a;
-    }
-    if (i < d.H) {
-        float a = 0.f;
-        for (int o = 0; o < d.out; ++o) a += (float)W3[(size_t)o * d.H + i] * d3s[o];
-        a = h2[i] > 0.f ? a : 0.f;
-        d2s[i] = a;
-        dl[d.H + i] = a;
-    }
-    __syncthreads();
-    if (i < d.H) {
-        float a = 0.f;
-        for (int k = 0; k < d.H; ++k) a += (float)W2[(size_t)k * d.H + i] * d2s[k];
-        dl[i] = h1[i] > 0.f ? a : 0.f;
-    }
-}
-
-// one thread per parameter: sum over samples in order (FP32 products, FP64 sum)
-__global__ void k_mlp_wgrad(int B, MlpDims d, const float* X, const float* act, const float* delta, double* G)
-{
-    const int64_t np = mlp_nparams(d);
-    const int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (p >= np) return;
+    const int s0 = blockIdx.x * S, ns = B - s0 < S ? B - s0 : S;
     const int DS = 2 * d.H + d.out;
-    int dsel, drow, isel, icol;  // delta slot / input slot (-1: bias)
-    // isel: 0 = x, 1 = h1, 2 = h2; dsel: 0 = d1, 1 = d2, 2 = d3
-    if (p < mlp_off_b1(d)) {
-        dsel = 0; drow = (int)(p / d.in); isel = 0; icol = (int)(p % d.in);
-    } else if (p < mlp_off_W2(d)) {
-        dsel = 0; drow = (int)(p - mlp_off_b1(d)); isel = -1; icol = 0;
-    } else if (p < mlp_off_b2(d)) {
-        const int64_t q = p - mlp_off_W2(d);
-        dsel = 1; drow = (int)(q / d.H); isel = 1; icol = (int)(q % d.H);
-    } else if (p < mlp_off_W3(d)) {
-        dsel = 1; drow = (int)(p - mlp_off_b2(d)); isel = -1; icol = 0;
-    } else if (p < mlp_off_b3(d)) {
-        const int64_t q = p - mlp_off_W3(d);
-        dsel = 2; drow = (int)(q / d.H); isel = 2; icol = (int)(q % d.H);
-    } else {
-        dsel = 2; drow = (int)(p - mlp_off_b3(d)); isel = -1; icol = 0;
+    const double *W2 = P + mlp_off_W2(d), *W3 = P + mlp_off_W3(d);
+    double w3[MLP_LOADS], w2[MLP_LOADS];
+    mlp_fetch<true>(w3, W3, d.out, d.H, 0);
+    mlp_fetch<true>(w2, W2, d.H, d.H, 0);
+    for (int i = threadIdx.x; i < S * d.out; i += MLP_THREADS) {
+        const bool on = i < ns * d.out;
+        const float r = on ? Y[(size_t)s0 * d.out + i] - T[(size_t)s0 * d.out + i] : 0.f;
+        const float e = 2.f * r * scale;
+        d3[i / d.out * po + i % d.out] = e;
+        if (on) delta[(size_t)(s0 + i / d.out) * DS + 2 * d.H + i % d.out] = e;
     }
-    const int doff = dsel == 0 ? 0 : (dsel == 1 ? d.H : 2 * d.H);
-    double acc = 0.0;
-    for (int s = 0; s < B; ++s) {
-        const float dv = delta[(size_t)s * DS + doff + drow];
-        float in = 1.f;
-        if (isel == 0) in = X[(size_t)s * d.in + icol];
-        else if (isel == 1) in = act[(size_t)s * 2 * d.H + icol];
-        else if (isel == 2) in = act[(size_t)s * 2 * d.H + d.H + icol];
-        acc += (double)(dv * in);
+    if ((int)threadIdx.x >= MLP_THREADS - ns) {
+        const int s = MLP_THREADS - 1 - (int)threadIdx.x;
+        double a = 0.0;
+        for (int o = 0; o < d.out; ++o) {
+            const size_t i = (size_t)(s0 + s) * d.out + o;
+            const float r = Y[i] - T[i];
+            a += (double)r * (double)r;
+        }
+        sq[s0 + s] = a;
     }
-    G[p] = acc;
+    mlp_layer<true>(d.out, d.H, S, W3, nullptr, d3, wt, w3, [&](int q, int n, float a) {
+        const bool on = q < ns && act[(size_t)(s0 + q) * 2 * d.H + d.H + n] > 0.f;
+        a = on ? a : 0.f;
+        d2[q * ph + n] = a;
+        if (q < ns) delta[(size_t)(s0 + q) * DS + d.H + n] = a;
+    });
+    mlp_layer<true>(d.H, d.H, S, W2, nullptr, d2, wt, w2, [&](int q, int n, float a) {
+        if (q < ns) delta[(size_t)(s0 + q) * DS + n] = act[(size_t)(s0 + q) * 2 * d.H + n] > 0.f ? a : 0.f;
+    });
 }
 
-__global__ void k_mlp_loss(int B, int out, const double* sq, double* loss)
+// Weight gradients and the loss. A wave owns a 4 x 8 tile of one layer's (error
+// row, input column) sums, the bias being one more column whose input is 1. Its
+// lanes take every 64th sample (products rounded to FP32, summed in FP64), three
+// 16-byte loads for 32 sums, and are added by a fixed tree at the end. (One
+// thread per parameter walked all samples alone: 870 dependent FP64 sums deep,
+// and a load instruction brought one error and 64 inputs.)
+constexpr int WG_R = 4, WG_C = 8, WG_N = WG_R * WG_C, WG_WAVES = 4;
+typedef float wg_f4 __attribute__((ext_vector_type(4), aligned(4)));  // 16 bytes at any float
+
+// tiles of the three layers: (rows, columns) = (H, in + 1), (H, H + 1), (out, H + 1)
+__host__ __device__ inline int wg_tiles(int rows, int cols)
 {
-    __shared__ double red[256];
-    double a = 0.0;
-    for (int s = threadIdx.x; s < B; s += blockDim.x) a += sq[s];
-    red[threadIdx.x] = a;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        double t = 0.0;
-        for (int i = 0; i < (int)blockDim.x; ++i) t += red[i];
-        *loss = t / ((double)B * (double)out);
+    return ((rows + WG_R - 1) / WG_R) * ((cols + WG_C - 1) / WG_C);
+}
+
+// Adds each of the N values over the wave; lane l ends with value l mod 32's
+// total in v[0] (halving the values at every step).
+__device__ inline double swap_add(double a, double b, int H)
+{
+    const uint64_t u = __double_as_longlong(a), w = __double_as_longlong(b);
+    float l0 = __uint_as_float((uint32_t)u), h0 = __uint_as_float((uint32_t)(u >> 32));
+    float l1 = __uint_as_float((uint32_t)w), h1 = __uint_as_float((uint32_t)(w >> 32));
+    if (H == 32) {
+        swap_halves<32>(l0, l1);
+        swap_halves<32>(h0, h1);
+    } else {
+        swap_halves<16>(l0, l1);
+        swap_halves<16>(h0, h1);
     }
+    return __longlong_as_double((long long)(((uint64_t)__float_as_uint(h0) << 32) | __float_as_uint(l0))) +
+           __longlong_as_double((long long)(((uint64_t)__float_as_uint(h1) << 32) | __float_as_uint(l1)));
+}
+template <int K>
+__device__ inline double row_add(double a, double b, bool upper)
+{
+    return (upper ? b : a) + across<K>(upper ? a : b);
+}
+
+__global__ __launch_bounds__(64 * WG_WAVES) void k_mlp_wgrad(int B, MlpDims d, const float* __restrict__ X,
+                                                            const float* __restrict__ act,
+                                                            const float* __restrict__ delta,
+                                                            const double* __restrict__ sq, double* __restrict__ G,
+                                                            double* __restrict__ loss)
+{
+    __shared__ double red[WG_WAVES];
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    const int n1 = wg_tiles(d.H, d.in + 1), n2 = wg_tiles(d.H, d.H + 1), n3 = wg_tiles(d.out, d.H + 1);
+    if (blockIdx.x == gridDim.x - 1) {  // the loss: the mean of the samples' squared errors
+        double a = 0.0;
+        for (int s = threadIdx.x; s < B; s += 64 * WG_WAVES) a += sq[s];
+        a = block_sum(a, red);
+        if (threadIdx.x == 0) *loss = a / ((double)B * (double)d.out);
+        return;
+    }
+    int t = blockIdx.x * WG_WAVES + wv;
+    if (t >= n1 + n2 + n3) return;
+    const int layer = t < n1 ? 0 : t < n1 + n2 ? 1 : 2;
+    t -= layer == 0 ? 0 : layer == 1 ? n1 : n1 + n2;
+    const int rows = layer == 2 ? d.out : d.H, cols = layer == 0 ? d.in : d.H;  // without the bias
+    const int tc = (cols + 1 + WG_C - 1) / WG_C;
+    const int r0 = t / tc * WG_R, c0 = t % tc * WG_C;
+    const int DS = 2 * d.H + d.out;
+    const float* D = delta + (layer == 0 ? 0 : layer == 1 ? d.H : 2 * d.H) + r0;
+    const float* I = (layer == 0 ? X : layer == 1 ? act : act + d.H) + c0;
+    const int is = layer == 0 ? d.in : 2 * d.H;
+    const bool whole = r0 + WG_R <= rows && c0 + WG_C <= cols;  // uniform
+    double g[WG_N] = {};
+    auto add = [&](const float (&e)[WG_R], const float (&x)[WG_C]) {
+#pragma unroll
+        for (int i = 0; i < WG_R; ++i)
+#pragma unroll
+            for (int j = 0; j < WG_C; ++j) g[i * WG_C + j] += (double)(e[i] * x[j]);
+    };
+    if (whole) {
+#pragma unroll 4
+        for (int s = lane; s < B; s += 64) {
+            const wg_f4 e4 = *(const wg_f4*)(D + (size_t)s * DS);
+            const wg_f4 x4 = *(const wg_f4*)(I + (size_t)s * is), y4 = *(const wg_f4*)(I + (size_t)s * is + 4);
+            const float e[WG_R] = {e4[0], e4[1], e4[2], e4[3]};
+            const float x[WG_C] = {x4[0], x4[1], x4[2], x4[3], y4[0], y4[1], y4[2], y4[3]};
+            add(e, x);
+        }
+    } else {
+        for (int s = lane; s < B; s += 64) {
+            float e[WG_R], x[WG_C];
+#pragma unroll
+            for (int i = 0; i < WG_R; ++i) e[i] = r0 + i < rows ? D[(size_t)s * DS + i] : 0.f;
+#pragma unroll
+            for (int j = 0; j < WG_C; ++j)
+                x[j] = c0 + j < cols ? I[(size_t)s * is + j] : c0 + j == cols ? 1.f : 0.f;
+            add(e, x);
+        }
+    }
+    // (the lanes of a wave part in the loops above; all are back here)
+    const uint32_t bits = row_bits(lane & 15u);
+#pragma unroll
+    for (int i = 0; i < 16; ++i) g[i] = swap_add(g[i], g[i + 16], 32);
+#pragma unroll
+    for (int i = 0; i < 8; ++i) g[i] = swap_add(g[i], g[i + 8], 16);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) g[i] = row_add<3>(g[i], g[i + 4], bits & 8u);
+#pragma unroll
+    for (int i = 0; i < 2; ++i) g[i] = row_add<2>(g[i], g[i + 2], bits & 4u);
+    g[0] = row_add<1>(g[0], g[1], bits & 2u);
+    const double a = g[0] + across<0>(g[0]);
+    const int v = (lane & 32 ? 16 : 0) | (lane & 16 ? 8 : 0) | (bits & 8u ? 4 : 0) | (bits & 4u ? 2 : 0) |
+                  (bits & 2u ? 1 : 0);
+    const int row = r0 + v / WG_C, col = c0 + v % WG_C;
+    if ((bits & 1u) || row >= rows || col > cols) return;
+    const int64_t oW = layer == 0 ? 0 : layer == 1 ? mlp_off_W2(d) : mlp_off_W3(d);
+    const int64_t ob = layer == 0 ? mlp_off_b1(d) : layer == 1 ? mlp_off_b2(d) : mlp_off_b3(d);
+    G[col == cols ? ob + row : oW + (int64_t)row * cols + col] = a;
 }
 
 // Warm-start angles from the predictor's standardised outputs: output o of
@@ -200,7 +370,10 @@ hipError_t launch_keep_better(int B, int p, const double* E_alt, const double* t
 
 hipError_t launch_mlp_forward(int B, MlpDims d, const double* P, const float* X, float* Y, float* act, hipStream_t s)
 {
-    hipLaunchKernelGGL(k_mlp_fwd, dim3(B), dim3(MLP_MAX_H), 0, s, B, d, P, X, Y, act);
+    const int S = mlp_samples(d.H), big = d.H > d.out ? d.H : d.out;
+    const size_t lds = sizeof(float) * ((size_t)big * mlp_row(big) +
+                                        (size_t)S * (mlp_pad(d.in) + 2 * mlp_pad(d.H)));
+    hipLaunchKernelGGL(k_mlp_fwd, dim3((B + S - 1) / S), dim3(MLP_THREADS), lds, s, B, d, S, P, X, Y, act);
     return hipGetLastError();
 }
 
@@ -210,10 +383,11 @@ hipError_t launch_mlp_backward(int B, MlpDims d, const double* P, const float* X
     float* delta = scratch;
     double* sq = (double*)(scratch + (size_t)B * (2 * d.H + d.out) + 1);  // 8-byte aligned below
     sq = (double*)(((uintptr_t)sq + 7) & ~(uintptr_t)7);
-    hipLaunchKernelGGL(k_mlp_delta, dim3(B), dim3(MLP_MAX_H), 0, s, B, d, P, Y, act, T, delta, sq);
-    const int64_t np = mlp_num_params(d);
-    hipLaunchKernelGGL(k_mlp_wgrad, dim3((unsigned)((np + 255) / 256)), dim3(256), 0, s, B, d, X, act, delta, G);
-    hipLaunchKernelGGL(k_mlp_loss, dim3(1), dim3(256), 0, s, B, d.out, sq, loss);
+    const int S = mlp_samples(d.H);
+    const size_t lds = sizeof(float) * ((size_t)d.H * mlp_row(d.H) + (size_t)S * (mlp_pad(d.out) + mlp_pad(d.H)));
+    hipLaunchKernelGGL(k_mlp_delta, dim3((B + S - 1) / S), dim3(MLP_THREADS), lds, s, B, d, S, P, Y, act, T, delta, sq);
+    const int tiles = wg_tiles(d.H, d.in + 1) + wg_tiles(d.H, d.H + 1) + wg_tiles(d.out, d.H + 1);
+    hipLaunchKernelGGL(k_mlp_wgrad, dim3((tiles + WG_WAVES - 1) / WG_WAVES + 1), dim3(64 * WG_WAVES), 0, s, B, d, X, act, delta, sq, G, loss);
     return hipGetLastError();
 }
 
