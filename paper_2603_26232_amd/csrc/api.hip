@@ -932,8 +932,8 @@ extern "C" qaoa_status_t qaoa_topk(qaoa_batch_t h, int32_t k, uint32_t* d_idx, f
         if (!d.skip) tk += (double)(1ull << (d.n - 1)) * 8.0;
     ProfScope ps("topk", st, tk + 16.0 * P.total_tiles * k);
     HIP_TRY(launch_topk(h->ws, h->d_subs, (const int2*)(h->ws + P.o_work_all), P.total_tiles, P.B, k,
-                        (P.flags & QAOA_FLAG_TOPK_RAW) ? 0 : 1, (uint64_t*)(h->ws + P.o_keys), d_idx, d_prob,
-                        st));
+                        (P.flags & QAOA_FLAG_TOPK_RAW) ? 0 : 1, P.only_small, (uint64_t*)(h->ws + P.o_keys), d_idx,
+                        d_prob, st));
     return ok();
 }
 

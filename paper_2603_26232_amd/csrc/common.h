@@ -210,7 +210,7 @@ hipError_t launch_reduce(const SubDesc* subs, int B, int p, int grad, Partials p
                          double* dgamma, double* dbeta, hipStream_t s);
 // ---- launchers (topk.hip) ----
 hipError_t launch_topk(uint8_t* ws, const SubDesc* subs, const int2* work, int nwork, int B, int k,
-                       int canonical, uint64_t* keys, uint32_t* idx, float* prob, hipStream_t s);
+                       int canonical, bool single, uint64_t* keys, uint32_t* idx, float* prob, hipStream_t s);
 // ---- launchers (cut.hip) ----
 hipError_t launch_maxcut_eval(int32_t nV, int64_t nE, const int32_t* u, const int32_t* v,
                               const int32_t* w, int64_t A, const uint32_t* assign, int64_t* cut,

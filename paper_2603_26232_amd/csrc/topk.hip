@@ -26,15 +26,28 @@
 // the value, and a larger low word means a smaller z. Every valid key is
 // nonzero (z < 2^30), so 0 serves as padding below all of them.
 //
-// Both stages find the k largest keys of a set by a most-significant-digit
-// radix select in LDS (8-bit digits, one histogram per digit, stopping as
-// soon as every key that shares the current prefix is needed), instead of
-// sorting: stage 1 takes one 4096-amplitude tile of the reduced state per
-// block, with its candidates in registers, and writes the tile's best k
-// unsorted; stage 2 selects a subgraph's best k from its per-tile lists,
-// sorts only those and expands them.
+// Stage 1 streams the reduced state once: a block takes a run of 4096-amplitude
+// tiles (a run that crosses subgraphs starts anew in each), with the next tile's
+// amplitudes on their way, and appends the keys above a threshold to a buffer in
+// LDS, which are few after the first tile; when the buffer is full, or long
+// beyond k, it is cut to its k largest, the smallest of which is the new
+// threshold. The run's best k are written unsorted. Stage 2 selects a subgraph's
+// best k from its runs' lists, orders them by rank and expands them; where every
+// subgraph is a single tile, stage 1 does that itself.
+//
+// A selection counts keys in 256 bins over the 8 octaves of probability below
+// the largest one (1/32 octave each: most keys of a state spread over them, so
+// the LDS atomics do not meet in one bin), then over the bin that holds the k-th,
+// until a bin boundary is the answer; if fewer than k keys are in that window, it
+// starts over the whole range.
 // Canonical mode takes only z with bit 0 clear (pi(z) = pi(~z)).
-#include "common.h"
+//
+// Bound: the 8 bytes per stored amplitude that stage 1 reads. Measured on 8704
+// tiles (four subgraphs, the largest of 26 qubits), k = 16: stage 1 74 us (3.9
+// TB/s), stage 2 13 us. A list per tile and a selection by digits from the top of
+// the key, whose first digits all keys share, took 113 and 202 us; runs of four
+// tiles instead of eight 70 and 21 us.
+#include "lane.h"
 
 namespace pq {
 
@@ -111,87 +124,98 @@ __device__ inline uint32_t tie_member(const TieGroups& t, uint32_t r0, uint32_t 
 
 struct SelState {
     int hist[256];
-    int wsum[16];
-    int digit, qrem, done, count, nonzero;
+    int wsum[4];
+    uint32_t wmax[16];
+    int bin, excl, h, total, count;
     uint64_t out[MAX_K];
 };
 
-// number of nonzero keys over the block (each thread passes its own count)
-__device__ inline int count_nonzero(SelState& S, int mine)
+__device__ inline uint32_t wave_max(uint32_t x)
 {
-    if (threadIdx.x == 0) S.nonzero = 0;
-    __syncthreads();
-    for (int off = 32; off > 0; off >>= 1) mine += __shfl_xor(mine, off);
-    if ((threadIdx.x & 63u) == 0 && mine) atomicAdd(&S.nonzero, mine);
-    __syncthreads();
-    return S.nonzero;
+    auto take = [&](float y) {
+        const uint32_t u = __float_as_uint(y);
+        x = u > x ? u : x;
+    };
+    take(across<0>(__uint_as_float(x)));
+    take(across<1>(__uint_as_float(x)));
+    take(across<2>(__uint_as_float(x)));
+    take(across<3>(__uint_as_float(x)));
+    float a = __uint_as_float(x), b = a;
+    swap_halves<16>(a, b);
+    take(a);
+    take(b);
+    a = b = __uint_as_float(x);
+    swap_halves<32>(a, b);
+    take(a);
+    take(b);
+    return x;
 }
 
-// the digit (from the top) that holds the q-th largest counted key; sets
-// done when exactly q keys were counted (then all of them are taken)
-__device__ void pick_digit(SelState& S, int q)
+// the largest value over the block's waves
+__device__ inline uint32_t block_max(SelState& S, uint32_t x)
 {
-    const int t = threadIdx.x;
-    int h = 0, incl = 0;
-    if (t < 256) {
-        h = S.hist[255 - t];
-        incl = h;
-        const int lane = t & 63;
-#pragma unroll
-        for (int o = 1; o < 64; o <<= 1) {
-            const int y = __shfl_up(incl, o, 64);
-            if (lane >= o) incl += y;
-        }
-        if (lane == 63) S.wsum[t >> 6] = incl;
-    }
+    x = wave_max(x);
+    if ((threadIdx.x & 63u) == 0) S.wmax[threadIdx.x >> 6] = x;
     __syncthreads();
-    if (t < 256) {
-        int base = 0;
-        for (int w = 0; w < (t >> 6); ++w) base += S.wsum[w];
-        incl += base;
-        const int excl = incl - h;
-        if (t == 255) S.done = (incl == q);
-        if (h > 0 && excl < q && q <= incl) {
-            S.digit = 255 - t;
-            S.qrem = q - excl;
-        }
-    }
-    __syncthreads();
+    for (int w = 0; w < (int)(blockDim.x >> 6); ++w) x = S.wmax[w] > x ? S.wmax[w] : x;
+    return x;
 }
 
-// Radix select of the q largest keys produced by src(i), i < n_local per
-// thread. Returns (prefix, digits) such that a nonzero key is among the q
-// largest iff digits == 0 or key >> (64 - 8 digits) >= prefix. Zero keys
-// (padding) are not counted, so q must not exceed the number of nonzero
-// keys (otherwise no digit is found); with unique keys this selects exactly q.
-template <typename Src>
-__device__ void radix_select(SelState& S, const Src& src, int n_local, int q, uint64_t& prefix, int& digits)
+// Smallest of the q largest keys that each(f) passes to f, every thread its own
+// (zero keys are none; at least q others, all different). top: the largest upper
+// word (probability, as bits) among them. Called by every thread of the block.
+template <typename Each>
+__device__ uint64_t select_smallest(SelState& S, const Each& each, int q, uint32_t top)
 {
     const int t = threadIdx.x;
-    prefix = 0;
-    digits = 0;
-    for (int r = 0; r < 8; ++r) {
+    uint64_t hi = ((uint64_t)top << 32) | 0xFFFFFFFFull;
+    uint64_t lo = hi > (1ull << 58) ? hi - (1ull << 58) + 1ull : 1ull;
+    int shift = 50;  // (hi - lo) >> shift < 256
+    for (bool first = true;; first = false) {
+        __syncthreads();  // the last round's results have been read
         if (t < 256) S.hist[t] = 0;
         __syncthreads();
-        const int shift = 56 - 8 * r;
-        for (int i = 0; i < n_local; ++i) {
-            const uint64_t key = src(i);
-            if (key != 0ull && (r == 0 || (key >> (shift + 8)) == prefix))
-                atomicAdd(&S.hist[(int)((key >> shift) & 255)], 1);
+        each([&](uint64_t key) {
+            if (key >= lo && key <= hi) atomicAdd(&S.hist[(int)((hi - key) >> shift)], 1);
+        });
+        __syncthreads();
+        int h = 0, incl = 0;
+        if (t < 256) {
+            h = S.hist[t];
+            incl = h;
+#pragma unroll
+            for (int o = 1; o < 64; o <<= 1) {
+                const int y = __shfl_up(incl, o, 64);
+                if ((t & 63) >= o) incl += y;
+            }
+            if ((t & 63) == 63) S.wsum[t >> 6] = incl;
         }
         __syncthreads();
-        pick_digit(S, q);
-        if (S.done) return;
-        prefix = (prefix << 8) | (uint64_t)S.digit;
-        q = S.qrem;
-        digits = r + 1;
-        __syncthreads();  // everyone has read digit/qrem before the next round
+        if (t < 256) {
+            for (int w = 0; w < (t >> 6); ++w) incl += S.wsum[w];
+            if (t == 255) S.total = incl;
+            if (incl - h < q && q <= incl) {  // one bin, if any
+                S.bin = t;
+                S.excl = incl - h;
+                S.h = h;
+            }
+        }
+        __syncthreads();
+        if (first && S.total < q) {
+            lo = 1ull;
+            shift = 56;
+            continue;
+        }
+        const uint64_t b = (uint64_t)S.bin;
+        const int excl = S.excl;
+        const uint64_t top_of = hi - (b << shift);
+        const uint64_t low_of = top_of - lo >= (1ull << shift) ? top_of - (1ull << shift) + 1ull : lo;
+        if (excl + S.h == q) return low_of;
+        q -= excl;
+        hi = top_of;
+        lo = low_of;
+        shift = shift >= 8 ? shift - 8 : 0;
     }
-}
-
-__device__ inline bool selected(uint64_t key, uint64_t prefix, int digits)
-{
-    return digits == 0 || (key >> (64 - 8 * digits)) >= prefix;
 }
 
 __device__ inline uint64_t make_key(float pr, uint32_t z)
@@ -199,10 +223,50 @@ __device__ inline uint64_t make_key(float pr, uint32_t z)
     return ((uint64_t)__float_as_uint(pr) << 32) | (uint64_t)(0xFFFFFFFFu - z);
 }
 
-// stage 1: one tile of one subgraph -> its best k keys (unsorted, 0-padded)
+// The n <= k <= 64 keys of S.out (any order, all different) in descending order,
+// expanded into their groups' strings in rank order: row b of the results. The
+// first wave does the work; S.out is in place (a barrier before).
+__device__ inline void write_row(const SelState& S, const TieGroups& tg, int n, int b, int k, uint32_t* idx,
+                                 float* prob, uint64_t* sorted)
+{
+    const int lane = threadIdx.x;
+    if (lane >= 64) return;
+    if (lane < n) {
+        const uint64_t key = S.out[lane];
+        int rank = 0;
+        for (int j = 0; j < n; ++j) rank += S.out[j] > key;
+        sorted[rank] = key;
+    }
+    asm volatile("" ::: "memory");  // one wave: the LDS keeps issue order
+    if (lane >= k) return;
+    const int g = tg.m >= 6 ? 0 : lane >> tg.m;  // group of output `lane`, and its string
+    const uint32_t j = tg.m >= 6 ? (uint32_t)lane : (uint32_t)lane & ((1u << tg.m) - 1u);
+    uint32_t z = 0xFFFFFFFFu;
+    float pr = -1.0f;
+    if (g < n) {
+        const uint64_t key = sorted[g];
+        z = tie_member(tg, 0xFFFFFFFFu - (uint32_t)(key & 0xFFFFFFFFull), j);
+        pr = __uint_as_float((uint32_t)(key >> 32));
+    }
+    idx[(size_t)b * k + lane] = z;
+    prob[(size_t)b * k + lane] = pr;
+}
+
+// stage 1: tiles [blockIdx * run, + run) of the batch. Each subgraph's part of
+// the run leaves its best k keys (unsorted, 0-padded) at slot k * (its first
+// tile); with finish (one tile per subgraph) the results.
+//
+// The first tile of a part has no threshold yet. A lower bound of it is the k-th
+// largest of the threads' largest keys: at most k threads have keys that large,
+// so at most 64 x 32 keys are appended. The same bound is taken where a later
+// tile's candidates do not fit.
+constexpr int SLACK = 256;  // keys beyond k that are kept before the buffer is cut
+constexpr int BUF = MAX_K * 32 + MAX_K + SLACK;
+
 template <bool CANON>
-__global__ __launch_bounds__(THREADS) void k_topk_tile(const uint8_t* ws, const SubDesc* subs, const int2* work,
-                                                      int k, uint64_t* out)
+__global__ __launch_bounds__(THREADS) void k_topk_run(const uint8_t* ws, const SubDesc* subs, const int2* work,
+                                                     int total, int run, int k, int finish, uint64_t* out,
+                                                     uint32_t* idx, float* prob)
 {
     // The stored state is reduced: amplitude z' (top bit clear, scaled by
     // sqrt(2)) stands for z' and its complement z' ^ (2^n - 1), each with
@@ -211,61 +275,140 @@ __global__ __launch_bounds__(THREADS) void k_topk_tile(const uint8_t* ws, const 
     constexpr int AMPS = TILE / THREADS;          // 16 amplitudes per thread
     constexpr int PER = CANON ? AMPS : 2 * AMPS;  // candidates per thread
     __shared__ SelState S;
-    const int2 wk = work[blockIdx.x];
-    const SubDesc* d = subs + wk.x;
-    const int n = d->n;
-    const uint32_t base = (uint32_t)wk.y * TILE;
-    const float2* st = (const float2*)(ws + d->psi) + base;
-    const uint32_t span = n - 1 < TILE_BITS ? (1u << (n - 1)) : (uint32_t)TILE;
-    const uint32_t full = (uint32_t)((1ull << n) - 1ull);
-    const TieGroups tg = tie_groups(d, CANON ? 1 : 0);
-    const int t = threadIdx.x;
-    uint64_t key[PER];
+    __shared__ uint64_t buf[BUF];
+    const int t = threadIdx.x, lane = t & 63;
+    const uint64_t below = (1ull << lane) - 1ull;
+    const int end = (blockIdx.x + 1) * run < total ? (blockIdx.x + 1) * run : total;
+    for (int first = blockIdx.x * run; first < end;) {
+        const int2 wk = work[first];
+        const SubDesc* d = subs + wk.x;
+        const int last = d->tile_base + d->ntiles < end ? d->tile_base + d->ntiles : end;
+        const int n = d->n;
+        const uint32_t span = n - 1 < TILE_BITS ? (1u << (n - 1)) : (uint32_t)TILE;
+        const uint32_t full = (uint32_t)((1ull << n) - 1ull);
+        const TieGroups tg = tie_groups(d, CANON ? 1 : 0);
+        const float2* st = (const float2*)(ws + d->psi) + (size_t)wk.y * TILE;
+        uint32_t base = (uint32_t)wk.y * TILE;
+        float2 next[AMPS];
+        auto load = [&](const float2* p) {
 #pragma unroll
-    for (int j = 0; j < AMPS; ++j) {
-        const uint32_t c = (uint32_t)t + (uint32_t)j * THREADS;
-        const bool ok = c < span;
-        float2 a = make_float2(0.f, 0.f);
-        if (ok) a = st[c];
-        const float pr = 0.5f * (a.x * a.x + a.y * a.y);
-        const uint32_t z = base + c;
-        // only the representatives of tie groups are ranked
-        if (CANON) {
-            const uint32_t zc = (z & 1u) ? z ^ full : z;
-            key[j] = (ok && is_representative(tg, zc)) ? make_key(pr, zc) : 0ull;
-        } else {
-            key[2 * j] = (ok && is_representative(tg, z)) ? make_key(pr, z) : 0ull;
-            key[2 * j + 1] = (ok && is_representative(tg, z ^ full)) ? make_key(pr, z ^ full) : 0ull;
+            for (int j = 0; j < AMPS; ++j) {
+                const uint32_t c = (uint32_t)t + (uint32_t)j * THREADS;
+                next[j] = c < span ? p[c] : make_float2(0.f, 0.f);
+            }
+        };
+        load(st);
+        uint64_t thr = 0;  // keys above it are candidates
+        int nbuf = 0;
+        if (t == 0) S.count = 0;
+        auto buffered = [&](int m, auto f) {
+            for (int i = t; i < m; i += THREADS) f(buf[i]);
+        };
+        auto buffer_top = [&](int m) {
+            uint32_t top = 0;
+            buffered(m, [&](uint64_t x) { top = (uint32_t)(x >> 32) > top ? (uint32_t)(x >> 32) : top; });
+            return block_max(S, top);
+        };
+        __syncthreads();
+        for (int tile = first; tile < last; ++tile, base += TILE) {
+            float pr[AMPS];
+#pragma unroll
+            for (int j = 0; j < AMPS; ++j) pr[j] = 0.5f * (next[j].x * next[j].x + next[j].y * next[j].y);
+            if (tile + 1 < last) load(st + (size_t)(tile + 1 - first) * TILE);
+            // candidate i of the tile: its key, or 0 (only the representatives
+            // of tie groups are ranked)
+            auto key_of = [&](int i) -> uint64_t {
+                const int j = CANON ? i : i >> 1;
+                const uint32_t c = (uint32_t)t + (uint32_t)j * THREADS;
+                uint32_t z = base + c;
+                if (CANON ? (z & 1u) : (uint32_t)(i & 1)) z ^= full;
+                return c < span && is_representative(tg, z) ? make_key(pr[j], z) : 0ull;
+            };
+            int now = 0;
+            for (bool bound = tile == first;; bound = true) {
+                if (bound) {
+                    uint64_t mx = 0;
+#pragma unroll
+                    for (int i = 0; i < PER; ++i) {
+                        const uint64_t key = key_of(i);
+                        mx = key > thr && key > mx ? key : mx;
+                    }
+                    const int some = __syncthreads_count(mx != 0ull);
+                    if (some >= k) {
+                        const uint32_t top = block_max(S, (uint32_t)(mx >> 32));
+                        thr = select_smallest(S, [&](auto f) { f(mx); }, k, top) - 1ull;
+                    }
+                }
+                const uint32_t pmin = (uint32_t)(thr >> 32);
+#pragma unroll
+                for (int i = 0; i < PER; ++i) {
+                    if (__ballot(__float_as_uint(pr[CANON ? i : i >> 1]) >= pmin) == 0ull) continue;
+                    const uint64_t key = key_of(i);
+                    const uint64_t mask = __ballot(key > thr);
+                    if (mask == 0ull) continue;
+                    int at = 0;
+                    if (lane == 0) at = atomicAdd(&S.count, __popcll(mask));
+                    at = __shfl(at, 0) + __popcll(mask & below);
+                    if (key > thr && at < BUF) buf[at] = key;
+                }
+                __syncthreads();
+                now = S.count;
+                if (now <= BUF) break;
+                __syncthreads();  // (every thread has read the count)
+                if (t == 0) S.count = nbuf;
+                __syncthreads();
+            }
+            nbuf = now;
+            if (now > k + SLACK) {
+                const uint32_t top = buffer_top(now);
+                const uint64_t low = select_smallest(S, [&](auto f) { buffered(now, f); }, k, top);
+                // the survivors, over the front of the buffer
+                constexpr int EACH = (BUF + THREADS - 1) / THREADS;
+                uint64_t mine[EACH];
+#pragma unroll
+                for (int i = 0; i < EACH; ++i) mine[i] = t + i * THREADS < now ? buf[t + i * THREADS] : 0ull;
+                __syncthreads();
+                if (t == 0) S.count = 0;
+                __syncthreads();
+#pragma unroll
+                for (int i = 0; i < EACH; ++i)
+                    if (mine[i] >= low) buf[atomicAdd(&S.count, 1)] = mine[i];
+                thr = low - 1ull;
+                nbuf = k;
+            }
+            __syncthreads();
         }
-    }
-    int mine = 0;
-#pragma unroll
-    for (int i = 0; i < PER; ++i) mine += key[i] != 0ull;
-    const int cnt = count_nonzero(S, mine);  // the tile's representatives
-    const int q = k < cnt ? k : cnt;
-    uint64_t prefix = 0;
-    int digits = 0;
-    if (t == 0) S.count = 0;
-    if (q > 0) radix_select(S, [&](int i) { return key[i]; }, PER, q, prefix, digits);
-    uint64_t* o = out + ((size_t)d->tile_base + wk.y) * k;
-#pragma unroll
-    for (int i = 0; i < PER; ++i) {
-        if (key[i] != 0ull && selected(key[i], prefix, digits)) {
-            const int slot = atomicAdd(&S.count, 1);
-            if (slot < k) o[slot] = key[i];
+        int n_out = nbuf;
+        if (nbuf > k) {
+            const uint32_t top = buffer_top(nbuf);
+            const uint64_t low = select_smallest(S, [&](auto f) { buffered(nbuf, f); }, k, top);
+            __syncthreads();
+            if (t == 0) S.count = 0;
+            __syncthreads();
+            buffered(nbuf, [&](uint64_t x) {
+                if (x >= low) S.out[atomicAdd(&S.count, 1)] = x;
+            });
+            n_out = k;
+        } else if (t < nbuf) {
+            S.out[t] = buf[t];
         }
+        __syncthreads();
+        if (finish) write_row(S, tg, n_out, wk.x, k, idx, prob, buf);
+        else if (t < k) out[(size_t)first * k + t] = t < n_out ? S.out[t] : 0ull;
+        __syncthreads();
+        first = last;
     }
-    __syncthreads();
-    for (int i = S.count + t; i < k; i += THREADS) o[i] = 0ull;
 }
 
-// stage 2: a subgraph's ntiles * k keys -> its best k, sorted; results
+// stage 2: a subgraph's lists (one per run that it has a part in) -> its best k
 constexpr int MERGE_THREADS = 1024;
+constexpr int MERGE_HELD = 16;  // keys a thread keeps in registers
 
-__global__ __launch_bounds__(MERGE_THREADS) void k_topk_merge(const SubDesc* subs, int k, int canonical,
+__global__ __launch_bounds__(MERGE_THREADS) void k_topk_merge(const SubDesc* subs, int run, int k, int canonical,
                                                              const uint64_t* in, uint32_t* idx, float* prob)
 {
     __shared__ SelState S;
+    __shared__ uint64_t sorted[MAX_K];
     const int b = blockIdx.x;
     const SubDesc* d = subs + b;
     const int t = threadIdx.x;
@@ -273,85 +416,80 @@ __global__ __launch_bounds__(MERGE_THREADS) void k_topk_merge(const SubDesc* sub
     if (d->skip) {
         // edgeless subgraph: |psi|^2 = 2^-n everywhere, so all candidates form
         // one tie group (every vertex free) with representative 0
-        if (t == 0) {
-            const uint64_t group = 1ull << tg.m;
-            for (int i = 0; i < k; ++i) {
-                const bool ok = (uint64_t)i < group;
-                idx[(size_t)b * k + i] = ok ? tie_member(tg, 0u, (uint32_t)i) : 0xFFFFFFFFu;
-                prob[(size_t)b * k + i] = ok ? ldexpf(1.0f, -d->n) : -1.0f;
-            }
+        if (t < k) {
+            const bool ok = (uint64_t)t < (1ull << tg.m);
+            idx[(size_t)b * k + t] = ok ? tie_member(tg, 0u, (uint32_t)t) : 0xFFFFFFFFu;
+            prob[(size_t)b * k + t] = ok ? ldexpf(1.0f, -d->n) : -1.0f;
         }
         return;
     }
-    const int total = d->ntiles * k;
-    const uint64_t* src = in + (size_t)d->tile_base * k;
+    // list 0 at the subgraph's first tile, list j > 0 at the j-th run boundary after it
+    const int t0 = d->tile_base, r0 = t0 / run;
+    const int lists = (t0 + d->ntiles - 1) / run - r0 + 1, total = lists * k;
+    auto at = [&](int x) -> uint64_t {
+        const int j = x / k;
+        return in[(size_t)(j == 0 ? t0 : (r0 + j) * run) * k + (x - j * k)];
+    };
     const int nloc = (total - t + MERGE_THREADS - 1) / MERGE_THREADS;  // keys t, t + 1024, ...
-    uint64_t prefix = 0;
-    int digits = 0;
-    int mine = 0;
-    for (int i = 0; i < nloc; ++i) mine += src[t + (size_t)i * MERGE_THREADS] != 0ull;
-    const int cnt = count_nonzero(S, mine);
-    const int q = k < cnt ? k : cnt;
+    const bool held = total <= MERGE_HELD * MERGE_THREADS;
+    uint64_t key[MERGE_HELD];
+#pragma unroll
+    for (int i = 0; i < MERGE_HELD; ++i) key[i] = held && i < nloc ? at(t + i * MERGE_THREADS) : 0ull;
     if (t == 0) S.count = 0;
-    if (t < MAX_K) S.out[t] = 0ull;
-    if (q > 0) radix_select(S, [&](int i) { return src[t + (size_t)i * MERGE_THREADS]; }, nloc, q, prefix, digits);
-    for (int i = 0; i < nloc; ++i) {
-        const uint64_t key = src[t + (size_t)i * MERGE_THREADS];
-        if (key != 0ull && selected(key, prefix, digits)) {
-            const int slot = atomicAdd(&S.count, 1);
-            if (slot < k) S.out[slot] = key;
-        }
-    }
     __syncthreads();
-    // sort the (at most 64) winners descending: bitonic over 64 slots
-    for (int size = 2; size <= MAX_K; size <<= 1) {
-        for (int stride = size >> 1; stride > 0; stride >>= 1) {
-            if (t < MAX_K / 2) {
-                const int lo = 2 * stride * (t / stride) + (t % stride);
-                const int hi = lo + stride;
-                const uint64_t a = S.out[lo], c = S.out[hi];
-                const bool desc = (lo & size) == 0;
-                if (desc ? (a < c) : (a > c)) {
-                    S.out[lo] = c;
-                    S.out[hi] = a;
-                }
-            }
-            __syncthreads();
+    uint32_t top = 0;
+    int mine = 0;
+    auto each = [&](auto f) {
+        if (held) {
+#pragma unroll
+            for (int i = 0; i < MERGE_HELD; ++i) f(key[i]);
+        } else {
+            for (int i = 0; i < nloc; ++i) f(at(t + i * MERGE_THREADS));
         }
-    }
-    // expand the selected groups, in order, into their strings in rank order
-    if (t == 0) {
-        const uint64_t group = 1ull << tg.m;
-        int out = 0;
-        for (int i = 0; i < k && out < k; ++i) {
-            const uint64_t key = S.out[i];
-            if (key == 0ull) break;
-            const uint32_t r0 = 0xFFFFFFFFu - (uint32_t)(key & 0xFFFFFFFFull);
-            const float pr = __uint_as_float((uint32_t)(key >> 32));
-            for (uint64_t j = 0; j < group && out < k; ++j, ++out) {
-                idx[(size_t)b * k + out] = tie_member(tg, r0, (uint32_t)j);
-                prob[(size_t)b * k + out] = pr;
-            }
-        }
-        for (; out < k; ++out) {
-            idx[(size_t)b * k + out] = 0xFFFFFFFFu;
-            prob[(size_t)b * k + out] = -1.0f;
-        }
-    }
+    };
+    each([&](uint64_t x) {
+        top = (uint32_t)(x >> 32) > top ? (uint32_t)(x >> 32) : top;
+        mine += x != 0ull;
+    });
+    for (int off = 32; off > 0; off >>= 1) mine += __shfl_xor(mine, off);
+    if ((t & 63) == 0 && mine) atomicAdd(&S.count, mine);
+    top = block_max(S, top);  // (its barrier also shows the count)
+    const int cnt = S.count;
+    const uint64_t low = cnt > k ? select_smallest(S, each, k, top) : 1ull;
+    __syncthreads();
+    if (t == 0) S.count = 0;
+    __syncthreads();
+    each([&](uint64_t x) {
+        if (x >= low) S.out[atomicAdd(&S.count, 1)] = x;
+    });
+    __syncthreads();
+    write_row(S, tg, cnt < k ? cnt : k, b, k, idx, prob, sorted);
 }
 
-hipError_t launch_topk(uint8_t* ws, const SubDesc* subs, const int2* work, int nwork, int B, int k,
-                       int canonical, uint64_t* keys, uint32_t* idx, float* prob, hipStream_t s)
+// Tiles per run: enough blocks for the chip (about 1024, four per CU) and few
+// lists per subgraph; 1 while the batch has fewer tiles than that.
+static int topk_run(int total)
 {
+    int run = 1;
+    while (run < 256 && total / (2 * run) >= 1024) run *= 2;
+    return run;
+}
+
+// single: no subgraph has more than one tile and none is skipped
+hipError_t launch_topk(uint8_t* ws, const SubDesc* subs, const int2* work, int nwork, int B, int k, int canonical,
+                       bool single, uint64_t* keys, uint32_t* idx, float* prob, hipStream_t s)
+{
+    const int run = topk_run(nwork), finish = single && run == 1;
     if (nwork > 0) {
+        const dim3 g((nwork + run - 1) / run), b(THREADS);
         if (canonical)
-            hipLaunchKernelGGL(k_topk_tile<true>, dim3(nwork), dim3(THREADS), 0, s, ws, subs, work, k, keys);
+            hipLaunchKernelGGL(k_topk_run<true>, g, b, 0, s, ws, subs, work, nwork, run, k, finish, keys, idx, prob);
         else
-            hipLaunchKernelGGL(k_topk_tile<false>, dim3(nwork), dim3(THREADS), 0, s, ws, subs, work, k, keys);
+            hipLaunchKernelGGL(k_topk_run<false>, g, b, 0, s, ws, subs, work, nwork, run, k, finish, keys, idx, prob);
         hipError_t e = hipGetLastError();
-        if (e != hipSuccess) return e;
+        if (e != hipSuccess || finish) return e;
     }
-    hipLaunchKernelGGL(k_topk_merge, dim3(B), dim3(MERGE_THREADS), 0, s, subs, k, canonical, keys, idx, prob);
+    hipLaunchKernelGGL(k_topk_merge, dim3(B), dim3(MERGE_THREADS), 0, s, subs, run, k, canonical, keys, idx, prob);
     return hipGetLastError();
 }
 
