@@ -1170,7 +1170,7 @@ MergePlan merge_plan(int32_t nV, int32_t M, int64_t nE, int32_t K, int32_t W)
     P.o_scores = region(sizeof(int64_t) * W);
     P.o_lvs = region(sizeof(MergeLvState) * (M + 1));
     P.o_maxinc = region(sizeof(uint32_t) * M);
-    P.o_hist = region(sizeof(int32_t) * MERGE_HIST_INTS);
+    P.o_hist = region(sizeof(int32_t) * MERGE_COPIES * MERGE_HIST_INTS);
     P.o_below = region(sizeof(int32_t));
     P.o_pcnt = region(sizeof(int64_t) * W);
     P.o_lvk = region(sizeof(int32_t) * M);

@@ -125,7 +125,8 @@ struct MergeLvState {
     int32_t count;   // survivors
 };
 
-constexpr int MERGE_HIST_INTS = 65536 + 4096;  // fine + coarse bins
+constexpr int MERGE_HIST_INTS = 65536 + 4096 + 256;  // fine + coarse + super bins of one copy
+constexpr int MERGE_COPIES = 8;                      // copies of the histogram
 
 struct MergeBufs {
     const MergeLevel* lv;
@@ -140,7 +141,7 @@ struct MergeBufs {
     MergeLvState* lvs;  // [M]
     uint32_t* maxinc;   // [M] largest possible score increment of level i
     int32_t* lvk;       // [M] valid candidates of level i
-    int32_t* hist;      // [MERGE_HIST_INTS]
+    int32_t* hist;      // [MERGE_COPIES][MERGE_HIST_INTS]
     int32_t* below;     // keys below the histogram's window
     int64_t* pcnt;      // [W] per parent: survivors above (low) / at (high) the threshold
 };

@@ -25,20 +25,21 @@
 // Level 1 (2K keys) runs in one workgroup (k_merge_select + k_merge_build).
 // Every later level runs in three launches over all surviving parents:
 //   expand  - the children's keys, and a histogram of (H - key): 65536 fine
-//             bins of one key value and 4096 coarse bins of 16, H an upper
+//             bins of one key value, 4096 coarse bins of 16 and 256 super bins
+//             of 256, H an upper
 //             bound of the level's keys (previous best key + the level's
 //             largest possible increment); each block aggregates its keys in
 //             LDS and adds only its nonzero bins to the global histogram;
 //   count   - every block finds the threshold key k* (keys above it survive,
 //             plus the first R keys equal to it in path order) from the
-//             coarse bins and 16 fine bins, then counts its parents'
+//             super bins, 16 coarse and 16 fine bins, then counts its parents'
 //             survivors; if the W-th key lies below the histogram's window
 //             (scores spread over more than 65536 values) each block
 //             computes k* from the keys themselves instead;
 //   scatter - the prefix of the per-parent counts gives each survivor its
-//             position; the survivors' rows are built; the histogram is
-//             cleared for the next level.
-#include "common.h"
+//             position; the survivors' rows are built; the histogram's super
+//             bins that hold something are cleared for the next level.
+#include "lane.h"
 
 namespace pq {
 
@@ -47,7 +48,10 @@ __device__ inline uint32_t row_bit(const uint32_t* row, int v) { return (row[v >
 constexpr int FINE_BINS = 65536;
 constexpr int COARSE_SHIFT = 4;
 constexpr int COARSE_BINS = FINE_BINS >> COARSE_SHIFT;  // 4096
-static_assert(FINE_BINS + COARSE_BINS == MERGE_HIST_INTS, "histogram layout");
+constexpr int SUPER_SHIFT = 8;
+constexpr int SUPER_BINS = FINE_BINS >> SUPER_SHIFT;    // 256
+constexpr int SUPER_AT = FINE_BINS + COARSE_BINS;
+static_assert(SUPER_AT + SUPER_BINS == MERGE_HIST_INTS, "histogram layout");
 constexpr int MX_THREADS = 256;  // expand / count / scatter blocks
 constexpr int LOCAL_BINS = 1024;
 
@@ -55,10 +59,15 @@ constexpr int LOCAL_BINS = 1024;
 // (those before the first 0xFFFFFFFF of the row); the level's largest
 // possible score increment (max_j C_i(b_j) + its total back-edge weight); the
 // histogram cleared for level 2. One wave per level (K <= 64).
-__global__ void k_merge_intra(const MergeLevel* lv, const int32_t* intra, const uint32_t* cand, int K, int64_t* ccut,
+__global__ void k_merge_intra(int M, const MergeLevel* lv, const int32_t* intra, const uint32_t* cand, int K, int64_t* ccut,
                               int32_t* lvk, uint32_t* maxinc, int32_t* hist, int32_t* below)
 {
     const int i = blockIdx.x;
+    for (int x = blockIdx.x * blockDim.x + threadIdx.x; x < MERGE_COPIES * MERGE_HIST_INTS / 4;
+         x += gridDim.x * blockDim.x)
+        ((int4*)hist)[x] = make_int4(0, 0, 0, 0);
+    if (i == 0 && threadIdx.x == 0) *below = 0;
+    if (i >= M) return;  // (these blocks only clear)
     const MergeLevel& L = lv[i];
     {
         const int lane = threadIdx.x;
@@ -88,8 +97,6 @@ __global__ void k_merge_intra(const MergeLevel* lv, const int32_t* intra, const 
         for (int k = 0; k < 32; ++k) wb += L.wk[k];
         maxinc[i] = (uint32_t)(best + wb);
     }
-    for (int x = blockIdx.x * blockDim.x + threadIdx.x; x < MERGE_HIST_INTS; x += gridDim.x * blockDim.x) hist[x] = 0;
-    if (i == 0 && threadIdx.x == 0) *below = 0;
 }
 
 // level 1: the 2 K_1 paths (j, o) in order b_1, ~b_1, b_2, ~b_2, ...
@@ -115,23 +122,28 @@ __device__ inline int32_t wave_sum(int32_t x)
     for (int o = 32; o > 0; o >>= 1) x += __shfl_xor(x, o, 64);
     return x;
 }
+// the wave's largest / smallest value, by lane permutations that need no LDS
+template <typename F>
+__device__ inline uint32_t wave_fold(uint32_t x, F pick)
+{
+    x = pick(x, __float_as_uint(across<0>(__uint_as_float(x))));
+    x = pick(x, __float_as_uint(across<1>(__uint_as_float(x))));
+    x = pick(x, __float_as_uint(across<2>(__uint_as_float(x))));
+    x = pick(x, __float_as_uint(across<3>(__uint_as_float(x))));
+    float a = __uint_as_float(x), c = a;
+    swap_halves<16>(a, c);
+    x = pick(__float_as_uint(a), __float_as_uint(c));
+    a = c = __uint_as_float(x);
+    swap_halves<32>(a, c);
+    return pick(__float_as_uint(a), __float_as_uint(c));
+}
 __device__ inline uint32_t wave_max(uint32_t x)
 {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) {
-        const uint32_t y = __shfl_xor(x, o, 64);
-        x = y > x ? y : x;
-    }
-    return x;
+    return wave_fold(x, [](uint32_t a, uint32_t c) { return a > c ? a : c; });
 }
 __device__ inline uint32_t wave_min(uint32_t x)
 {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) {
-        const uint32_t y = __shfl_xor(x, o, 64);
-        x = y < x ? y : x;
-    }
-    return x;
+    return wave_fold(x, [](uint32_t a, uint32_t c) { return a < c ? a : c; });
 }
 // exclusive prefix of the per-wave values slots[0..NW) at wave wv, and their
 // total (lanes 0..NW-1 read one slot each)
@@ -408,6 +420,20 @@ __global__ void k_merge_build(const MergeLevel* lv, const uint32_t* cand, const 
 // A block covers PPB = MX_THREADS / Kp parents, Kp = K rounded up to a power
 // of two; thread t is child j = t % Kp of local parent t / Kp (j >= K idle),
 // so a parent's children are consecutive lanes of one wave.
+//
+// A level is a chain of dependent steps, so its time is latency: at 2000
+// vertices (104 subgraphs, K 16, W 4096: 256 blocks, 65536 keys a level) the
+// three launches take 11.3 + 6.4 + 7.5 us and a whole merge 2.57 ms (before the
+// histogram had copies 21 us for expand and 3.4 ms, before the loads were issued
+// ahead of their use and the rows staged as one flat range 4.27 ms). Expand was
+// bound by the blocks' additions to the same lines of the histogram: with 2
+// blocks it took 5 us, with 256 always 19 or more. So where there are many
+// blocks, eight copies share them, and count sums the copies, which three
+// levels of bins keep short: 256 super bins, one per thread, then 16 coarse and
+// 16 fine ones, each by one wave-wide load. The line lies at 64
+// blocks, where both cost the same; a level with one copy / with eight, in us
+// (1000 vertices, K 16): 32 blocks 27.2 / 29.6, 64 29.4 / 29.7, 128 33.4 / 30.0,
+// 256 41.8 / 32.2; K 64: 32 21.8 / 23.6, 128 27.6 / 24.2, 1024 83.5 / 48.9.
 
 constexpr int EDGE_STAGE = 2048;  // back edges staged in LDS per round
 constexpr int ROW_STAGE = 4096;   // row words staged in LDS (else read from memory)
@@ -418,38 +444,53 @@ __global__ __launch_bounds__(MX_THREADS) void k_merge_expand(const MergeLevel* l
                                                              const uint32_t* rows, int nw, const int64_t* scores,
                                                              const int32_t* npaths, const MergeLvState* lvs,
                                                              const uint32_t* maxinc, uint32_t* keys, int32_t* hist,
-                                                             int32_t* below)
+                                                             int copies, int32_t* below)
 {
     __shared__ int32_t A[MX_THREADS][32];
     __shared__ int32_t lh[LOCAL_BINS];
     __shared__ int32_t se_u[EDGE_STAGE], se_w[EDGE_STAGE];
     __shared__ uint32_t srow[ROW_STAGE];
-    __shared__ int32_t s_kbeg[33];
+    __shared__ int32_t s_kbeg[33], s_wk[32];
     __shared__ uint32_t s_dmin;
     const int t = threadIdx.x;
     const int PPB = MX_THREADS >> lgKp;
     const int pl = t >> lgKp, j = t & ((1 << lgKp) - 1);
     const int p0 = blockIdx.x * PPB;
-    const int np = npaths[i];
+    // (every uniform value is read before the first is waited for)
+    const MergeLevel& L = lv[i];
+    const int np = npaths[i], start = L.start, size = L.size, back_off = L.back_off, nb = L.kbeg[32];
+    const int valid = lvk[i];
+    const uint32_t H = lvs[i - 1].best + maxinc[i];  // >= every key of the level
     if (p0 >= np) return;  // uniform
     const int nact = np - p0 < PPB ? np - p0 : PPB;
-    const MergeLevel& L = lv[i];
     const int p = p0 + pl;
     const bool mine = pl < nact && j < K;
-    // this child's inputs, loaded ahead of the staging
+    // this child's inputs, loaded ahead of the staging (total weights < 2^31)
     const uint32_t b = mine ? cand[(size_t)i * K + j] : 0u;
-    const int64_t base_score = mine ? scores[p] + ccut[(size_t)i * K + j] : 0;
-    const bool act = mine && j < lvk[i];
-    const uint32_t H = lvs[i - 1].best + maxinc[i];  // >= every key of the level
+    const int32_t base_score = mine ? (int32_t)(scores[p] + ccut[(size_t)i * K + j]) : 0;
+    const bool act = mine && j < valid;
     // rows of the block's parents up to the word of the shared vertex
-    const int wl = (L.start >> 5) + 1;
+    const int wl = (start >> 5) + 1;
     const bool rows_lds = nact * wl <= ROW_STAGE;
-    if (rows_lds)
-        for (int q = 0; q < nact; ++q)
-            for (int w = t; w < wl; w += MX_THREADS) srow[q * wl + w] = rows[(size_t)(p0 + q) * nw + w];
+    if (rows_lds) {
+        // lanes over words, then parents: 2^lw >= wl words
+        int lw = 0;
+        while ((1 << lw) < wl) ++lw;
+        const int per = MX_THREADS >> lw;  // parents at a time (0: more words than threads)
+        if (per > 0) {
+            const int w = t & ((1 << lw) - 1);
+#pragma unroll 4
+            for (int q = t >> lw; q < nact; q += per)
+                if (w < wl) srow[q * wl + w] = rows[(size_t)(p0 + q) * nw + w];
+        } else {
+            for (int q = 0; q < nact; ++q)
+                for (int w = t; w < wl; w += MX_THREADS) srow[q * wl + w] = rows[(size_t)(p0 + q) * nw + w];
+        }
+    }
     for (int x = t; x < LOCAL_BINS; x += MX_THREADS) lh[x] = 0;
     for (int x = t; x < nact * 32; x += MX_THREADS) A[x >> 5][x & 31] = 0;
     if (t < 33) s_kbeg[t] = L.kbeg[t];
+    if (t >= 64 && t < 96) s_wk[t - 64] = (int32_t)L.wk[t - 64];
     if (t == 0) s_dmin = 0xFFFFFFFFu;
     auto bit_of = [&](int q, int v) -> uint32_t {
         return rows_lds ? (srow[q * wl + (v >> 5)] >> (v & 31)) & 1u : row_bit(rows + (size_t)(p0 + q) * nw, v);
@@ -457,12 +498,12 @@ __global__ __launch_bounds__(MX_THREADS) void k_merge_expand(const MergeLevel* l
     // back-edge weights A_k of every parent: the thread that owns (q, k) sums
     // the edges into local vertex k (sorted by k) whose earlier endpoint is 1
     // in parent q
-    const int nb = L.kbeg[32];
     for (int e0 = 0; e0 < nb || e0 == 0; e0 += EDGE_STAGE) {
         const int ne = nb - e0 < EDGE_STAGE ? nb - e0 : EDGE_STAGE;
-        __syncthreads();  // the previous round's readers are done (first round: staging above is visible)
+        if (e0) __syncthreads();  // the previous round's readers are done
+#pragma unroll 4
         for (int x = t; x < ne; x += MX_THREADS) {
-            const int32_t* E = back + 3 * (size_t)(L.back_off + e0 + x);
+            const int32_t* E = back + 3 * (size_t)(back_off + e0 + x);
             se_u[x] = E[0];
             se_w[x] = E[2];
         }
@@ -487,27 +528,26 @@ __global__ __launch_bounds__(MX_THREADS) void k_merge_expand(const MergeLevel* l
     __syncthreads();
     uint32_t key = 0;
     if (act) {
-        const uint32_t o = (b & 1u) ^ bit_of(pl, L.start);
-        int64_t s = base_score;
-        const int size = L.size;
-        for (int k = 1; k < size; ++k) {
-            const uint32_t y = ((b >> k) & 1u) ^ o;
-            s += y ? (L.wk[k] - (int64_t)A[pl][k]) : (int64_t)A[pl][k];
-        }
+        const uint32_t y = b ^ (((b & 1u) ^ bit_of(pl, start)) ? 0xFFFFFFFFu : 0u);
+        int32_t s = base_score;
+        // (vertices beyond the level's size have no back edges: A and W are 0)
+#pragma unroll 8
+        for (int k = 1; k < size; ++k) s += (y >> k) & 1u ? s_wk[k] - A[pl][k] : A[pl][k];
         key = (uint32_t)(s + 1);
     }
     if (mine) keys[(size_t)p * K + j] = key;
     // histogram of d = H - key
     const uint32_t d = H - key;
     const bool inwin = key != 0u && d < (uint32_t)FINE_BINS;
-    const int32_t nbelow = wave_sum(key != 0u && !inwin);
+    const int32_t nbelow = __popcll(__ballot(key != 0u && !inwin));
     if ((t & 63) == 0 && nbelow) atomicAdd(below, nbelow);
     const uint32_t wmin = wave_min(inwin ? d : 0xFFFFFFFFu);
     if ((t & 63) == 0 && wmin != 0xFFFFFFFFu) atomicMin(&s_dmin, wmin);
     __syncthreads();
     const uint32_t dmin = s_dmin;
     if (dmin == 0xFFFFFFFFu) return;  // no key of the block in the window (uniform)
-    const uint32_t base = dmin & ~(uint32_t)((1 << COARSE_SHIFT) - 1);  // local bins align with coarse bins
+    hist += (size_t)(blockIdx.x & (uint32_t)(copies - 1)) * MERGE_HIST_INTS;
+    const uint32_t base = dmin & ~(uint32_t)((1 << SUPER_SHIFT) - 1);  // local bins align with super bins
     if (inwin) {
         const uint32_t lb = d - base;
         if (lb < (uint32_t)LOCAL_BINS) {
@@ -515,10 +555,12 @@ __global__ __launch_bounds__(MX_THREADS) void k_merge_expand(const MergeLevel* l
         } else {  // the block's keys spread wider than the local window
             atomicAdd(&hist[d], 1);
             atomicAdd(&hist[FINE_BINS + (d >> COARSE_SHIFT)], 1);
+            atomicAdd(&hist[SUPER_AT + (d >> SUPER_SHIFT)], 1);
         }
     }
     __syncthreads();
-    // flush: thread t owns local bins 4t .. 4t + 3; four threads make one coarse bin
+    // flush: thread t owns local bins 4t .. 4t + 3; four threads make one coarse
+    // bin, a wave one super bin
     int32_t c4 = 0;
 #pragma unroll
     for (int c = 0; c < 4; ++c) {
@@ -529,6 +571,37 @@ __global__ __launch_bounds__(MX_THREADS) void k_merge_expand(const MergeLevel* l
     c4 += __shfl_xor(c4, 1, 64);
     c4 += __shfl_xor(c4, 2, 64);
     if ((t & 3) == 0 && c4) atomicAdd(&hist[FINE_BINS + (base >> COARSE_SHIFT) + (t >> 2)], c4);
+#pragma unroll
+    for (int o = 4; o < 64; o <<= 1) c4 += __shfl_xor(c4, o, 64);
+    if ((t & 63) == 0 && c4) atomicAdd(&hist[SUPER_AT + (base >> SUPER_SHIFT) + (t >> 6)], c4);
+}
+
+// bin x + lane % 16 summed over the copies, in every lane of a wave
+__device__ inline int32_t copies_sum(const int32_t* hist, int x, int copies)
+{
+    const int lane = threadIdx.x & 63;
+    int32_t n = 0;
+    for (int c = lane >> 4; c < copies; c += 4) n += hist[(size_t)c * MERGE_HIST_INTS + x + (lane & 15)];
+    n += __shfl_xor(n, 16, 64);
+    return n + __shfl_xor(n, 32, 64);
+}
+
+// Of 16 bins (one per lane, repeated four times): the first nonzero one, and the
+// one in which the running count, started at `above`, reaches `need` (above
+// becomes the count before it).
+__device__ inline int first_bin(int32_t n) { return __ffsll((unsigned long long)__ballot(n != 0)) - 1; }
+__device__ inline int crossing_bin(int32_t n, int32_t need, int32_t& above)
+{
+    const int c = threadIdx.x & 15;
+    int32_t upto = n;
+#pragma unroll
+    for (int o = 1; o < 16; o <<= 1) {
+        const int32_t y = __shfl_up(upto, o, 16);
+        if (c >= o) upto += y;
+    }
+    const int at = __ffsll((unsigned long long)__ballot(above + upto >= need)) - 1;
+    above += __shfl(upto - n, at, 64);
+    return at;
 }
 
 // Threshold of the level from the histogram (every block identically), then
@@ -537,24 +610,24 @@ __global__ __launch_bounds__(MX_THREADS) void k_merge_expand(const MergeLevel* l
 __global__ __launch_bounds__(MX_THREADS) void k_merge_count(int i, int K, int lgKp, const int32_t* npaths_in,
                                                             int Wsel, const MergeLvState* lvs_prev,
                                                             const uint32_t* maxinc, const uint32_t* keys,
-                                                            const int32_t* hist, const int32_t* below,
+                                                            const int32_t* hist, int copies, const int32_t* below,
                                                             int64_t* pcnt, MergeLvState* st, int32_t* npaths_out)
 {
     __shared__ SelShared<MX_THREADS> S;
     __shared__ int32_t s_first, s_cross;
     constexpr int NW = MX_THREADS / 64;
-    constexpr int CPT = COARSE_BINS / MX_THREADS;  // 16 coarse bins per thread
+    static_assert(SUPER_BINS == MX_THREADS, "one super bin per thread");
     const int t = threadIdx.x, lane = t & 63, wv = t >> 6;
-    const int np = *npaths_in;
+    // this parent's keys and every uniform value are read before the first is waited for
+    const int PPB = MX_THREADS >> lgKp;
+    const int pl = t >> lgKp, j = t & ((1 << lgKp) - 1);
+    const int p = blockIdx.x * PPB + pl;
+    const int np = *npaths_in, nbelow = *below;
+    const uint32_t key = (p < np && j < K) ? keys[(size_t)p * K + j] : 0u;
     const int32_t N = np * K;
     const uint32_t H = lvs_prev->best + maxinc[i];
-    const int32_t* coarse = hist + FINE_BINS;
-    int32_t cb[CPT], part = 0;
-#pragma unroll
-    for (int c = 0; c < CPT; ++c) {
-        cb[c] = coarse[CPT * t + c];
-        part += cb[c];
-    }
+    int32_t part = 0;
+    for (int c = 0; c < copies; ++c) part += hist[(size_t)c * MERGE_HIST_INTS + SUPER_AT + t];
     int32_t incl = part;
 #pragma unroll
     for (int o = 1; o < 64; o <<= 1) {
@@ -563,26 +636,21 @@ __global__ __launch_bounds__(MX_THREADS) void k_merge_count(int i, int K, int lg
     }
     if (lane == 63) S.wa[wv] = incl;
     if (t == 0) {
-        s_first = COARSE_BINS;
+        s_first = SUPER_BINS;
         s_cross = -1;
     }
     __syncthreads();
     int32_t wbefore, inwin;
     wave_slots_prefix<NW>(S.wa, wv, wbefore, inwin);
-    const int32_t nvalid = inwin + *below;
+    const int32_t nvalid = inwin + nbelow;
     const int32_t need = nvalid < Wsel ? nvalid : Wsel;  // survivors
-    int32_t run = wbefore + incl - part;
-    int first = -1;
-#pragma unroll
-    for (int c = 0; c < CPT; ++c) {
-        if (cb[c] && first < 0) first = CPT * t + c;
-        if (run < need && run + cb[c] >= need) {  // exactly one bin of one thread, if any
-            S.s_above = run;
-            s_cross = CPT * t + c;
-        }
-        run += cb[c];
+    const int32_t run = wbefore + incl - part;
+    if (run < need && run + part >= need) {  // exactly one thread, if any
+        S.s_above = run;
+        s_cross = t;
     }
-    if (first >= 0) atomicMin(&s_first, first);
+    const uint64_t some = __ballot(part != 0);
+    if (lane == 0 && some) atomicMin(&s_first, (wv << 6) + __ffsll((unsigned long long)some) - 1);
     __syncthreads();
     SelResult res;
     res.nvalid = nvalid;
@@ -590,27 +658,19 @@ __global__ __launch_bounds__(MX_THREADS) void k_merge_count(int i, int K, int lg
     res.kstar = 0;
     res.R = 0;
     if (need > 0 && s_cross >= 0) {
-        // fine bins of the first nonzero coarse bin (the best key) and of the crossing one
-        const int fb = s_first << COARSE_SHIFT;
-        int dtop = fb;
-        for (int c = 0; c < (1 << COARSE_SHIFT); ++c)
-            if (hist[fb + c]) {
-                dtop = fb + c;
-                break;
-            }
-        res.best = H - (uint32_t)dtop;
+        // the best key: first super, coarse and fine bin; the threshold: the
+        // crossing ones (every wave computes the same)
+        const int32_t* coarse = hist + FINE_BINS;
+        int32_t above = S.s_above;
+        const int32_t f1 = copies_sum(coarse, s_first << 4, copies), x1 = copies_sum(coarse, s_cross << 4, copies);
+        const int fb = ((s_first << 4) + first_bin(f1)) << COARSE_SHIFT;
+        const int xb = ((s_cross << 4) + crossing_bin(x1, need, above)) << COARSE_SHIFT;
+        const int32_t f2 = copies_sum(hist, fb, copies), x2 = copies_sum(hist, xb, copies);
+        res.best = H - (uint32_t)(fb + first_bin(f2));
+        const int at = crossing_bin(x2, need, above);
         if (nvalid > Wsel) {
-            const int xb = s_cross << COARSE_SHIFT;
-            int32_t r2 = S.s_above;
-            for (int c = 0; c < (1 << COARSE_SHIFT); ++c) {
-                const int32_t n = hist[xb + c];
-                if (r2 < Wsel && r2 + n >= Wsel) {
-                    res.kstar = H - (uint32_t)(xb + c);
-                    res.R = Wsel - r2;
-                    break;
-                }
-                r2 += n;
-            }
+            res.kstar = H - (uint32_t)(xb + at);
+            res.R = Wsel - above;
         }
     } else if (need > 0) {
         // the Wsel-th key (or the best one) lies below the window: select from the keys
@@ -625,11 +685,7 @@ __global__ __launch_bounds__(MX_THREADS) void k_merge_count(int i, int K, int lg
         *npaths_out = need;
     }
     // per-parent counts
-    const int PPB = MX_THREADS >> lgKp;
-    const int pl = t >> lgKp, j = t & ((1 << lgKp) - 1);
-    const int p = blockIdx.x * PPB + pl;
     if (blockIdx.x * PPB >= np) return;  // uniform
-    const uint32_t key = (p < np && j < K) ? keys[(size_t)p * K + j] : 0u;
     const bool g = key > res.kstar, e = key != 0u && key == res.kstar;
     const uint64_t seg = parent_lanes(lane, lgKp);
     const int32_t ng = __popcll(__ballot(g) & seg), ne = __popcll(__ballot(e) & seg);
@@ -642,7 +698,7 @@ __global__ __launch_bounds__(MX_THREADS) void k_merge_scatter(const MergeLevel* 
                                                               const MergeLvState* st, const uint32_t* keys,
                                                               const int64_t* pcnt, const uint32_t* prow,
                                                               uint32_t* nrow, int nw, int64_t* scores, int final_out,
-                                                              int nV, int32_t* hist, int32_t* below)
+                                                              int nV, int32_t* hist, int copies, int32_t* below)
 {
     __shared__ int64_t s_red[MX_THREADS / 64];
     __shared__ int64_t s_pc[MX_THREADS];
@@ -650,32 +706,48 @@ __global__ __launch_bounds__(MX_THREADS) void k_merge_scatter(const MergeLevel* 
     __shared__ int32_t s_pos[MX_THREADS], s_src[MX_THREADS];
     __shared__ uint32_t s_bits[MX_THREADS];
     const int t = threadIdx.x, lane = t & 63, wv = t >> 6;
-    {  // the next level's histogram starts from zero (every block clears its share)
-        const int per = (MERGE_HIST_INTS + (int)gridDim.x - 1) / (int)gridDim.x;
-        const int lo = blockIdx.x * per, hi = lo + per < MERGE_HIST_INTS ? lo + per : MERGE_HIST_INTS;
-        for (int x = lo + t; x < hi; x += MX_THREADS) hist[x] = 0;
-        if (blockIdx.x == 0 && t == 0) *below = 0;
+    // The next level's histogram starts from zero: every block clears its share of
+    // the (copy, super bin) pairs, those that hold something (few do).
+    for (int x0 = blockIdx.x; x0 < copies * SUPER_BINS; x0 += 64 * gridDim.x) {
+        const int x = x0 + lane * gridDim.x;
+        int32_t* at = hist + (size_t)(x / SUPER_BINS) * MERGE_HIST_INTS;
+        uint64_t some = __ballot(x < copies * SUPER_BINS && at[SUPER_AT + x % SUPER_BINS] != 0);
+        __syncthreads();  // every wave has looked
+        for (; some; some &= some - 1) {
+            const int y = x0 + (__ffsll((unsigned long long)some) - 1) * (int)gridDim.x, sb = y % SUPER_BINS;
+            int32_t* h = hist + (size_t)(y / SUPER_BINS) * MERGE_HIST_INTS;
+            h[(sb << SUPER_SHIFT) + t] = 0;
+            if (t < 16) h[FINE_BINS + (sb << 4) + t] = 0;
+            if (t == 0) h[SUPER_AT + sb] = 0;
+        }
     }
+    if (blockIdx.x == 0 && t == 0) *below = 0;
     const int PPB = MX_THREADS >> lgKp;
     const int p0 = blockIdx.x * PPB;
-    const int np = npaths[i];
+    const MergeLevel& L = lv[i];
+    const int np = npaths[i], start = L.start, size = L.size;
+    const uint32_t kstar = st->kstar;
+    const int32_t R = st->R;
     if (p0 >= np) return;  // uniform
     const int pl = t >> lgKp, j = t & ((1 << lgKp) - 1);
     const int p = p0 + pl;
-    const MergeLevel& L = lv[i];
     // independent loads first: this child's key, candidate and the parent's
-    // bit of the shared vertex, the threshold, the block's parent counts
+    // bit of the shared vertex, the block's parent counts
     const bool mine = p < np && j < K;
     const uint32_t key = mine ? keys[(size_t)p * K + j] : 0u;
     const uint32_t b = mine ? cand[(size_t)i * K + j] : 0u;
-    const uint32_t xs = mine ? row_bit(prow + (size_t)p * nw, L.start) : 0u;
-    const uint32_t kstar = st->kstar;
-    const int32_t R = st->R;
-    s_pc[t] = (t < PPB && p0 + t < np) ? pcnt[p0 + t] : 0;
+    const uint32_t xs = mine ? row_bit(prow + (size_t)p * nw, start) : 0u;
+    const int64_t pc = (t < PPB && p0 + t < np) ? pcnt[p0 + t] : 0;
     if (t == 0) s_n = 0;
-    // (gt, eq) counts of the parents before this block
+    // (gt, eq) counts of the parents before this block, 16-byte loads
     int64_t acc = 0;
-    for (int x = t; x < p0; x += MX_THREADS) acc += pcnt[x];
+#pragma unroll 4
+    for (int x = 2 * t; x + 1 < p0; x += 2 * MX_THREADS) {
+        const longlong2 v = *(const longlong2*)(pcnt + x);
+        acc += v.x + v.y;
+    }
+    if ((p0 & 1) && t == 0) acc += pcnt[p0 - 1];
+    s_pc[t] = pc;
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) acc += __shfl_xor(acc, o, 64);
     if (lane == 0) s_red[wv] = acc;
@@ -693,19 +765,23 @@ __global__ __launch_bounds__(MX_THREADS) void k_merge_scatter(const MergeLevel* 
         const int slot = atomicAdd(&s_n, 1);
         s_pos[slot] = pos;
         s_src[slot] = p;
-        s_bits[slot] = level_bits(b, o, L.size);
+        s_bits[slot] = level_bits(b, o, size);
         scores[final_out ? 0 : pos] = (int64_t)key - 1;  // final: the best cut
     }
     __syncthreads();
-    // rows: wave w builds survivors w, w + 4, ...; lanes over the words
-    const int nwp = final_out ? nw : (L.start + L.size + 31) >> 5;
+    // rows: lanes over the words of a survivor, then over survivors
+    const int nwp = final_out ? nw : (start + size + 31) >> 5;
     const int n = s_n;
-    for (int s = wv; s < n; s += MX_THREADS / 64) {
+    int lw = 0;
+    while ((1 << lw) < nwp && lw < 8) ++lw;
+    const int w0 = t & ((1 << lw) - 1);
+#pragma unroll 4
+    for (int s = t >> lw; s < n; s += MX_THREADS >> lw) {
         const uint32_t* src = prow + (size_t)s_src[s] * nw;
         uint32_t* dst = nrow + (size_t)(final_out ? 0 : s_pos[s]) * nw;
         const uint32_t bits = s_bits[s];
-        for (int q = lane; q < nwp; q += 64) {
-            uint32_t w = place_bits(src[q], q, L.start, L.size, bits);
+        for (int q = w0; q < nwp; q += 1 << lw) {
+            uint32_t w = place_bits(src[q], q, start, size, bits);
             if (final_out && q == nw - 1 && (nV & 31)) w &= (1u << (nV & 31)) - 1u;
             dst[q] = w;
         }
@@ -722,7 +798,7 @@ __global__ void k_merge_fail(uint32_t* out, int nw, int64_t* cut, const int32_t*
 hipError_t launch_merge(const MergeBufs& m, int M, int K, int W, int nw, int nV, const uint32_t* cand,
                         uint32_t* best, int64_t* best_cut, hipStream_t s)
 {
-    hipLaunchKernelGGL(k_merge_intra, dim3(M), dim3(64), 0, s, m.lv, m.intra, cand, K, m.ccut, m.lvk, m.maxinc,
+    hipLaunchKernelGGL(k_merge_intra, dim3(M + 128), dim3(64), 0, s, M, m.lv, m.intra, cand, K, m.ccut, m.lvk, m.maxinc,
                        m.hist, m.below);
     hipLaunchKernelGGL(k_merge_first, dim3(1), dim3(128), 0, s, m.lvk, K, m.ccut, m.keys, m.counts);
     // level 1: counts[0] = 1 path, counts[1] = its survivors
@@ -735,18 +811,19 @@ hipError_t launch_merge(const MergeBufs& m, int M, int K, int W, int nw, int nV,
     while ((1 << lgKp) < K) ++lgKp;
     const int PPB = MX_THREADS >> lgKp;
     const int nblk = (W + PPB - 1) / PPB;
+    const int copies = nblk > 64 ? MERGE_COPIES : 1;
     int cur = 0;
     for (int i = 1; i < M; ++i) {
         const bool last = i == M - 1;
         hipLaunchKernelGGL(k_merge_expand, dim3(nblk), dim3(MX_THREADS), 0, s, m.lv, i, m.back, cand, K, lgKp,
                            m.ccut, m.lvk, m.rows[cur], nw, m.scores, m.counts, m.lvs, m.maxinc, m.keys, m.hist,
-                           m.below);
+                           copies, m.below);
         hipLaunchKernelGGL(k_merge_count, dim3(nblk), dim3(MX_THREADS), 0, s, i, K, lgKp, m.counts + i,
-                           last ? 1 : W, m.lvs + (i - 1), m.maxinc, m.keys, m.hist, m.below, m.pcnt, m.lvs + i,
+                           last ? 1 : W, m.lvs + (i - 1), m.maxinc, m.keys, m.hist, copies, m.below, m.pcnt, m.lvs + i,
                            m.counts + i + 1);
         hipLaunchKernelGGL(k_merge_scatter, dim3(nblk), dim3(MX_THREADS), 0, s, m.lv, i, cand, K, lgKp, m.counts,
                            m.lvs + i, m.keys, m.pcnt, m.rows[cur], last ? best : m.rows[cur ^ 1], nw,
-                           last ? best_cut : m.scores, last ? 1 : 0, nV, m.hist, m.below);
+                           last ? best_cut : m.scores, last ? 1 : 0, nV, m.hist, copies, m.below);
         cur ^= 1;
     }
     hipLaunchKernelGGL(k_merge_fail, dim3(1), dim3(64), 0, s, best, nw, best_cut, m.counts + M);
