@@ -4,52 +4,179 @@
 
 namespace pq {
 
-__device__ inline int64_t block_sum_i64(int64_t x, int64_t* red)
+// cut[a] = sum_e w_e [x_a(u_e) != x_a(v_e)], x_a bit-packed (vertex t = word
+// t/32, bit t%32). An edge id outside [0, nV) makes every result -1.
+//
+// A workgroup takes G assignments, so that an edge is read once for all of them
+// (one assignment each read 160 MB of edges at 20,000 edges and 1024 assignments,
+// and two words of the assignment for each edge). It first lays the assignments
+// out in LDS as one byte per vertex, bit g for assignment g: an edge is then two
+// byte reads and an exclusive or. More vertices than LDS_VERTICES are looked up
+// in the packed words instead.
+//
+// G is the largest of 8, 4, 2, 1 that leaves a workgroup per CU. If there are
+// fewer than that even with one each and the edges are many, `splits` workgroups
+// share the edges of the same assignments and add to results cleared before; a
+// pass over the edges then sets -1 if an id is out of range. Small calls are bound
+// by latency, large ones by the vector units (an AND, a select and a 64-bit
+// addition per edge and assignment). Before / now, in us, weighted: 2000 vertices,
+// 20,000 edges, 1024 assignments 43.5 / 11.7, 4096 assignments 124 / 30.9; one
+// assignment, 200,000 edges 242 / 11.9 (16,383 edges, not split, about 9); 16,000
+// vertices, 1.28 M edges, 1000 assignments 3696 / 473; 100,000 vertices, not in
+// LDS, 200,000 edges, 300 assignments 377 / 237 (60,000, in LDS: 376 / 79). Fewer
+// than CUT_FEW_EDGES leave most of 1024 threads idle: 500 edges, 4096 assignments
+// 16.1 with them and 6.7 with 256; from 4096 on both are the same.
+constexpr int CUT_THREADS = 1024;
+constexpr int CUT_FEW_EDGES = 4096;  // fewer: workgroups of a quarter of the threads
+constexpr int CUT_CUS = 256;
+constexpr int LDS_VERTICES = 60 * 1024;
+constexpr int EDGES_PER_SPLIT = 8192;
+
+__device__ inline int64_t wave_sum_i64(int64_t x)
 {
     for (int off = 32; off > 0; off >>= 1) x += __shfl_xor(x, off);
-    const uint32_t tid = threadIdx.x;
-    if ((tid & 63u) == 0) red[tid >> 6] = x;
-    __syncthreads();
-    int64_t s = 0;
-    if (tid == 0)
-        for (int i = 0; i < (int)(blockDim.x >> 6); ++i) s += red[i];
-    __syncthreads();
-    return s;
+    return x;
 }
 
-// cut[a] = sum_e w_e [x_a(u_e) != x_a(v_e)], x_a bit-packed (vertex t = word
-// t/32, bit t%32). An edge id outside [0, nV) makes the result -1.
-__global__ __launch_bounds__(THREADS) void k_maxcut(int32_t nV, int64_t nE, const int32_t* u, const int32_t* v,
-                                                   const int32_t* w, int64_t A, const uint32_t* assign,
-                                                   int64_t* cut)
+// bit g: whether assignment a0 + g has bit t of word q set
+template <int G>
+__device__ inline uint32_t assigned(const uint32_t* x, int64_t nw, int na, int32_t t)
 {
-    __shared__ int64_t red[THREADS / 64];
+    uint32_t bits = 0;
+#pragma unroll
+    for (int g = 0; g < G; ++g)
+        if (g < na) bits |= ((x[g * nw + (t >> 5)] >> (t & 31)) & 1u) << g;
+    return bits;
+}
+
+template <int G, int T, bool LDS, bool WEIGHTED>
+__global__ __launch_bounds__(T) void k_maxcut(int32_t nV, int64_t nE, const int32_t* u, const int32_t* v,
+                                                       const int32_t* w, int64_t A, const uint32_t* assign,
+                                                       int splits, int64_t per, int64_t* cut)
+{
+    extern __shared__ uint8_t bits_of[];
+    __shared__ int64_t red[T / 64][G];
+    const int t = threadIdx.x;
     const int64_t nw = (nV + 31) / 32;
-    for (int64_t a = blockIdx.x; a < A; a += gridDim.x) {
-        const uint32_t* x = assign + a * nw;
-        int64_t acc = 0, bad = 0;
-        for (int64_t e = threadIdx.x; e < nE; e += THREADS) {
-            const int32_t p = u[e], q = v[e];
-            if ((uint32_t)p >= (uint32_t)nV || (uint32_t)q >= (uint32_t)nV) {
-                bad = 1;
-                continue;
-            }
-            const uint32_t xp = (x[p >> 5] >> (p & 31)) & 1u;
-            const uint32_t xq = (x[q >> 5] >> (q & 31)) & 1u;
-            if (xp != xq) acc += w ? (int64_t)w[e] : 1;
+    const int64_t groups = (A + G - 1) / G;
+    const int split = blockIdx.x % splits;
+    const int64_t e0 = split * per, e1 = e0 + per < nE ? e0 + per : nE;
+    for (int64_t group = blockIdx.x / splits; group < groups; group += gridDim.x / splits) {
+        const int64_t a0 = group * G;
+        const int na = A - a0 < G ? (int)(A - a0) : G;
+        const uint32_t* x = assign + a0 * nw;
+        if (LDS) {
+            for (int32_t y = t; y < nV; y += T) bits_of[y] = (uint8_t)assigned<G>(x, nw, na, y);
+            __syncthreads();
         }
-        acc = block_sum_i64(acc, red);
-        bad = block_sum_i64(bad, red);
-        if (threadIdx.x == 0) cut[a] = bad ? -1 : acc;
+        int64_t acc[G];
+#pragma unroll
+        for (int g = 0; g < G; ++g) acc[g] = 0;
+        bool bad = false;
+        // four edges in flight per thread; one beyond the end joins a vertex to itself
+        for (int64_t e = e0 + t; e < e1; e += 4 * T) {
+            int32_t p[4], q[4], we[4];
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                const bool in = e + k * T < e1;
+                p[k] = in ? u[e + k * T] : 0;
+                q[k] = in ? v[e + k * T] : 0;
+                we[k] = !WEIGHTED ? 1 : in ? w[e + k * T] : 0;
+            }
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                if ((uint32_t)p[k] >= (uint32_t)nV || (uint32_t)q[k] >= (uint32_t)nV) {
+                    bad = true;
+                    continue;
+                }
+                const uint32_t d = LDS ? (uint32_t)(bits_of[p[k]] ^ bits_of[q[k]])
+                                       : assigned<G>(x, nw, na, p[k]) ^ assigned<G>(x, nw, na, q[k]);
+#pragma unroll
+                for (int g = 0; g < G; ++g) acc[g] += (d >> g) & 1u ? we[k] : 0;
+            }
+        }
+#pragma unroll
+        for (int g = 0; g < G; ++g) {
+            const int64_t sum = wave_sum_i64(acc[g]);
+            if ((t & 63) == 0) red[t >> 6][g] = sum;
+        }
+        const int any_bad = __syncthreads_or(bad);
+        if (t < na) {
+            int64_t sum = 0;
+            for (int k = 0; k < T / 64; ++k) sum += red[k][t];
+            if (splits == 1)
+                cut[a0 + t] = any_bad ? -1 : sum;
+            else
+                atomicAdd((unsigned long long*)&cut[a0 + t], (unsigned long long)sum);
+        }
+        __syncthreads();  // red and bits_of are free again
     }
+}
+
+__global__ void k_maxcut_clear(int64_t A, int64_t* cut)
+{
+    const int64_t a = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (a < A) cut[a] = 0;
+}
+
+// -1 for every assignment if an edge id is out of range (as each workgroup that
+// finds one writes)
+__global__ __launch_bounds__(THREADS) void k_maxcut_check(int32_t nV, int64_t nE, const int32_t* u, const int32_t* v,
+                                                         int64_t A, int64_t* cut)
+{
+    bool bad = false;
+    for (int64_t e = (int64_t)blockIdx.x * THREADS + threadIdx.x; e < nE; e += (int64_t)gridDim.x * THREADS)
+        bad |= (uint32_t)u[e] >= (uint32_t)nV || (uint32_t)v[e] >= (uint32_t)nV;
+    if (!__syncthreads_or(bad)) return;
+    for (int64_t a = threadIdx.x; a < A; a += THREADS) cut[a] = -1;
+}
+
+template <int G, int T>
+static void launch_maxcut_gt(int64_t grid, bool lds, int32_t nV, int64_t nE, const int32_t* u, const int32_t* v,
+                             const int32_t* w, int64_t A, const uint32_t* assign, int splits, int64_t* cut,
+                             hipStream_t s)
+{
+    auto* k = lds ? (w ? k_maxcut<G, T, true, true> : k_maxcut<G, T, true, false>)
+                  : (w ? k_maxcut<G, T, false, true> : k_maxcut<G, T, false, false>);
+    hipLaunchKernelGGL(k, dim3((unsigned)grid), dim3(T), lds ? (size_t)nV : 0, s, nV, nE, u, v, w, A, assign, splits,
+                       (nE + splits - 1) / splits, cut);
+}
+
+template <int G>
+static void launch_maxcut_g(int64_t grid, bool lds, int32_t nV, int64_t nE, const int32_t* u, const int32_t* v,
+                            const int32_t* w, int64_t A, const uint32_t* assign, int splits, int64_t* cut,
+                            hipStream_t s)
+{
+    auto* f = nE < CUT_FEW_EDGES ? launch_maxcut_gt<G, CUT_THREADS / 4> : launch_maxcut_gt<G, CUT_THREADS>;
+    f(grid, lds, nV, nE, u, v, w, A, assign, splits, cut, s);
 }
 
 hipError_t launch_maxcut_eval(int32_t nV, int64_t nE, const int32_t* u, const int32_t* v, const int32_t* w,
                               int64_t A, const uint32_t* assign, int64_t* cut, hipStream_t s)
 {
     if (A <= 0) return hipSuccess;
-    const int64_t grid = A < 65536 ? A : 65536;
-    hipLaunchKernelGGL(k_maxcut, dim3((unsigned)grid), dim3(THREADS), 0, s, nV, nE, u, v, w, A, assign, cut);
+    int G = 8;
+    while (G > 1 && A < (int64_t)G * CUT_CUS) G >>= 1;
+    const int64_t groups = (A + G - 1) / G;
+    int splits = 1;
+    while (groups * splits * 2 <= CUT_CUS && nE >= (int64_t)splits * 2 * EDGES_PER_SPLIT) splits *= 2;
+    const bool lds = nV <= LDS_VERTICES;
+    const int64_t grid = groups < 65536 ? groups * splits : 65536;  // splits > 1 only with few groups
+    if (splits > 1)
+        hipLaunchKernelGGL(k_maxcut_clear, dim3((unsigned)((A + THREADS - 1) / THREADS)), dim3(THREADS), 0, s, A, cut);
+    if (G == 8)
+        launch_maxcut_g<8>(grid, lds, nV, nE, u, v, w, A, assign, splits, cut, s);
+    else if (G == 4)
+        launch_maxcut_g<4>(grid, lds, nV, nE, u, v, w, A, assign, splits, cut, s);
+    else if (G == 2)
+        launch_maxcut_g<2>(grid, lds, nV, nE, u, v, w, A, assign, splits, cut, s);
+    else
+        launch_maxcut_g<1>(grid, lds, nV, nE, u, v, w, A, assign, splits, cut, s);
+    if (splits > 1) {
+        const int64_t blocks = (nE + 8 * THREADS - 1) / (8 * THREADS);
+        hipLaunchKernelGGL(k_maxcut_check, dim3((unsigned)(blocks < CUT_CUS ? blocks : CUT_CUS)), dim3(THREADS), 0, s, nV, nE,
+                           u, v, A, cut);
+    }
     return hipGetLastError();
 }
 
