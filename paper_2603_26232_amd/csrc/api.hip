@@ -230,6 +230,16 @@ constexpr uint64_t CACHE_FIT_BYTES = 224ull << 20;
 // 157 us).
 constexpr int64_t WIDE_MIN_TILES = 128;
 
+// Up to this many tiles, subgraphs with the same number of groups run in the same
+// launches, whatever their group sizes: a pass over few tiles costs its latency (5
+// to 12 us), so one launch per shape multiplies it. Gradients, p = 3, a launch per
+// shape / joined, in us: one subgraph each of 14 and 16 qubits (10 tiles) 99 / 54,
+// 14, 18 and 20 (162) 173 / 73, eight of 19 and of 20 (1536) 242 / 200, 64 each of
+// 14..18 (3968) 531 / 454, 32 of 14 and of 20 (4160) 530 / 492, 32 of 19 and of 20
+// (6144) 738 / 721. Beyond that the states no longer fit the last-level cache and
+// the launches are long.
+constexpr int64_t JOIN_MAX_TILES = 8192;
+
 // layout-chain code of group g (see launch_fwd_pass): 3 for group 0; for a
 // high group 2 (8 qubits), 4 (5..7), 1 (4), 5 (1..3); on wide tiles the
 // group's size
@@ -239,6 +249,15 @@ int chain_of(const SubDesc& d, int g)
     const int nb = d.gsize[g];
     if (d.wide) return nb;
     return nb == 8 ? 2 : (nb >= 5 ? 4 : (nb == 4 ? 1 : 5));
+}
+
+// one code for two shapes: 5 serves groups of up to 4 qubits, 4 those of more, 6 all
+// (each group's arithmetic is the same under any code that serves it)
+int chain_for_both(int a, int b)
+{
+    if (a == b) return a;
+    const bool few = a == 1 || a == 5, few_b = b == 1 || b == 5;
+    return few && few_b ? 5 : (a == 2 || a == 4) && (b == 2 || b == 4) ? 4 : 6;
 }
 
 // Tile of position i in a class's work list. Workgroups go round robin over
@@ -423,15 +442,22 @@ qaoa_status_t make_plan(int32_t B, const int32_t* nq, const int64_t* eoff, const
         for (int b = 0; b < B; ++b)
             if (P.subs[b].ngroups >= 2) order.push_back(b);
         std::stable_sort(order.begin(), order.end(), [&](int a, int c) { return P.subs[a].n > P.subs[c].n; });
+        int64_t narrow_tiles[MAX_GROUPS + 1] = {};
+        for (int b : order)
+            if (!P.subs[b].wide) narrow_tiles[P.subs[b].ngroups] += P.subs[b].ntiles;
         for (int b : order) {
             const SubDesc& d = P.subs[b];
             if (d.skip) continue;
+            const bool join = !d.wide && narrow_tiles[d.ngroups] <= JOIN_MAX_TILES;
             int ci = -1;
             for (size_t k = 0; k < P.classes.size(); ++k) {
                 bool same = P.classes[k].G == d.ngroups && P.classes[k].wide == (d.wide != 0);
-                for (int g = 0; same && g < d.ngroups; ++g) same = P.classes[k].chain[g] == chain_of(d, g);
+                for (int g = 0; same && !join && g < d.ngroups; ++g) same = P.classes[k].chain[g] == chain_of(d, g);
                 if (same) ci = (int)k;
             }
+            if (join && ci >= 0)
+                for (int g = 0; g < d.ngroups; ++g)
+                    P.classes[ci].chain[g] = chain_for_both(P.classes[ci].chain[g], chain_of(d, g));
             if (ci < 0) {
                 Plan::Class c{};
                 c.G = d.ngroups;

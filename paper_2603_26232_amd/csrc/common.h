@@ -178,7 +178,8 @@ hipError_t launch_mlp_backward(int B, MlpDims d, const double* P, const float* X
 hipError_t launch_cut_tables(uint8_t* ws, const SubDesc* subs, const int2* work, int nwork,
                              hipStream_t s);
 // chain: layout-chain code of the pass's group (3: group 0; 2 / 4: a high
-// group of 8 / 5..7 qubits; 1 / 5: a high group of 4 / 1..3 qubits)
+// group of 8 / 5..7 qubits; 1 / 5: a high group of 4 / 1..3 qubits; 6: high
+// groups of all sizes)
 hipError_t launch_fwd_pass(uint8_t* ws, const SubDesc* subs, const int2* work, int nwork, int chain,
                            PassOps ops, Partials part, int lut_max, int prec, hipStream_t s);
 hipError_t launch_bwd_pass(uint8_t* ws, const SubDesc* subs, const int2* work, int nwork, int chain,

@@ -180,6 +180,14 @@ __device__ inline float xb_bit(const float2 (&ps)[REGS], const float2 (&la)[REGS
     return a0 + a1;
 }
 
+// cmul with its roundings spelled out: which product of a sum the compiler rounds
+// first may else depend on the code around it, and the kernels for one size of
+// group and for all sizes have to agree
+__device__ inline float2 cmul_fixed(float2 a, float2 b)
+{
+    return make_float2(fmaf(a.x, b.x, -(a.y * b.y)), fmaf(a.x, b.y, a.y * b.x));
+}
+
 __device__ inline void scale_regs(float2 (&v)[REGS], float2 f)
 {
 #pragma unroll
@@ -846,11 +854,9 @@ __global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(PQ_MF_W
 // ---------------------------------------------------------------------------
 enum { B_FUSED = 0, B_SINGLE = 1, B_MID = 2, B_LAST = 3 };
 
-// The fused kind on group 0 is held to four waves per SIMD (the most that
-// its LDS tile allows); left free, it takes 130 registers and runs three.
-template <int CH, bool FULL, int KIND, bool STORE_PSI = true>
-__global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu((KIND == B_FUSED || KIND == B_LAST) && CH == 3 ? 4 : PQ_BWD_WAVES))) void k_bwd_pass(
-    uint8_t* ws, const SubDesc* subs, const int2* work, PassOps ops, Partials part)
+template <int CH, bool FULL, int KIND, bool STORE_PSI>
+__device__ __forceinline__ void bwd_pass_body(uint8_t* ws, const SubDesc* subs, const int2* work, PassOps ops,
+                                              Partials part)
 {
     extern __shared__ float2 smem[];
     float2* lds = smem;
@@ -976,8 +982,8 @@ __global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu((KIND =
 #pragma unroll
                 for (int r = 0; r < REGS; ++r) {
                     const float2 f = lut[cr[r]];
-                    ps[r] = cmul(ps[r], f);
-                    la[r] = cmul(la[r], f);
+                    ps[r] = cmul_fixed(ps[r], f);
+                    la[r] = cmul_fixed(la[r], f);
                 }
                 __builtin_amdgcn_sched_barrier(0);
                 seg_bwd<CH, FULL, false>(ps, la, lds, geo.c, post, tid, acc_post);
@@ -1006,6 +1012,38 @@ __global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu((KIND =
     }
 }
 
+// The fused kind on group 0 is held to four waves per SIMD (the most that
+// its LDS tile allows); left free, it takes 130 registers and runs three.
+template <int CH, bool FULL, int KIND, bool STORE_PSI>
+__global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu((KIND == B_FUSED || KIND == B_LAST) && CH == 3 ? 4 : PQ_BWD_WAVES))) void k_bwd_pass(
+    uint8_t* ws, const SubDesc* subs, const int2* work, PassOps ops, Partials part)
+{
+    bwd_pass_body<CH, FULL, KIND, STORE_PSI>(ws, subs, work, ops, part);
+}
+
+// Groups of up to four and of more qubits in one launch: each workgroup walks the
+// layouts of its own group, so a subgraph's results do not depend on the others.
+__device__ inline bool few_qubits(const SubDesc* subs, const int2* work, const PassOps& ops)
+{
+    return subs[work[blockIdx.x].x].gsize[ops.group] <= 4;
+}
+
+template <int KIND>
+__global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(PQ_FWD_WAVES))) void k_fwd_mixed(
+    uint8_t* ws, const SubDesc* subs, const int2* work, PassOps ops, Partials part)
+{
+    if (few_qubits(subs, work, ops)) fwd_pass_body<1, false, KIND, PREC_VALU>(ws, subs, work, ops, part);
+    else fwd_pass_body<2, false, KIND, PREC_VALU>(ws, subs, work, ops, part);
+}
+
+template <int KIND, bool STORE_PSI>
+__global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(PQ_BWD_WAVES))) void k_bwd_mixed(
+    uint8_t* ws, const SubDesc* subs, const int2* work, PassOps ops, Partials part)
+{
+    if (few_qubits(subs, work, ops)) bwd_pass_body<1, false, KIND, STORE_PSI>(ws, subs, work, ops, part);
+    else bwd_pass_body<2, false, KIND, STORE_PSI>(ws, subs, work, ops, part);
+}
+
 // ---------------------------------------------------------------------------
 // launchers
 // ---------------------------------------------------------------------------
@@ -1022,16 +1060,18 @@ static size_t pass_lds(int lut_max) { return (size_t)(LDS_TILE + lut_max) * size
 
 // chain codes: 3 = group 0; 2 / 4 = a high group of 8 / 5..7 qubits;
 // 1 / 5 = a high group of 4 / 1..3 qubits (the second of each pair has
-// register bits that are not active qubits)
-#define PQ_LAUNCH_CH(KERNEL, KIND)                                                                              \
-    do {                                                                                                        \
-        switch (chain) {                                                                                        \
-        case 3: hipLaunchKernelGGL((KERNEL<3, true, KIND>), g, b, lds, s, ws, subs, work, ops, part); break;    \
-        case 2: hipLaunchKernelGGL((KERNEL<2, true, KIND>), g, b, lds, s, ws, subs, work, ops, part); break;    \
-        case 4: hipLaunchKernelGGL((KERNEL<2, false, KIND>), g, b, lds, s, ws, subs, work, ops, part); break;   \
-        case 1: hipLaunchKernelGGL((KERNEL<1, true, KIND>), g, b, lds, s, ws, subs, work, ops, part); break;    \
-        default: hipLaunchKernelGGL((KERNEL<1, false, KIND>), g, b, lds, s, ws, subs, work, ops, part); break;  \
-        }                                                                                                       \
+// register bits that are not active qubits); 6 = high groups of all sizes
+#define PQ_LAUNCH_CH(KERNEL, MIXED, ...)                                                                            \
+    do {                                                                                                            \
+        switch (chain) {                                                                                            \
+        case 3: hipLaunchKernelGGL((KERNEL<3, true, __VA_ARGS__>), g, b, lds, s, ws, subs, work, ops, part); break; \
+        case 2: hipLaunchKernelGGL((KERNEL<2, true, __VA_ARGS__>), g, b, lds, s, ws, subs, work, ops, part); break; \
+        case 4: hipLaunchKernelGGL((KERNEL<2, false, __VA_ARGS__>), g, b, lds, s, ws, subs, work, ops, part); break;\
+        case 1: hipLaunchKernelGGL((KERNEL<1, true, __VA_ARGS__>), g, b, lds, s, ws, subs, work, ops, part); break; \
+        case 5: hipLaunchKernelGGL((KERNEL<1, false, __VA_ARGS__>), g, b, lds, s, ws, subs, work, ops, part); break;\
+        case 6: hipLaunchKernelGGL((MIXED<__VA_ARGS__>), g, b, lds, s, ws, subs, work, ops, part); break;           \
+        default: return hipErrorInvalidValue;                                                                       \
+        }                                                                                                           \
     } while (0)
 
 // group 0 with a matrix-core mixer block (PREC 1 or 2)
@@ -1047,23 +1087,14 @@ static size_t pass_lds(int lut_max) { return (size_t)(LDS_TILE + lut_max) * size
                                part);                                                                           \
     } while (0)
 
-#define PQ_LAUNCH_CH2(KERNEL, KIND, X)                                                                          \
-    do {                                                                                                        \
-        switch (chain) {                                                                                        \
-        case 3: hipLaunchKernelGGL((KERNEL<3, true, KIND, X>), g, b, lds, s, ws, subs, work, ops, part); break; \
-        case 2: hipLaunchKernelGGL((KERNEL<2, true, KIND, X>), g, b, lds, s, ws, subs, work, ops, part); break; \
-        case 4: hipLaunchKernelGGL((KERNEL<2, false, KIND, X>), g, b, lds, s, ws, subs, work, ops, part); break;\
-        case 1: hipLaunchKernelGGL((KERNEL<1, true, KIND, X>), g, b, lds, s, ws, subs, work, ops, part); break; \
-        default: hipLaunchKernelGGL((KERNEL<1, false, KIND, X>), g, b, lds, s, ws, subs, work, ops, part);      \
-        }                                                                                                       \
-    } while (0)
-
 hipError_t launch_fwd_pass(uint8_t* ws, const SubDesc* subs, const int2* work, int nwork, int chain, PassOps ops,
                            Partials part, int lut_max, int prec, hipStream_t s)
 {
     if (nwork <= 0) return hipSuccess;
     const size_t lds = pass_lds(lut_max);
     const dim3 g(nwork), b(THREADS);
+    // the first pass is group 0's
+    if (ops.init && (ops.group != 0 || chain != 3)) return hipErrorInvalidValue;
     if (prec != PREC_VALU && chain == 3) {
         if (ops.init) PQ_LAUNCH_MF(F_FIRST);
         else if (ops.epi_e) PQ_LAUNCH_MF(F_LAST);
@@ -1071,10 +1102,10 @@ hipError_t launch_fwd_pass(uint8_t* ws, const SubDesc* subs, const int2* work, i
         else PQ_LAUNCH_MF(F_SINGLE);
         return hipGetLastError();
     }
-    if (ops.init) PQ_LAUNCH_CH(k_fwd_pass, F_FIRST);
-    else if (ops.epi_e) PQ_LAUNCH_CH(k_fwd_pass, F_LAST);
-    else if (ops.ph >= 0) PQ_LAUNCH_CH(k_fwd_pass, F_MID);
-    else PQ_LAUNCH_CH(k_fwd_pass, F_SINGLE);
+    if (ops.init) hipLaunchKernelGGL((k_fwd_pass<3, true, F_FIRST>), g, b, lds, s, ws, subs, work, ops, part);
+    else if (ops.epi_e) PQ_LAUNCH_CH(k_fwd_pass, k_fwd_mixed, F_LAST);
+    else if (ops.ph >= 0) PQ_LAUNCH_CH(k_fwd_pass, k_fwd_mixed, F_MID);
+    else PQ_LAUNCH_CH(k_fwd_pass, k_fwd_mixed, F_SINGLE);
     return hipGetLastError();
 }
 
@@ -1086,12 +1117,12 @@ hipError_t launch_bwd_pass(uint8_t* ws, const SubDesc* subs, const int2* work, i
     const dim3 g(nwork), b(THREADS);
     // the last pass mirrors the first forward pass (group 0 of layer 1)
     if (ops.last && (ops.group != 0 || chain != 3)) return hipErrorInvalidValue;
-    if (ops.fused) PQ_LAUNCH_CH(k_bwd_pass, B_FUSED);
-    else if (ops.last) PQ_LAUNCH_CH(k_bwd_pass, B_LAST);
-    else if (ops.ph >= 0 && ops.nopsi) PQ_LAUNCH_CH2(k_bwd_pass, B_MID, false);
-    else if (ops.ph >= 0) PQ_LAUNCH_CH(k_bwd_pass, B_MID);
-    else if (ops.nopsi) PQ_LAUNCH_CH2(k_bwd_pass, B_SINGLE, false);
-    else PQ_LAUNCH_CH(k_bwd_pass, B_SINGLE);
+    if (ops.fused) PQ_LAUNCH_CH(k_bwd_pass, k_bwd_mixed, B_FUSED, true);
+    else if (ops.last) hipLaunchKernelGGL((k_bwd_pass<3, true, B_LAST, true>), g, b, lds, s, ws, subs, work, ops, part);
+    else if (ops.ph >= 0 && ops.nopsi) PQ_LAUNCH_CH(k_bwd_pass, k_bwd_mixed, B_MID, false);
+    else if (ops.ph >= 0) PQ_LAUNCH_CH(k_bwd_pass, k_bwd_mixed, B_MID, true);
+    else if (ops.nopsi) PQ_LAUNCH_CH(k_bwd_pass, k_bwd_mixed, B_SINGLE, false);
+    else PQ_LAUNCH_CH(k_bwd_pass, k_bwd_mixed, B_SINGLE, true);
     return hipGetLastError();
 }
 
