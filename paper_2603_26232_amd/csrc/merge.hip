@@ -54,48 +54,50 @@ constexpr int SUPER_AT = FINE_BINS + COARSE_BINS;
 static_assert(SUPER_AT + SUPER_BINS == MERGE_HIST_INTS, "histogram layout");
 constexpr int MX_THREADS = 256;  // expand / count / scatter blocks
 constexpr int LOCAL_BINS = 1024;
+constexpr int INTRA_THREADS = 256;
 
 // C_i(b_j) for every level and candidate; the number of valid candidates
 // (those before the first 0xFFFFFFFF of the row); the level's largest
 // possible score increment (max_j C_i(b_j) + its total back-edge weight); the
-// histogram cleared for level 2. One wave per level (K <= 64).
-__global__ void k_merge_intra(int M, const MergeLevel* lv, const int32_t* intra, const uint32_t* cand, int K, int64_t* ccut,
-                              int32_t* lvk, uint32_t* maxinc, int32_t* hist, int32_t* below)
+// histogram cleared for level 2. One workgroup per level (K <= 64).
+__global__ __launch_bounds__(INTRA_THREADS) void k_merge_intra(int M, const MergeLevel* lv, const int32_t* intra,
+                                                              const uint32_t* cand, int K, int lgKp, int64_t* ccut,
+                                                              int32_t* lvk, uint32_t* maxinc, int32_t* hist,
+                                                              int32_t* below)
 {
-    const int i = blockIdx.x;
-    for (int x = blockIdx.x * blockDim.x + threadIdx.x; x < MERGE_COPIES * MERGE_HIST_INTS / 4;
-         x += gridDim.x * blockDim.x)
+    __shared__ uint64_t s_cut[64];
+    const int i = blockIdx.x, t = threadIdx.x;
+    for (int x = blockIdx.x * INTRA_THREADS + t; x < MERGE_COPIES * MERGE_HIST_INTS / 4; x += gridDim.x * INTRA_THREADS)
         ((int4*)hist)[x] = make_int4(0, 0, 0, 0);
-    if (i == 0 && threadIdx.x == 0) *below = 0;
+    if (i == 0 && t == 0) *below = 0;
     if (i >= M) return;  // (these blocks only clear)
     const MergeLevel& L = lv[i];
-    {
-        const int lane = threadIdx.x;
-        const uint64_t bad = __ballot(lane < K && cand[(size_t)i * K + lane] == 0xFFFFFFFFu);
-        if (lane == 0) lvk[i] = bad ? __ffsll((unsigned long long)bad) - 1 : K;
-    }
-    int32_t best = 0;  // total weight < 2^31
-    for (int j = threadIdx.x; j < K; j += blockDim.x) {
-        const uint32_t b = cand[(size_t)i * K + j];
-        int64_t c = 0;
-        if (b != 0xFFFFFFFFu) {
-            for (int e = 0; e < L.intra_cnt; ++e) {
-                const int32_t* E = intra + 3 * (size_t)(L.intra_off + e);
-                if (((b >> E[0]) ^ (b >> E[1])) & 1u) c += E[2];
-            }
-        }
-        ccut[(size_t)i * K + j] = c;
-        best = (int32_t)c > best ? (int32_t)c : best;
-    }
+    // thread t takes every parts-th edge for candidate t % Kp
+    const int j = t & ((1 << lgKp) - 1), parts = INTRA_THREADS >> lgKp;
+    const uint32_t b = j < K ? cand[(size_t)i * K + j] : 0xFFFFFFFFu;
+    if (t < 64) s_cut[t] = 0;
+    __syncthreads();
+    int64_t c = 0;
+    const int32_t* E = intra + 3 * (size_t)L.intra_off;
+#pragma unroll 4
+    for (int e = t >> lgKp; e < L.intra_cnt; e += parts)
+        c += ((b >> E[3 * e]) ^ (b >> E[3 * e + 1])) & 1u ? E[3 * e + 2] : 0;
+    if (b != 0xFFFFFFFFu && c) atomicAdd((unsigned long long*)&s_cut[j], (unsigned long long)c);
+    __syncthreads();
+    if (t >= 64) return;
+    const uint64_t bad = __ballot(t < K && cand[(size_t)i * K + t] == 0xFFFFFFFFu);
+    const int32_t wk = t < 32 ? (int32_t)L.wk[t] : 0;  // total weight < 2^31
+    int32_t best = (int32_t)s_cut[t], wb = wk;
+    if (t < K) ccut[(size_t)i * K + t] = (int64_t)s_cut[t];
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) {
         const int32_t y = __shfl_xor(best, o, 64);
         best = y > best ? y : best;
+        wb += __shfl_xor(wb, o, 64);
     }
-    if (threadIdx.x == 0) {
-        int64_t wb = 0;
-        for (int k = 0; k < 32; ++k) wb += L.wk[k];
-        maxinc[i] = (uint32_t)(best + wb);
+    if (t == 0) {
+        lvk[i] = bad ? __ffsll((unsigned long long)bad) - 1 : K;
+        maxinc[i] = (uint32_t)best + (uint32_t)wb;
     }
 }
 
@@ -417,8 +419,8 @@ __global__ void k_merge_build(const MergeLevel* lv, const uint32_t* cand, const 
 // ---------------------------------------------------------------------------
 // Levels 2..M: expand / count / scatter
 // ---------------------------------------------------------------------------
-// A block covers PPB = MX_THREADS / Kp parents, Kp = K rounded up to a power
-// of two; thread t is child j = t % Kp of local parent t / Kp (j >= K idle),
+// A block covers PPB = MX_THREADS / Kp parents (expand: epb, at most as many), Kp =
+// K rounded up to a power of two; thread t is child j = t % Kp of local parent t / Kp (j >= K idle),
 // so a parent's children are consecutive lanes of one wave.
 //
 // A level is a chain of dependent steps, so its time is latency: at 2000
@@ -431,7 +433,7 @@ __global__ void k_merge_build(const MergeLevel* lv, const uint32_t* cand, const 
 // blocks, eight copies share them, and count sums the copies, which three
 // levels of bins keep short: 256 super bins, one per thread, then 16 coarse and
 // 16 fine ones, each by one wave-wide load. The line lies at 64
-// blocks, where both cost the same; a level with one copy / with eight, in us
+// blocks (of expand), where both cost the same; a level with one copy / eight, in us
 // (1000 vertices, K 16): 32 blocks 27.2 / 29.6, 64 29.4 / 29.7, 128 33.4 / 30.0,
 // 256 41.8 / 32.2; K 64: 32 21.8 / 23.6, 128 27.6 / 24.2, 1024 83.5 / 48.9.
 
@@ -439,7 +441,7 @@ constexpr int EDGE_STAGE = 2048;  // back edges staged in LDS per round
 constexpr int ROW_STAGE = 4096;   // row words staged in LDS (else read from memory)
 
 __global__ __launch_bounds__(MX_THREADS) void k_merge_expand(const MergeLevel* lv, int i, const int32_t* back,
-                                                             const uint32_t* cand, int K, int lgKp,
+                                                             const uint32_t* cand, int K, int lgKp, int epb,
                                                              const int64_t* ccut, const int32_t* lvk,
                                                              const uint32_t* rows, int nw, const int64_t* scores,
                                                              const int32_t* npaths, const MergeLvState* lvs,
@@ -453,16 +455,15 @@ __global__ __launch_bounds__(MX_THREADS) void k_merge_expand(const MergeLevel* l
     __shared__ int32_t s_kbeg[33], s_wk[32];
     __shared__ uint32_t s_dmin;
     const int t = threadIdx.x;
-    const int PPB = MX_THREADS >> lgKp;
     const int pl = t >> lgKp, j = t & ((1 << lgKp) - 1);
-    const int p0 = blockIdx.x * PPB;
+    const int p0 = blockIdx.x * epb;
     // (every uniform value is read before the first is waited for)
     const MergeLevel& L = lv[i];
     const int np = npaths[i], start = L.start, size = L.size, back_off = L.back_off, nb = L.kbeg[32];
     const int valid = lvk[i];
     const uint32_t H = lvs[i - 1].best + maxinc[i];  // >= every key of the level
     if (p0 >= np) return;  // uniform
-    const int nact = np - p0 < PPB ? np - p0 : PPB;
+    const int nact = np - p0 < epb ? np - p0 : epb;
     const int p = p0 + pl;
     const bool mine = pl < nact && j < K;
     // this child's inputs, loaded ahead of the staging (total weights < 2^31)
@@ -514,13 +515,27 @@ __global__ __launch_bounds__(MX_THREADS) void k_merge_expand(const MergeLevel* l
             const int hi = (s_kbeg[k + 1] < e0 + ne ? s_kbeg[k + 1] : e0 + ne) - e0;
             int32_t sum = 0;
             int e = lo;
-            for (; e + 4 <= hi; e += 4) {  // four independent LDS chains in flight
-                const int u0 = se_u[e], u1 = se_u[e + 1], u2 = se_u[e + 2], u3 = se_u[e + 3];
-                const int32_t w0 = se_w[e], w1 = se_w[e + 1], w2 = se_w[e + 2], w3 = se_w[e + 3];
-                sum += (bit_of(q, u0) ? w0 : 0) + (bit_of(q, u1) ? w1 : 0) + (bit_of(q, u2) ? w2 : 0) +
-                       (bit_of(q, u3) ? w3 : 0);
+            for (; e + 8 <= hi; e += 8) {  // eight independent LDS chains in flight
+                int32_t u[8], w[8];
+#pragma unroll
+                for (int c = 0; c < 8; ++c) {
+                    u[c] = se_u[e + c];
+                    w[c] = se_w[e + c];
+                }
+#pragma unroll
+                for (int c = 0; c < 8; ++c) sum += bit_of(q, u[c]) ? w[c] : 0;
             }
-            for (; e < hi; ++e) sum += bit_of(q, se_u[e]) ? se_w[e] : 0;
+            for (; e < hi; e += 4) {  // the rest by fours, the last edge again with weight 0
+                int32_t u[4], w[4];
+#pragma unroll
+                for (int c = 0; c < 4; ++c) {
+                    const int x = e + c < hi ? e + c : hi - 1;
+                    u[c] = se_u[x];
+                    w[c] = e + c < hi ? se_w[x] : 0;
+                }
+#pragma unroll
+                for (int c = 0; c < 4; ++c) sum += bit_of(q, u[c]) ? w[c] : 0;
+            }
             A[q][k] += sum;  // (q, k) has one owner
         }
         if (nb == 0) break;
@@ -798,8 +813,10 @@ __global__ void k_merge_fail(uint32_t* out, int nw, int64_t* cut, const int32_t*
 hipError_t launch_merge(const MergeBufs& m, int M, int K, int W, int nw, int nV, const uint32_t* cand,
                         uint32_t* best, int64_t* best_cut, hipStream_t s)
 {
-    hipLaunchKernelGGL(k_merge_intra, dim3(M + 128), dim3(64), 0, s, M, m.lv, m.intra, cand, K, m.ccut, m.lvk, m.maxinc,
-                       m.hist, m.below);
+    int lgKp = 0;
+    while ((1 << lgKp) < K) ++lgKp;
+    hipLaunchKernelGGL(k_merge_intra, dim3(M + 32), dim3(INTRA_THREADS), 0, s, M, m.lv, m.intra, cand, K, lgKp, m.ccut,
+                       m.lvk, m.maxinc, m.hist, m.below);
     hipLaunchKernelGGL(k_merge_first, dim3(1), dim3(128), 0, s, m.lvk, K, m.ccut, m.keys, m.counts);
     // level 1: counts[0] = 1 path, counts[1] = its survivors
     const bool last0 = M == 1;
@@ -807,15 +824,22 @@ hipError_t launch_merge(const MergeBufs& m, int M, int K, int W, int nw, int nV,
                        m.surv, m.counts + 1, m.lvs);
     hipLaunchKernelGGL(k_merge_build, dim3(last0 ? 1 : W), dim3(64), 0, s, m.lv, cand, m.surv, m.counts + 1,
                        last0 ? best : m.rows[0], nw, last0 ? best_cut : m.scores, last0 ? 1 : 0, nV);
-    int lgKp = 0;
-    while ((1 << lgKp) < K) ++lgKp;
     const int PPB = MX_THREADS >> lgKp;
     const int nblk = (W + PPB - 1) / PPB;
-    const int copies = nblk > 64 ? MERGE_COPIES : 1;
+    // Expand's workgroups take fewer parents where there are few of them, down to
+    // one (parent, vertex) pair per thread: their back edges are what takes long. A
+    // level in us, PPB parents / fewer (1000 vertices): K 4, W 64 53.3 / 22.2, W 4096
+    // 57.5 / 32.7; K 16, W 64 26.2 / 21.4, W 2048 30.0 / 26.5. With 512 workgroups
+    // instead of 256 a sparse graph's merge (2000 vertices, W 4096) takes 2.69
+    // instead of 2.59 ms, a denser one's level (1000) 30.1 instead of 31.4 us.
+    int epb = PPB;
+    while (epb * 32 > MX_THREADS && (W + epb - 1) / epb < 256) epb /= 2;
+    const int eblk = (W + epb - 1) / epb;
+    const int copies = eblk > 64 ? MERGE_COPIES : 1;
     int cur = 0;
     for (int i = 1; i < M; ++i) {
         const bool last = i == M - 1;
-        hipLaunchKernelGGL(k_merge_expand, dim3(nblk), dim3(MX_THREADS), 0, s, m.lv, i, m.back, cand, K, lgKp,
+        hipLaunchKernelGGL(k_merge_expand, dim3(eblk), dim3(MX_THREADS), 0, s, m.lv, i, m.back, cand, K, lgKp, epb,
                            m.ccut, m.lvk, m.rows[cur], nw, m.scores, m.counts, m.lvs, m.maxinc, m.keys, m.hist,
                            copies, m.below);
         hipLaunchKernelGGL(k_merge_count, dim3(nblk), dim3(MX_THREADS), 0, s, i, K, lgKp, m.counts + i,
