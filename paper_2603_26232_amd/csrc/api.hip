@@ -306,22 +306,21 @@ std::vector<int> even_split(int rest, int parts)
 // state per layer: 21..26 qubits (2 groups instead of 3) and 29, 30 (3 instead
 // of 4). Measured over 2^28 amplitudes at p = 3, 4096-amplitude against wide
 // tiles: forward 2.67 -> 1.59 ms at 21 qubits, 2.70 -> 1.66 at 24, 2.81 -> 1.95
-// at 25 (64-byte rows), 2.79 -> 2.47 at 26 (32-byte rows); gradient 5.94 -> 4.37,
+// at 25 (64-byte rows), 2.79 -> 2.15 at 26 (pairs; one state 0.63 -> 0.49); gradient 5.94 -> 4.37,
 // 6.06 -> 4.68, 6.26 -> 5.10 and 6.21 -> 6.30 ms.
 int wide_groups_for(int n) { return 1 + (n - WIDE_BITS + WIDE_GROUP_MAX - 1) / WIDE_GROUP_MAX; }
 bool wide_saves(int n) { return n > SMALL_MAX_N + 2 && wide_groups_for(n) < groups_for(n); }
 
-// Exceptions. 26 qubits: the 32-byte rows take back the gradient's gain, and a
-// single state (256 MB) streams from the last-level cache faster than that
-// (0.64 against 0.71 ms). Gradients of denser graphs: at generic angles dE/dgamma
+// Exceptions. 26 qubits: the 32-byte rows take back the gradient's gain (the
+// forward passes have tiles in pairs for them). Gradients of denser graphs: at generic angles dE/dgamma
 // is small beside the C(z)-weighted terms that cancel in it (10^-5 and less of
 // them at 21 qubits and half of all edges), so another order of the roundings
 // moves its leading digits without being more or less exact; those subgraphs
 // keep the tiles, and the bits, that they have.
-bool wide_allowed(const SubDesc& d, bool grad, int64_t wsum, int n26)
+bool wide_allowed(const SubDesc& d, bool grad, int64_t wsum)
 {
     if (d.skip || !wide_saves(d.n) || !tuned_split(d.n).empty()) return false;
-    if (d.n == 26 && (grad || n26 < 2)) return false;
+    if (d.n == 26 && grad) return false;
     return !grad || 2 * wsum <= 3 * d.n;
 }
 
@@ -386,13 +385,11 @@ qaoa_status_t make_plan(int32_t B, const int32_t* nq, const int64_t* eoff, const
     // a reduced index, the tile's highest bit); strided groups: the rest.
     {
         int64_t wide_tiles = 0;
-        int n26 = 0;
         std::vector<char> wide(B, 0);
-        for (const SubDesc& d : P.subs) n26 += d.n == 26 && !d.skip;
         for (int b = 0; b < B; ++b) {
             const SubDesc& d = P.subs[b];
             // (the matrix-core modes are defined on 4096-amplitude tiles)
-            wide[b] = P.prec == 0 && wide_allowed(d, grad, d.lut_len - 1, n26);
+            wide[b] = P.prec == 0 && wide_allowed(d, grad, d.lut_len - 1);
             if (wide[b]) wide_tiles += 1ll << (d.n - 1 - WIDE_BITS);
         }
         for (int b = 0; b < B; ++b) {

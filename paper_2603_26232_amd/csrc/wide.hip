@@ -20,6 +20,8 @@
 // passes hold two states in registers (two waves per SIMD), so one workgroup
 // owns the CU's LDS and exchanges whole amplitudes.
 //
+// The 12-qubit group's forward passes take tiles in pairs (see k_fwd_wide).
+//
 // Measured on 1.68e8 amplitudes (ten 25-qubit states, one launch; algorithmic
 // bytes): group 0 middle forward 557 us (5.1 TB/s), 11-qubit middle forward
 // 790 us (3.6 TB/s: a copy of 64-byte rows reaches 3.6), group 0 middle
@@ -43,11 +45,26 @@ namespace {
 constexpr int WT = WIDE_THREADS, WR = WIDE_REGS;
 enum { LLIN = 0, LL1 = 1 };
 constexpr uint32_t EX_SLOTS = WIDE_TILE + WIDE_TILE / 32;  // one pad slot per 32 amplitudes
+constexpr uint32_t HALF_SLOTS = EX_SLOTS + 32;  // of a pair: its halves in different banks
 
+// A thread's place: its tile position without register bits, and, with two tiles per
+// workgroup (PAIR), which of the two. The halves of a pair differ in the index bit
+// above the C passive tile bits; lanes run over it right after those, so a pair's
+// rows are twice as long.
 template <int L>
 __device__ inline uint32_t thread_part(uint32_t tid)
 {
     return L == LLIN ? tid : row_bits(tid & 15u) | ((tid >> 4) << 9);
+}
+struct Place {
+    uint32_t q, half;
+};
+template <int L, bool PAIR, int C>
+__device__ inline Place place(uint32_t tid)
+{
+    if constexpr (!PAIR) return {thread_part<L>(tid), 0u};
+    else if constexpr (L == LLIN) return {(tid & ((1u << C) - 1u)) | ((tid >> (C + 1)) << C), (tid >> C) & 1u};
+    else return {row_bits(tid & 15u) | ((tid >> 5) << 9), (tid >> 4) & 1u};
 }
 template <int L>
 __host__ __device__ constexpr uint32_t reg_part(uint32_t r)
@@ -57,13 +74,15 @@ __host__ __device__ constexpr uint32_t reg_part(uint32_t r)
 __host__ __device__ constexpr uint32_t slot(uint32_t q) { return q + (q >> 5); }  // additive over disjoint bits
 
 // Layout change of one state through a buffer of single floats. In LL1 a wave
-// reads and writes only its own eighth of the buffer (tile bits 11..13), so
+// reads and writes only its own part of the buffer (tile bits 11..13, or 10..13 of
+// both tiles of a pair), so
 // after a change to LL1 no barrier is needed before the next one writes.
-template <int LF, int LT>
+template <int LF, int LT, bool PAIR, int C>
 __device__ inline void xchg(float* ex, uint32_t tid, float2 (&v)[WR])
 {
-    float* p = ex + slot(thread_part<LF>(tid));
-    const float* s = ex + slot(thread_part<LT>(tid));
+    const Place f = place<LF, PAIR, C>(tid), o = place<LT, PAIR, C>(tid);
+    float* p = ex + f.half * HALF_SLOTS + slot(f.q);
+    const float* s = ex + o.half * HALF_SLOTS + slot(o.q);
 #pragma unroll
     for (int r = 0; r < WR; ++r) p[slot(reg_part<LF>(r))] = v[r].x;
     __syncthreads();
@@ -178,12 +197,12 @@ __device__ inline float xb_round(const float2 (&ps)[WR], const float2 (&la)[WR])
 }
 
 // One RX segment, LLIN -> LL1 (UP) or back.
-template <int NB, bool UP>
+template <int NB, bool UP, bool PAIR>
 __device__ inline void seg_rot(float2 (&v)[WR], float* ex, float t, uint32_t tid)
 {
     constexpr int A = UP ? LLIN : LL1, B = UP ? LL1 : LLIN;
     rx_round<A, NB>(v, t);
-    xchg<A, B>(ex, tid, v);
+    xchg<A, B, PAIR, low_bit<NB>()>(ex, tid, v);
     rx_round<B, NB>(v, t);
 }
 
@@ -247,10 +266,11 @@ __device__ inline Geo wide_geo(const SubDesc* sd, int g, uint32_t t)
     return r;
 }
 
-template <int L, bool G0>
+template <int L, bool G0, bool PAIR = false, int C = 0>
 __device__ inline void load_state(float2 (&v)[WR], const float2* st, const Geo& geo, uint32_t tid)
 {
-    uint32_t base = (geo.zb ^ gmapT<G0, WIDE_BITS>(geo, thread_part<L>(tid))) << 3;
+    const Place at = place<L, PAIR, C>(tid);
+    uint32_t base = (geo.zb ^ gmapT<G0, WIDE_BITS>(geo, at.q) ^ (at.half << C)) << 3;
     asm volatile("" : "+v"(base));  // keeps the shift out of the per-register XOR
 #pragma unroll
     for (int r = 0; r < WR; ++r) v[r] = at_off(st, base ^ (gmapT<G0, WIDE_BITS>(geo, reg_part<L>(r)) << 3));
@@ -258,12 +278,13 @@ __device__ inline void load_state(float2 (&v)[WR], const float2* st, const Geo& 
 }
 
 // store slot q to amplitude q ^ m
-template <int L, bool G0>
+template <int L, bool G0, bool PAIR = false, int C = 0>
 __device__ inline void store_state(const float2 (&v)[WR], float2* st, const Geo& geo, uint32_t tid, uint32_t m)
 {
     __builtin_amdgcn_sched_barrier(0);
+    const Place at = place<L, PAIR, C>(tid);
     uint32_t base =
-        (geo.zb ^ gmapT<G0, WIDE_BITS>(geo, thread_part<L>(tid)) ^ gmapT<G0, WIDE_BITS>(geo, m)) << 3;
+        (geo.zb ^ gmapT<G0, WIDE_BITS>(geo, at.q) ^ gmapT<G0, WIDE_BITS>(geo, m) ^ (at.half << C)) << 3;
     asm volatile("" : "+v"(base));
 #pragma unroll
     for (int r = 0; r < WR; ++r) at_off(st, base ^ (gmapT<G0, WIDE_BITS>(geo, reg_part<L>(r)) << 3)) = v[r];
@@ -326,19 +347,34 @@ enum { B_FUSED = 0, B_SINGLE = 1, B_MID = 2, B_LAST = 3 };
 
 // Forward pass. FIRST synthesises the phased |+> in LL1 and walks to LLIN;
 // MID walks to LL1, phases and walks back; SINGLE and LAST end in LL1.
-template <int NB, int KIND>
-__global__ __launch_bounds__(WT) __attribute__((amdgpu_waves_per_eu(4))) void k_fwd_wide(uint8_t* ws,
-                                                                                      const SubDesc* subs,
-                                                                                      const int2* work, PassOps ops,
-                                                                                      Partials part)
+//
+// The strided group of 12 qubits (26-qubit states) has rows of 32 bytes. Its
+// workgroups take a pair of neighbouring tiles each (1024 threads, the same
+// registers and LDS per CU as two workgroups), which doubles the rows, and the XCDs
+// work in eight parts of a state instead of next to each other, so that the rows in
+// flight are spread over the memory channels. Four states, p = 3: 2.43 ms without
+// either, 2.25 with pairs, 2.16 with both; p = 4 2.96, 2.91, 2.75. (11 qubits, 64-byte
+// rows, one state of 25 qubits, p = 3: 214 us, 225 with pairs, 242 with both. The
+// backward passes have no registers for pairs, and with the parts they are slower.)
+template <int NB, int KIND, bool PAIR = false>
+__global__ __launch_bounds__(PAIR ? 2 * WT : WT) __attribute__((amdgpu_waves_per_eu(4))) void k_fwd_wide(
+    uint8_t* ws, const SubDesc* subs, const int2* work, PassOps ops, Partials part)
 {
+    constexpr int THR = PAIR ? 2 * WT : WT, C = low_bit<NB>();
     extern __shared__ float wsm[];
     float* ex = wsm;
-    float2* lut = (float2*)(wsm + EX_SLOTS);
-    __shared__ double red[WT / 64];
+    float2* lut = (float2*)(wsm + (PAIR ? 2 * HALF_SLOTS : EX_SLOTS));
+    __shared__ double red[THR / 64];
     constexpr bool HAS_PRE = KIND != F_FIRST, HAS_PH = KIND == F_FIRST || KIND == F_MID;
     const uint32_t tid = threadIdx.x;
-    const int2 wk = work[blockIdx.x];
+    int2 wk = work[blockIdx.x];
+    if constexpr (PAIR) {
+        // each XCD takes an eighth of a state's tiles, four pairs in a row at a time
+        constexpr uint32_t np = 1u << (NB - 1);  // tiles of a state: one strided group
+        const uint32_t j = blockIdx.x % (np / 2);
+        wk = work[blockIdx.x / (np / 2) * np];
+        wk.y = (int)((j & 7u) * (np / 8) + (j >> 5) * 8u + ((j >> 3) & 3u) * 2u);
+    }
     const SubDesc* sd = subs + wk.x;
     const uint32_t t = (uint32_t)wk.y;
     constexpr bool G0 = NB == 0;
@@ -354,10 +390,12 @@ __global__ __launch_bounds__(WT) __attribute__((amdgpu_waves_per_eu(4))) void k_
     const uint32_t m_pre = (HAS_PRE && pre.flip) ? gb : 0u;
     const uint32_t m_end = m_pre ^ ((HAS_PH && post.flip) ? gb : 0u);
     float2 v[WR];
-    if constexpr (HAS_PRE) load_state<LLIN, G0>(v, src, geo, tid);
+    if constexpr (HAS_PRE) load_state<LLIN, G0, PAIR, C>(v, src, geo, tid);
     Cuts cr;
-    if constexpr (KIND != F_SINGLE)
-        load_cuts<gb>(cr, tile_tab(ws, sd, g, t), sd->tabw, tid, m_pre != 0u);  // LAST: m_pre = m_end
+    if constexpr (KIND != F_SINGLE) {  // (LAST: m_pre = m_end)
+        const uint32_t half = PAIR ? (tid >> 4) & 1u : 0u, row = PAIR ? (tid & 15u) | ((tid >> 5) << 4) : tid;
+        load_cuts<gb>(cr, tile_tab(ws, sd, g, t + half), sd->tabw, row, m_pre != 0u);
+    }
     if constexpr (HAS_PH) {
         // phase table with the factors of the segments before and after it
         // (FIRST: and the amplitude of |+>) folded in
@@ -365,11 +403,11 @@ __global__ __launch_bounds__(WT) __attribute__((amdgpu_waves_per_eu(4))) void k_
         const float2* L = (const float2*)(ws + sd->lut) + (size_t)ops.ph * len;
         const float amp = (float)(1.0 / sqrt((double)(1ull << (sd->n - 1))));
         const float2 F = HAS_PRE ? cmul(pre.Ff, post.Ff) : make_float2(amp * post.Ff.x, amp * post.Ff.y);
-        for (int i = tid; i < len; i += WT) lut[i] = cmul(L[i], F);
+        for (int i = tid; i < len; i += THR) lut[i] = cmul(L[i], F);
         if constexpr (!HAS_PRE) __syncthreads();  // (MID: the exchange's barriers come before the table is read)
     }
     if constexpr (HAS_PRE) {
-        seg_rot<NB, true>(v, ex, pre.t, tid);
+        seg_rot<NB, true, PAIR>(v, ex, pre.t, tid);
         if constexpr (!HAS_PH) scale_regs(v, pre.Ff);
     }
     if constexpr (HAS_PH) {
@@ -378,8 +416,8 @@ __global__ __launch_bounds__(WT) __attribute__((amdgpu_waves_per_eu(4))) void k_
             const float2 f = lut[cr.at(r)];
             v[r] = HAS_PRE ? cmul(v[r], f) : f;
         }
-        seg_rot<NB, false>(v, ex, post.t, tid);
-        store_state<LLIN, G0>(v, st, geo, tid, m_end);
+        seg_rot<NB, false, PAIR>(v, ex, post.t, tid);
+        store_state<LLIN, G0, PAIR, C>(v, st, geo, tid, m_end);
     } else {
         double acc = 0.0;
         if constexpr (KIND == F_LAST) {
@@ -387,10 +425,11 @@ __global__ __launch_bounds__(WT) __attribute__((amdgpu_waves_per_eu(4))) void k_
             for (int r = 0; r < WR; ++r)
                 acc += ((double)v[r].x * v[r].x + (double)v[r].y * v[r].y) * (double)cr.at(r);
         }
-        store_state<LL1, G0>(v, st, geo, tid, m_end);
+        store_state<LL1, G0, PAIR, C>(v, st, geo, tid, m_end);
         if constexpr (KIND == F_LAST) {
             acc = block_sum(acc, red);
-            if (tid == 0) part.e[sd->tile_base + t] = acc;
+            if (tid == 0) part.e[sd->tile_base + t] = acc;  // (a pair's sum at its first tile)
+            if (PAIR && tid == 1) part.e[sd->tile_base + t + 1] = 0.0;
         }
     }
 }
@@ -513,34 +552,55 @@ __global__ __launch_bounds__(WT) __attribute__((amdgpu_waves_per_eu(2))) void k_
 
 // ---------------------------------------------------------------------------
 // launchers. Chain codes: 3 = group 0, 7..12 = a strided group of that many
-// qubits (the even splits of 21..26, 29 and 30 qubits).
+// qubits (the even splits of 21..26, 29 and 30 qubits). Only the middle one of
+// three groups has passes of its own (SINGLE): 8 qubits of 29 and 30. Gradients
+// do not run groups of 12 (26 qubits).
 // ---------------------------------------------------------------------------
-#define PQ_WIDE(KERNEL, ...)                                                                                        \
-    do {                                                                                                            \
-        switch (chain) {                                                                                            \
-        case 3: hipLaunchKernelGGL((KERNEL<0, __VA_ARGS__>), g, b, lds, s, ws, subs, work, ops, part); break;       \
-        case 7: hipLaunchKernelGGL((KERNEL<7, __VA_ARGS__>), g, b, lds, s, ws, subs, work, ops, part); break;       \
-        case 8: hipLaunchKernelGGL((KERNEL<8, __VA_ARGS__>), g, b, lds, s, ws, subs, work, ops, part); break;       \
-        case 9: hipLaunchKernelGGL((KERNEL<9, __VA_ARGS__>), g, b, lds, s, ws, subs, work, ops, part); break;       \
-        case 10: hipLaunchKernelGGL((KERNEL<10, __VA_ARGS__>), g, b, lds, s, ws, subs, work, ops, part); break;     \
-        case 11: hipLaunchKernelGGL((KERNEL<11, __VA_ARGS__>), g, b, lds, s, ws, subs, work, ops, part); break;     \
-        case 12: hipLaunchKernelGGL((KERNEL<12, __VA_ARGS__>), g, b, lds, s, ws, subs, work, ops, part); break;     \
-        default: return hipErrorInvalidValue;                                                                       \
-        }                                                                                                           \
-    } while (0)
+using PassKernel = void (*)(uint8_t*, const SubDesc*, const int2*, PassOps, Partials);
+
+template <int KIND>
+static PassKernel fwd_kernel(int chain)
+{
+    switch (chain) {
+    case 3: return k_fwd_wide<0, KIND>;
+    case 7: return k_fwd_wide<7, KIND>;
+    case 8: return k_fwd_wide<8, KIND>;
+    case 9: return k_fwd_wide<9, KIND>;
+    case 10: return k_fwd_wide<10, KIND>;
+    case 11: return k_fwd_wide<11, KIND>;
+    case 12: return k_fwd_wide<12, KIND, true>;
+    default: return nullptr;
+    }
+}
+
+template <int KIND, bool SPSI>
+static PassKernel bwd_kernel(int chain)
+{
+    switch (chain) {
+    case 3: return k_bwd_wide<0, KIND, SPSI>;
+    case 7: return k_bwd_wide<7, KIND, SPSI>;
+    case 8: return k_bwd_wide<8, KIND, SPSI>;
+    case 9: return k_bwd_wide<9, KIND, SPSI>;
+    case 10: return k_bwd_wide<10, KIND, SPSI>;
+    case 11: return k_bwd_wide<11, KIND, SPSI>;
+    default: return nullptr;
+    }
+}
 
 hipError_t launch_fwd_wide(uint8_t* ws, const SubDesc* subs, const int2* work, int nwork, int chain, PassOps ops,
                            Partials part, int lut_max, hipStream_t s)
 {
     if (nwork <= 0) return hipSuccess;
-    const size_t lds = EX_SLOTS * sizeof(float) + (size_t)lut_max * sizeof(float2);
-    const dim3 g(nwork), b(WT);
-    if (ops.init) {
-        if (chain != 3) return hipErrorInvalidValue;
-        hipLaunchKernelGGL((k_fwd_wide<0, F_FIRST>), g, b, lds, s, ws, subs, work, ops, part);
-    } else if (ops.epi_e) PQ_WIDE(k_fwd_wide, F_LAST);
-    else if (ops.ph >= 0) PQ_WIDE(k_fwd_wide, F_MID);
-    else PQ_WIDE(k_fwd_wide, F_SINGLE);
+    const bool pair = chain == 12;
+    if (pair && nwork % (1 << 11)) return hipErrorInvalidValue;  // whole states of 26 qubits
+    const size_t lds = (pair ? 2 * HALF_SLOTS : EX_SLOTS) * sizeof(float) + (size_t)lut_max * sizeof(float2);
+    PassKernel k = nullptr;
+    if (ops.init) k = chain == 3 ? k_fwd_wide<0, F_FIRST> : nullptr;
+    else if (ops.epi_e) k = fwd_kernel<F_LAST>(chain);
+    else if (ops.ph >= 0) k = fwd_kernel<F_MID>(chain);
+    else k = chain == 8 ? k_fwd_wide<8, F_SINGLE> : nullptr;
+    if (!k) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(k, dim3(pair ? nwork / 2 : nwork), dim3(pair ? 2 * WT : WT), lds, s, ws, subs, work, ops, part);
     return hipGetLastError();
 }
 
@@ -549,16 +609,14 @@ hipError_t launch_bwd_wide(uint8_t* ws, const SubDesc* subs, const int2* work, i
 {
     if (nwork <= 0) return hipSuccess;
     const size_t lds = EX_SLOTS * sizeof(float2) + (size_t)lut_max * sizeof(float2);
-    const dim3 g(nwork), b(WT);
-    if (ops.last) {
-        // the last pass mirrors the first forward pass (group 0 of layer 1)
-        if (ops.group != 0 || chain != 3) return hipErrorInvalidValue;
-        hipLaunchKernelGGL((k_bwd_wide<0, B_LAST, false>), g, b, lds, s, ws, subs, work, ops, part);
-    } else if (ops.fused) PQ_WIDE(k_bwd_wide, B_FUSED, false);
-    else if (ops.ph >= 0 && ops.nopsi) PQ_WIDE(k_bwd_wide, B_MID, false);
-    else if (ops.ph >= 0) PQ_WIDE(k_bwd_wide, B_MID, true);
-    else if (ops.nopsi) PQ_WIDE(k_bwd_wide, B_SINGLE, false);
-    else PQ_WIDE(k_bwd_wide, B_SINGLE, true);
+    PassKernel k = nullptr;
+    // the last pass mirrors the first forward pass (group 0 of layer 1)
+    if (ops.last) k = ops.group == 0 && chain == 3 ? k_bwd_wide<0, B_LAST, false> : nullptr;
+    else if (ops.fused) k = bwd_kernel<B_FUSED, false>(chain);
+    else if (ops.ph >= 0) k = ops.nopsi ? bwd_kernel<B_MID, false>(chain) : bwd_kernel<B_MID, true>(chain);
+    else if (chain == 8) k = ops.nopsi ? k_bwd_wide<8, B_SINGLE, false> : k_bwd_wide<8, B_SINGLE, true>;
+    if (!k) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(k, dim3(nwork), dim3(WT), lds, s, ws, subs, work, ops, part);
     return hipGetLastError();
 }
 
