@@ -32,7 +32,6 @@ __device__ inline RxCoef rx_coef(const SubDesc* sd, double bt)
     double s, c;
     sincos(bt, &s, &c);
     RxCoef rc;
-    rc.cs = make_float2((float)c, (float)s);
     // e^{-i beta X} = c (I - i tan(beta) X)            when |cos| >= |sin|
     //               = -i s X (I + i cot(beta) X)       otherwise
     // i.e. f (I - i t X) X^flip with (f, t) = (c, tan) or (-i s, -cot)

@@ -30,7 +30,6 @@ constexpr int LUT_MAX = 2048;  // phase table entries per layer (sum of weights 
 // Stored states are symmetry-reduced: the ansatz state is invariant under
 // flipping every bit (psi(~z) = psi(z)), so only the 2^(n-1) amplitudes with
 // the top bit clear are stored, scaled by sqrt(2) to unit norm.
-constexpr int HALF_BITS = TILE_BITS - 1;  // qubits 0..10 in group 0; tile bit 11 = the complement
 constexpr int SMALL_MAX_N = 13;  // n <= 13: the reduced state (<= 4096 amplitudes) is one workgroup's tile
 // the tile passes address a stored state with 32-bit byte offsets
 static_assert((8ull << (QAOA_MAX_QUBITS - 1)) <= (1ull << 32), "a stored state must fit 32-bit byte offsets");
@@ -84,7 +83,6 @@ __host__ __device__ inline uint64_t state_bytes(int n) { return 8ull << (n - 1);
 // per-qubit factors raised to the size of group g, forward (c or -i s) and
 // inverse (c or +i s).
 struct RxCoef {
-    float2 cs;  // (cos beta, sin beta)
     float t;
     int32_t mode;
     float fsq;  // |per-qubit factor|^2

@@ -75,17 +75,6 @@ __host__ __device__ constexpr int layout_bit0()
 // padded LDS slot; lds_idx(a | b) = lds_idx(a) + lds_idx(b) for disjoint bits
 __host__ __device__ constexpr uint32_t lds_idx(uint32_t q) { return q + (q >> 4); }
 
-// register bits whose tile bit is an active qubit of the group
-template <int L>
-__device__ inline unsigned active_mask(int c)
-{
-    unsigned m = 0;
-#pragma unroll
-    for (int k = 0; k < 4; ++k)
-        if (layout_bit0<L>() + k >= c) m |= 1u << k;
-    return m;
-}
-
 // Layout chains per group shape: CH = 3 (group 0: every tile bit active),
 // 2 (a high group of 5..8 qubits), 1 (a high group of at most 4 qubits).
 template <int CH, int I>
