@@ -67,7 +67,7 @@ def log(*a):
 
 def _record(path, kernel):
     """The RECORD line of `kernel` in a committed profile summary, if that
-    summary was taken on the current kernel source; else None."""
+    summary was taken on the current kernel sources; else None."""
     if not os.path.exists(path):
         return None
     rec = None
@@ -78,10 +78,10 @@ def _record(path, kernel):
                 rec = r
     if not rec:
         return None
-    src = os.path.join(ROOT, "paper_2603_26232_amd", "csrc", rec.get("source", "sim.hip"))
-    sha = hashlib.sha256(open(src, "rb").read()).hexdigest()
-    if sha != rec.get("source_sha256"):
-        return None
+    for name, sha in (rec.get("sources") or {rec.get("source", "sim.hip"): rec.get("source_sha256")}).items():
+        src = os.path.join(ROOT, "paper_2603_26232_amd", "csrc", name)
+        if hashlib.sha256(open(src, "rb").read()).hexdigest() != sha:
+            return None
     return rec
 
 
