@@ -316,11 +316,13 @@ bool wide_saves(int n) { return n > SMALL_MAX_N + 2 && wide_groups_for(n) < grou
 // is small beside the C(z)-weighted terms that cancel in it (10^-5 and less of
 // them at 21 qubits and half of all edges), so another order of the roundings
 // moves its leading digits without being more or less exact; those subgraphs
-// keep the tiles, and the bits, that they have.
-bool wide_allowed(const SubDesc& d, bool grad, int64_t wsum)
+// keep the tiles, and the bits, that they have. So do gradients of one layer, where
+// the usual starting angle beta = pi/8 is a stationary point of every triangle-free
+// subgraph and Adam blows dE/dbeta's rounding noise up to its step size.
+bool wide_allowed(const SubDesc& d, bool grad, int64_t wsum, int max_p)
 {
     if (d.skip || !wide_saves(d.n) || !tuned_split(d.n).empty()) return false;
-    if (d.n == 26 && grad) return false;
+    if (grad && (d.n == 26 || max_p == 1)) return false;
     return !grad || 2 * wsum <= 3 * d.n;
 }
 
@@ -389,7 +391,7 @@ qaoa_status_t make_plan(int32_t B, const int32_t* nq, const int64_t* eoff, const
         for (int b = 0; b < B; ++b) {
             const SubDesc& d = P.subs[b];
             // (the matrix-core modes are defined on 4096-amplitude tiles)
-            wide[b] = P.prec == 0 && wide_allowed(d, grad, d.lut_len - 1);
+            wide[b] = P.prec == 0 && wide_allowed(d, grad, d.lut_len - 1, max_p);
             if (wide[b]) wide_tiles += 1ll << (d.n - 1 - WIDE_BITS);
         }
         for (int b = 0; b < B; ++b) {

@@ -514,12 +514,145 @@ __global__ __launch_bounds__(ST) __attribute__((amdgpu_waves_per_eu(4))) void k_
     }
 }
 
+// One layer with its gradient, one qubit at a time in LDS with the plain (cos, sin)
+// form of each rotation. At p = 1 the usual starting angle beta = pi/8 is a
+// stationary point of every triangle-free subgraph, and Adam's first steps there
+// are the rounding noise of dE/dbeta blown up to the step size, so the order of the
+// roundings decides the angles: this order is kept, although the kernel above is
+// faster. (Five steps on 60 vertices in subgraphs of 9..13: 247 us.)
+__device__ inline void rx_pair(float2& a, float2& b, float c, float s)
+{
+    const float2 na = make_float2(c * a.x + s * b.y, c * a.y - s * b.x);
+    const float2 nb = make_float2(c * b.x + s * a.y, c * b.y - s * a.x);
+    a = na;
+    b = nb;
+}
+
+__global__ __launch_bounds__(THREADS) void k_small_layer(uint8_t* ws, const SubDesc* subs, const int32_t* list,
+                                                        SmallArgs A, Partials part)
+{
+    extern __shared__ float2 dyn[];
+    __shared__ double red[THREADS / 64];
+    __shared__ double s_angle[2];  // gamma, beta
+    const uint32_t tid = threadIdx.x;
+    const int b = list[blockIdx.x];
+    const SubDesc* sd = subs + b;
+    const int n = sd->n, len = sd->lut_len;
+    const uint32_t dim = 1u << (n - 1), half = dim >> 1, comp = dim - 1;
+    float2* ps = dyn;
+    float2* la = dyn + A.lut_at;
+    float2* lut = dyn + 2 * A.lut_at;
+    const uint8_t* tab = ws + sd->tab;
+    const bool w1 = sd->tabw == 1;
+    auto cut = [&](uint32_t z) { return w1 ? (uint32_t)tab[z] : (uint32_t)((const uint16_t*)tab)[z]; };
+    const bool opt = A.iters > 0, mine = opt && tid < 2;
+    const size_t idx = (tid == 0 ? 0 : (size_t)A.B) + (size_t)b;  // theta: gamma, then beta, of every subgraph
+    double th = 0.0, m = 0.0, v = 0.0;
+    if (mine) {
+        th = A.theta[idx];
+        m = A.m[idx];
+        v = A.v[idx];
+    }
+    if (tid < 2) s_angle[tid] = opt ? th : tid == 0 ? A.gamma[b] : A.beta[b];
+    const int32_t t0 = opt ? *A.step : 0;
+    const float a0 = (float)(1.0 / sqrt((double)dim));
+    for (int it = 0; it < (opt ? A.iters : 1); ++it) {
+        __syncthreads();
+        for (int i = (int)tid; i < len; i += THREADS) lut[i] = lut_entry(i, s_angle[0]);
+        double sn, co;
+        sincos(s_angle[1], &sn, &co);
+        const float2 cs = make_float2((float)co, (float)sn);
+        for (uint32_t z = tid; z < dim; z += THREADS) ps[z] = make_float2(a0, 0.f);
+        __syncthreads();
+        for (uint32_t z = tid; z < dim; z += THREADS) ps[z] = cmulf(ps[z], lut[cut(z)]);
+        for (int j = 0; j < n - 1; ++j) {
+            __syncthreads();
+            for (uint32_t i = tid; i < half; i += THREADS) {
+                const uint32_t z = ((i >> j) << (j + 1)) | (i & ((1u << j) - 1u));
+                rx_pair(ps[z], ps[z | (1u << j)], cs.x, cs.y);
+            }
+        }
+        __syncthreads();
+        for (uint32_t i = tid; i < half; i += THREADS) rx_pair(ps[i], ps[i ^ comp], cs.x, cs.y);
+        if (dim == 1 && tid == 0) ps[0] = cmulf(ps[0], make_float2(cs.x, -cs.y));
+        __syncthreads();
+        double e = 0.0;
+        for (uint32_t z = tid; z < dim; z += THREADS) {
+            const uint32_t c = cut(z);
+            e += ((double)ps[z].x * ps[z].x + (double)ps[z].y * ps[z].y) * (double)c;
+            la[z] = make_float2((float)c * ps[z].x, (float)c * ps[z].y);
+        }
+        e = block_sum(e, red);
+        double xb = 0.0;
+        // the top qubit (complement pairs; for n = 1 the single amplitude with
+        // itself) first, then qubits n-2..0
+        for (int j = n - 1; j >= 0; --j) {
+            __syncthreads();
+            float a = 0.f;
+            if (j == n - 1 && dim == 1) {
+                if (tid == 0) {
+                    a += la[0].x * ps[0].y - la[0].y * ps[0].x;
+                    ps[0] = cmulf(ps[0], make_float2(cs.x, cs.y));
+                    la[0] = cmulf(la[0], make_float2(cs.x, cs.y));
+                }
+            } else {
+                for (uint32_t i = tid; i < half; i += THREADS) {
+                    const uint32_t z = j == n - 1 ? i : ((i >> j) << (j + 1)) | (i & ((1u << j) - 1u));
+                    const uint32_t z1 = j == n - 1 ? i ^ comp : z | (1u << j);
+                    a += la[z].x * ps[z1].y - la[z].y * ps[z1].x;
+                    a += la[z1].x * ps[z].y - la[z1].y * ps[z].x;
+                    rx_pair(ps[z], ps[z1], cs.x, -cs.y);
+                    rx_pair(la[z], la[z1], cs.x, -cs.y);
+                }
+            }
+            xb += (double)a;
+        }
+        __syncthreads();
+        xb = block_sum(xb, red);
+        double gg = 0.0;
+        for (uint32_t z = tid; z < dim; z += THREADS)
+            gg += (double)((float)cut(z) * (la[z].x * ps[z].y - la[z].y * ps[z].x));
+        gg = block_sum(gg, red);
+        if (tid == 0) {
+            part.e[sd->tile_base] = e;
+            if (A.E) A.E[b] = e;
+            if (!opt) {
+                part.gg[sd->tile_base] = gg;
+                part.gb[sd->tile_base] = xb;
+                if (A.dgamma) {
+                    A.dgamma[b] = 2.0 * gg;
+                    A.dbeta[b] = 2.0 * xb;
+                }
+            }
+            red[0] = gg;
+            red[1] = xb;
+        }
+        __syncthreads();
+        if (mine) {
+            const double t = (double)(t0 + it + 1);
+            adam_update(th, m, v, 2.0 * red[tid], 1.0 - pow(A.b1, t), 1.0 - pow(A.b2, t), A.lr, A.b1, A.b2, A.eps, 1.0);
+            s_angle[tid] = th;
+        }
+    }
+    if (mine) {
+        A.theta[idx] = th;
+        A.m[idx] = m;
+        A.v[idx] = v;
+    }
+}
+
 // max_n, max_len: the list's largest qubit count and phase table. The tables
 // of all layers are kept where they fit 4096 entries, else one at a time.
 hipError_t launch_small(uint8_t* ws, const SubDesc* subs, const int32_t* list, int nlist, int max_n, int max_len,
                         bool grad, SmallArgs A, Partials part, hipStream_t s)
 {
     if (nlist <= 0) return hipSuccess;
+    if (grad && A.p == 1) {
+        A.lut_at = 1u << (max_n - 1);
+        hipLaunchKernelGGL(k_small_layer, dim3(nlist), dim3(THREADS), (2 * A.lut_at + max_len) * sizeof(float2), s, ws,
+                           subs, list, A, part);
+        return hipGetLastError();
+    }
     A.lut_at = max_n >= 11 ? 2u << (max_n - 1) : 0u;
     A.lut_cap = A.p * max_len < 4096 ? A.p * max_len : 4096;
     if (A.lut_cap < max_len) A.lut_cap = max_len;

@@ -44,7 +44,7 @@ def test_rule_for_wide_tiles():
     def slots(n, B, edges, flags=0x1 | 0x80):
         nq, off, u, v, w = batch_arrays([n] * B, edges)
         size = lambda p: _abi.qaoa_workspace_bytes(B, nq, off, w, p, 1, flags)
-        return (size(2) - size(1)) // (B * 8 << (n - 1))
+        return (size(3) - size(2)) // (B * 8 << (n - 1))
 
     for n, B, sparse, groups in [(20, 4, True, 2), (21, 1, True, 3), (21, 2, True, 2), (24, 1, True, 2),
                                  (25, 1, True, 2), (26, 2, True, 3), (27, 1, True, 3), (29, 1, True, 3),
@@ -95,7 +95,7 @@ def test_states(sizes, p, heavy):
 def test_gradient(sizes, p, memory):
     edges = [_edges(n, 1, 80 + 5 * i, sparse=True)[0] for i, n in enumerate(sizes)]
     gamma, beta = synth.uniform_angles(700 + p, p, batch=len(sizes))
-    bt = _batch(sizes, edges, max_p=p, max_k=4, gradient=True, gradient_memory=memory)
+    bt = _batch(sizes, edges, max_p=max(p, 2), max_k=4, gradient=True, gradient_memory=memory)  # (one layer: no wide tiles)
     E, dg, db = (t.cpu().numpy() for t in bt.expectation_grad(gamma, beta))
     again = [t.cpu().numpy() for t in bt.expectation_grad(gamma, beta)]
     assert np.array_equal(E, again[0]) and np.array_equal(dg, again[1]) and np.array_equal(db, again[2])
@@ -119,7 +119,7 @@ def test_gradient_29_qubits_matches_the_p1_closed_form():
     u = np.arange(m, dtype=np.int32)
     v = ((u + 1) % m).astype(np.int32)
     g, b = 0.7, 0.3
-    bt = QaoaBatch([n], [(u, v, np.ones(m, np.int32))], max_p=1, max_k=1, gradient=True)
+    bt = QaoaBatch([n], [(u, v, np.ones(m, np.int32))], max_p=2, max_k=1, gradient=True)
     E, dg, db = (float(t.reshape(-1)[0]) for t in bt.expectation_grad(np.array([[g]]), np.array([[b]])))
     s4, c4 = np.sin(4 * b), np.cos(4 * b)
     assert abs(E - m * (0.5 + 0.5 * s4 * np.sin(g) * np.cos(g))) <= E_TOL * m
