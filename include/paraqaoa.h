@@ -376,7 +376,8 @@ qaoa_status_t qaoa_state_offset(qaoa_batch_t h, int32_t b, size_t* out_offset);
  * split named here, batches large enough take 16384-amplitude tiles (13 low
  * qubits and the top one, strided groups of at most 12) for subgraphs where
  * that saves a group: 21..26, 29 and 30 qubits, in gradient batches up to 25
- * qubits and 29, 30, and only where the weight sum is at most 1.5 n.
+ * qubits and 29, 30, and only where the weight sum is at most 1.5 n and
+ * max_p is more than 1.
  * sizes[0..count) are the strided group sizes in qubit order for subgraphs
  * with n qubits (each 1..8, at most 3 groups, adding up to n - 12); count = 0
  * restores the default (fewest groups, sizes as even as possible). Batches
