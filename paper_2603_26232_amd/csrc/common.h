@@ -182,6 +182,11 @@ hipError_t launch_fwd_pass(uint8_t* ws, const SubDesc* subs, const int2* work, i
                            PassOps ops, Partials part, int lut_max, int prec, hipStream_t s);
 hipError_t launch_bwd_pass(uint8_t* ws, const SubDesc* subs, const int2* work, int nwork, int chain,
                            PassOps ops, Partials part, int lut_max, hipStream_t s);
+// ---- launchers (mixed.hip) ---- the passes of chain code 6
+hipError_t launch_fwd_mixed(uint8_t* ws, const SubDesc* subs, const int2* work, int nwork, PassOps ops, Partials part,
+                            int lut_max, hipStream_t s);
+hipError_t launch_bwd_mixed(uint8_t* ws, const SubDesc* subs, const int2* work, int nwork, PassOps ops, Partials part,
+                            int lut_max, hipStream_t s);
 // ---- launchers (small.hip) ----
 // Arguments of the whole-state kernel: angles [B*p]; outputs that may be NULL;
 // with iters > 0 theta, m, v [2*B*p] and the Adam constants (then gamma and
