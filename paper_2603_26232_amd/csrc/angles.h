@@ -38,9 +38,14 @@ __device__ inline RxCoef rx_coef(const SubDesc* sd, double bt)
     const bool tanm = fabs(c) >= fabs(s);
     rc.mode = tanm ? 0 : 1;
     rc.t = (float)(tanm ? s / c : -c / s);
-    rc.fsq = (float)(tanm ? c * c : s * s);
+    double f = tanm ? c : s;
+    // On wide tiles the factor is that of the rounded t, which makes f (I - i t X)
+    // unitary: the rounding of t otherwise changes the state's norm by as much for
+    // every qubit. (The other tiles keep f, and with it their bits; see wide_allowed.)
+    if (sd->wide) f = copysign(1.0 / sqrt(1.0 + (double)rc.t * rc.t), f);
+    rc.fsq = (float)(f * f);
     // per-qubit factors: forward c or -i s, inverse c or +i s
-    const double fr = tanm ? c : 0.0, fi_f = tanm ? 0.0 : -s, fi_i = tanm ? 0.0 : s;
+    const double fr = tanm ? f : 0.0, fi_f = tanm ? 0.0 : -f, fi_i = tanm ? 0.0 : f;
     for (int g = 0; g < MAX_GROUPS; ++g) {
         const int nq = g < sd->ngroups ? sd->gsize[g] : 0;
         double r, i;
