@@ -80,18 +80,19 @@ __device__ inline void rx_lane(float2 (&v)[R], float t)
     }
 }
 
-// a += la.x * (partner's ps.y), b += la.y * (partner's ps.x), four amplitudes
+// per amplitude la.x * (partner's ps.y) - la.y * (partner's ps.x), which cancel, one
+// after the other into a (even registers) or b (odd ones)
 #define PQ_XB_LANE(D)                                                                                            \
     asm("s_nop 1\n\t"                                                                                            \
         "v_fmac_f32_dpp %0, %3, %10 " D "\n\t"                                                                   \
-        "v_fmac_f32_dpp %1, %2, %11 " D "\n\t"                                                                   \
-        "v_fmac_f32_dpp %0, %5, %12 " D "\n\t"                                                                   \
-        "v_fmac_f32_dpp %1, %4, %13 " D "\n\t"                                                                   \
+        "v_fmac_f32_dpp %1, %5, %12 " D "\n\t"                                                                   \
+        "v_fmac_f32_dpp %0, %2, -%11 " D "\n\t"                                                                  \
+        "v_fmac_f32_dpp %1, %4, -%13 " D "\n\t"                                                                  \
         "v_fmac_f32_dpp %0, %7, %14 " D "\n\t"                                                                   \
-        "v_fmac_f32_dpp %1, %6, %15 " D "\n\t"                                                                   \
-        "v_fmac_f32_dpp %0, %9, %16 " D "\n\t"                                                                   \
-        "v_fmac_f32_dpp %1, %8, %17 " D                                                                          \
-        : "+v"(a), "+v"(b)                                                                                       \
+        "v_fmac_f32_dpp %1, %9, %16 " D "\n\t"                                                                   \
+        "v_fmac_f32_dpp %0, %6, -%15 " D "\n\t"                                                                  \
+        "v_fmac_f32_dpp %1, %8, -%17 " D                                                                         \
+        : "+&v"(a), "+&v"(b)                                                                                     \
         : "v"(ps[r].x), "v"(ps[r].y), "v"(ps[r + 1].x), "v"(ps[r + 1].y), "v"(ps[r + 2].x), "v"(ps[r + 2].y),    \
           "v"(ps[r + 3].x), "v"(ps[r + 3].y), "v"(la[r].x), "v"(la[r].y), "v"(la[r + 1].x), "v"(la[r + 1].y),    \
           "v"(la[r + 2].x), "v"(la[r + 2].y), "v"(la[r + 3].x), "v"(la[r + 3].y))
@@ -112,11 +113,12 @@ __device__ inline float xb_lane(const float2 (&ps)[R], const float2 (&la)[R])
     } else {
 #pragma unroll
         for (int r = 0; r < R; ++r) {
-            a = fmaf(across<K>(ps[r].y), la[r].x, a);
-            b = fmaf(across<K>(ps[r].x), la[r].y, b);
+            float& x = r & 1 ? b : a;
+            x = fmaf(across<K>(ps[r].y), la[r].x, x);
+            x = fmaf(-across<K>(ps[r].x), la[r].y, x);
         }
     }
-    return a - b;
+    return a + b;
 }
 
 // exchanges lane bit 4 (H = 16) or 5 (H = 32) of a pair of registers: afterwards

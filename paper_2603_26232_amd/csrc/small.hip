@@ -18,7 +18,8 @@
 // n flips of a layer cancel here: together they complement the index and the
 // top qubit's flip complements it back. f^n sits in the phase table, which the
 // workgroup builds itself from the angles (FP64 products, sine and cosine).
-// Gradient terms are FP32 sums per lane and index bit, FP64 beyond.
+// Beta terms are FP32 sums per lane and index bit (at most eight amplitudes), FP64
+// beyond; gamma terms FP64 throughout.
 //
 // Measured at p = 3, one subgraph, against one rotation per pass over LDS by 256
 // lanes: forward 46.8 -> 9.1 us at 13 qubits (28.0 -> 8.4 at 12), an optimiser
@@ -77,10 +78,12 @@ __device__ inline float xb_reg(const float2 (&ps)[R], const float2 (&la)[R])
     float a = 0.f, b = 0.f;
 #pragma unroll
     for (int r = 0; r < R; ++r) {
-        a = fmaf(la[r].x, ps[r ^ (1 << K)].y, a);
-        b = fmaf(la[r].y, ps[r ^ (1 << K)].x, b);
+        const float2 o = ps[r ^ (1 << K)];
+        float& x = r & 1 ? b : a;
+        x = fmaf(la[r].x, o.y, x);
+        x = fmaf(-la[r].y, o.x, x);
     }
-    return a - b;
+    return a + b;
 }
 
 // exchanges lane bit 4 (H = 16) or 5 (H = 32) with register bit 0
@@ -113,10 +116,11 @@ __device__ inline float xb_with(const float2 (&o)[R], const float2 (&la)[R])
     float a = 0.f, b = 0.f;
 #pragma unroll
     for (int r = 0; r < R; ++r) {
-        a = fmaf(la[r].x, o[r].y, a);
-        b = fmaf(la[r].y, o[r].x, b);
+        float& x = r & 1 ? b : a;
+        x = fmaf(la[r].x, o[r].y, x);
+        x = fmaf(-la[r].y, o[r].x, x);
     }
-    return a - b;
+    return a + b;
 }
 
 // Forward rotation of every index bit in the wave: lane bits nl (6, or n - 1
@@ -396,12 +400,13 @@ __device__ __forceinline__ void run(uint8_t* ws, const SubDesc* sd, int b, const
                         const uint32_t q = r ^ (R - 1);
                         const uint32_t j = xslot<W>((q & ~WM) | (wv ^ WM), q & WM, lane ^ lflip);
                         const float2 a = x[i], po = x[j], c = y[i], lo = y[j];
-                        xa = fmaf(c.x, po.y, xa);
-                        xb = fmaf(c.y, po.x, xb);
+                        float& xr = r & 1 ? xb : xa;
+                        xr = fmaf(c.x, po.y, xr);
+                        xr = fmaf(-c.y, po.x, xr);
                         v[r] = make_float2(fmaf(s.t, po.y, a.x), fmaf(-s.t, po.x, a.y));
                         la[r] = make_float2(fmaf(s.t, lo.y, c.x), fmaf(-s.t, lo.x, c.y));
                     }
-                    s.add(xa - xb);
+                    s.add(xa + xb);
                     alt ^= 1;
                 } else {
                     float2 u[R], po[R], lo[R];
@@ -420,12 +425,12 @@ __device__ __forceinline__ void run(uint8_t* ws, const SubDesc* sd, int b, const
                     back_reg<1>(v, la, s);
                     if constexpr (KW > 2) back_reg<2>(v, la, s);
                 }
-                float g = 0.f;
+                double g = 0.0;
 #pragma unroll
                 for (int r = 0; r < R; ++r)
-                    g = fmaf((float)cut(r, alt), fmaf(la[r].x, v[r].y, -la[r].y * v[r].x), g);
+                    g += (double)((float)cut(r, alt) * fmaf(la[r].x, v[r].y, -la[r].y * v[r].x));
                 const float2 F = S.F[l];
-                const double gg = wave_total((double)g * ((double)F.x * F.x + (double)F.y * F.y));
+                const double gg = wave_total(g * ((double)F.x * F.x + (double)F.y * F.y));
                 const double xb = wave_total(s.acc);
                 if (lane == 0) {
                     S.sg[l][wv] = gg;

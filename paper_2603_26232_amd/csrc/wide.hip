@@ -177,21 +177,22 @@ __device__ inline float xb_bit(const float2 (&ps)[WR], const float2 (&la)[WR])
     return a0 + a1;
 }
 
+// the beta terms of the layout's bits: FP32 over a lane's 32 amplitudes, FP64 over bits
 template <int L, int NB>
-__device__ inline float xb_round(const float2 (&ps)[WR], const float2 (&la)[WR])
+__device__ inline double xb_round(const float2 (&ps)[WR], const float2 (&la)[WR])
 {
     constexpr int Q = L == LLIN ? 9 : 4;
-    float a = 0.f;
-    if constexpr (active<NB>(Q)) a += xb_bit<0>(ps, la);
-    if constexpr (active<NB>(Q + 1)) a += xb_bit<1>(ps, la);
-    if constexpr (active<NB>(Q + 2)) a += xb_bit<2>(ps, la);
-    if constexpr (active<NB>(Q + 3)) a += xb_bit<3>(ps, la);
-    if constexpr (active<NB>(Q + 4)) a += xb_bit<4>(ps, la);
+    double a = 0.0;
+    if constexpr (active<NB>(Q)) a += (double)xb_bit<0>(ps, la);
+    if constexpr (active<NB>(Q + 1)) a += (double)xb_bit<1>(ps, la);
+    if constexpr (active<NB>(Q + 2)) a += (double)xb_bit<2>(ps, la);
+    if constexpr (active<NB>(Q + 3)) a += (double)xb_bit<3>(ps, la);
+    if constexpr (active<NB>(Q + 4)) a += (double)xb_bit<4>(ps, la);
     if constexpr (L == LL1) {
-        if constexpr (active<NB>(3)) a += xb_lane<3>(ps, la);
-        if constexpr (active<NB>(2)) a += xb_lane<2>(ps, la);
-        if constexpr (active<NB>(1)) a += xb_lane<1>(ps, la);
-        if constexpr (active<NB>(0)) a += xb_lane<0>(ps, la);
+        if constexpr (active<NB>(3)) a += (double)xb_lane<3>(ps, la);
+        if constexpr (active<NB>(2)) a += (double)xb_lane<2>(ps, la);
+        if constexpr (active<NB>(1)) a += (double)xb_lane<1>(ps, la);
+        if constexpr (active<NB>(0)) a += (double)xb_lane<0>(ps, la);
     }
     return a;
 }
@@ -221,7 +222,7 @@ __device__ inline void seg_rot2(float2 (&v)[WR], float2* ex, float t, uint32_t t
 template <int L, int NB>
 __device__ inline void bwd_round(float2 (&ps)[WR], float2 (&la)[WR], const RxC& rc, float& wdone, double& acc)
 {
-    acc += (double)(wdone * xb_round<L, NB>(ps, la));
+    acc += (double)wdone * xb_round<L, NB>(ps, la);
     __builtin_amdgcn_sched_barrier(0);
     rx_round<L, NB>(ps, -rc.t);
     rx_round<L, NB>(la, -rc.t);
@@ -485,19 +486,19 @@ __global__ __launch_bounds__(WT) __attribute__((amdgpu_waves_per_eu(2))) void k_
     double acc_pre = 0.0, acc_ph = 0.0, acc_post = 0.0, acc_e = 0.0;
     if constexpr (KIND == B_LAST) {
         seg_rot2<NB>(la, ex, -pre.t, tid);
-        float a = 0.f;
+        float a[2] = {0.f, 0.f};
 #pragma unroll
         for (int r = 0; r < WR; ++r) {
             const uint32_t c = cr.at(r);
             ps[r] = lut[c];
-            a = fmaf((float)c, fmaf(la[r].x, ps[r].y, -la[r].y * ps[r].x), a);
+            a[r & 1] = fmaf((float)c, fmaf(la[r].x, ps[r].y, -la[r].y * ps[r].x), a[r & 1]);
         }
-        acc_ph = (double)a;
+        acc_ph = (double)a[0] + (double)a[1];
         // beta terms in both layouts
-        acc_pre += (double)xb_round<LL1, NB>(ps, la);
+        acc_pre += xb_round<LL1, NB>(ps, la);
         xchg2<LL1, LLIN>(ex, tid, ps);
         xchg2<LL1, LLIN>(ex, tid, la);
-        acc_pre += (double)xb_round<LLIN, NB>(ps, la);
+        acc_pre += xb_round<LLIN, NB>(ps, la);
     } else if constexpr (KIND == B_FUSED) {
         seg_rot2<NB>(ps, ex, pre.t, tid);
         scale_regs(ps, pre.Ff);
@@ -521,11 +522,11 @@ __global__ __launch_bounds__(WT) __attribute__((amdgpu_waves_per_eu(2))) void k_
             scale_regs(la, pre.Fi);
             store_state<LL1, G0>(la, sl, geo, tid, m_end);
         } else {
-            float a = 0.f;
+            float a[2] = {0.f, 0.f};
 #pragma unroll
             for (int r = 0; r < WR; ++r)
-                a = fmaf((float)cr.at(r), fmaf(la[r].x, ps[r].y, -la[r].y * ps[r].x), a);
-            acc_ph = (double)a * (double)(pre.Fi.x * pre.Fi.x + pre.Fi.y * pre.Fi.y);
+                a[r & 1] = fmaf((float)cr.at(r), fmaf(la[r].x, ps[r].y, -la[r].y * ps[r].x), a[r & 1]);
+            acc_ph = ((double)a[0] + (double)a[1]) * (double)(pre.Fi.x * pre.Fi.x + pre.Fi.y * pre.Fi.y);
             __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
             for (int r = 0; r < WR; ++r) {
