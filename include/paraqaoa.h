@@ -115,8 +115,10 @@ typedef void* qaoa_stream_t;
  * qaoa_optimize keep the class of the largest subgraphs on the caller's
  * stream and give the other classes and the small-subgraph kernel to three
  * side streams of the library, forked from and joined back to the caller's
- * stream with events within each call (each Adam step of qaoa_optimize), so
- * that the smaller classes fill the device while the largest one runs.
+ * stream with events within each call (the classes within each Adam step of
+ * qaoa_optimize; its small-subgraph kernel, which runs all the steps of its
+ * subgraphs in one launch, once around them), so that the smaller classes fill
+ * the device while the largest one runs.
  * Results are bit-identical to the default. The side streams and events are
  * created once per device (default priority) by the first qaoa_batch_create
  * with this flag, with that device current, and are kept until the process

@@ -711,21 +711,25 @@ struct qaoa_batch_s {
 // small-subgraph kernel (if any) and every class. Default: all on st, in
 // order. Concurrent classes: class 0 (the largest subgraphs) on st, the rest
 // each on the side stream with the least work so far (tiles x passes),
-// forked from st and joined back into it.
+// forked from st and joined back into it. with_small = false leaves the
+// small-subgraph kernel out. A caller that has given the last side stream work of
+// its own holds the lock and passes nside = NSIDE - 1.
 template <typename F>
-static qaoa_status_t for_each_class(qaoa_batch_t h, int32_t p, hipStream_t st, F body)
+static qaoa_status_t for_each_class(qaoa_batch_t h, int32_t p, hipStream_t st, bool with_small, int nside, F body)
 {
     const Plan& P = h->P;
     const int nc = (int)P.classes.size();
-    if (!h->side || nc + (P.nsmall ? 1 : 0) < 2) {
+    const bool small = P.nsmall && with_small;
+    if (!h->side || nc + small < 2) {
         qaoa_status_t s;
-        if (P.nsmall && (s = body(-1, st)) != QAOA_OK) return s;
+        if (small && (s = body(-1, st)) != QAOA_OK) return s;
         for (int k = 0; k < nc; ++k)
             if ((s = body(k, st)) != QAOA_OK) return s;
         return QAOA_OK;
     }
     SideStreams& ss = *h->side;
-    std::lock_guard<std::mutex> lk(g_side_mu);
+    std::unique_lock<std::mutex> lk(g_side_mu, std::defer_lock);
+    if (nside == NSIDE) lk.lock();
     HIP_TRY(hipEventRecord(ss.fork, st));
     double load[NSIDE] = {};
     bool used[NSIDE] = {};
@@ -735,7 +739,7 @@ static qaoa_status_t for_each_class(qaoa_batch_t h, int32_t p, hipStream_t st, F
     };
     auto pick = [&](double w) -> hipStream_t {
         int j = 0;
-        for (int i = 1; i < NSIDE; ++i)
+        for (int i = 1; i < nside; ++i)
             if (load[i] < load[j]) j = i;
         load[j] += w;
         if (!used[j]) {
@@ -747,10 +751,11 @@ static qaoa_status_t for_each_class(qaoa_batch_t h, int32_t p, hipStream_t st, F
     qaoa_status_t s = QAOA_OK;
     if (nc > 0) s = body(0, st);
     for (int k = 1; k < nc && s == QAOA_OK && ferr == hipSuccess; ++k)
-        s = body(k, pick((double)P.classes[k].work.size() * (P.classes[k].wide ? WIDE_TILE / TILE : 1) * (double)(p * (P.classes[k].G - 1) + 1)));
-    if (P.nsmall && s == QAOA_OK && ferr == hipSuccess) s = body(-1, pick((double)P.nsmall * p));
+        s = body(k, pick((double)P.classes[k].work.size() * (P.classes[k].wide ? WIDE_TILE / TILE : 1) *
+                         (double)(p * (P.classes[k].G - 1) + 1)));
+    if (small && s == QAOA_OK && ferr == hipSuccess) s = body(-1, pick((double)P.nsmall * p));
     // join every side stream that was forked, also after an error
-    for (int j = 0; j < NSIDE; ++j) {
+    for (int j = 0; j < nside; ++j) {
         if (!used[j]) continue;
         note(hipEventRecord(ss.join[j], ss.s[j]));
         note(hipStreamWaitEvent(st, ss.join[j], 0));
@@ -904,7 +909,7 @@ extern "C" qaoa_status_t qaoa_apply_layers(qaoa_batch_t h, int32_t p, const doub
         ProfScope ps("angle_prep", st, angle_bytes(P, p));
         HIP_TRY(launch_angle_prep(h->ws, h->d_subs, P.B, p, d_gamma, d_beta, st));
     }
-    s = for_each_class(h, p, st, [&](int k, hipStream_t cs) -> qaoa_status_t {
+    s = for_each_class(h, p, st, true, NSIDE, [&](int k, hipStream_t cs) -> qaoa_status_t {
         if (k < 0) {
             ProfScope ps("small", cs, small_bytes(P, p, false));
             HIP_TRY(small_subgraphs(h, false, SmallArgs{p, P.B, 0, 0, 0, d_gamma, d_beta}, cs));
@@ -968,7 +973,6 @@ static qaoa_status_t enqueue_class_grad(qaoa_batch_t h, int k, int32_t p, const 
 {
     Plan& P = h->P;
     if (k < 0) {
-        if (a.iters > 0) return QAOA_OK;  // the optimiser has run them
         ProfScope ps("small", st, small_bytes(P, p, true));
         HIP_TRY(small_subgraphs(h, true, a, st));
         return QAOA_OK;
@@ -1023,11 +1027,13 @@ static qaoa_status_t enqueue_class_grad(qaoa_batch_t h, int k, int32_t p, const 
     return QAOA_OK;
 }
 
-// the small-subgraph kernel and every tile pass of one gradient evaluation
-// (forward sweep, fused turn, adjoint sweep), after the angle tables are set
-static qaoa_status_t enqueue_grad_passes(qaoa_batch_t h, int32_t p, const SmallArgs& a, hipStream_t st)
+// the small-subgraph kernel (unless a holds steps: the optimiser runs it itself)
+// and every tile pass of one gradient evaluation (forward sweep, fused turn,
+// adjoint sweep), after the angle tables are set
+static qaoa_status_t enqueue_grad_passes(qaoa_batch_t h, int32_t p, const SmallArgs& a, int nside, hipStream_t st)
 {
-    return for_each_class(h, p, st, [&](int k, hipStream_t cs) { return enqueue_class_grad(h, k, p, a, cs); });
+    return for_each_class(h, p, st, a.iters == 0, nside,
+                          [&](int k, hipStream_t cs) { return enqueue_class_grad(h, k, p, a, cs); });
 }
 
 extern "C" qaoa_status_t qaoa_expectation_grad(qaoa_batch_t h, int32_t p, const double* d_gamma,
@@ -1051,7 +1057,7 @@ extern "C" qaoa_status_t qaoa_expectation_grad(qaoa_batch_t h, int32_t p, const 
         a.dgamma = d_dgamma;
         a.dbeta = d_dbeta;
     }
-    s = enqueue_grad_passes(h, p, a, st);
+    s = enqueue_grad_passes(h, p, a, NSIDE, st);
     if (s != QAOA_OK) return s;
     if (!P.only_small) {
         ProfScope ps("reduce", st, 8.0 * P.total_tiles * (1.0 + p * (MAX_GROUPS + 1.0)));
@@ -1095,22 +1101,47 @@ extern "C" qaoa_status_t qaoa_optimize(qaoa_batch_t h, int32_t p, int32_t iters,
     a.b1 = beta1;
     a.b2 = beta2;
     a.eps = eps;
-    if (P.nsmall) {
-        ProfScope ps("small", st, iters * small_bytes(P, p, true));
-        HIP_TRY(small_subgraphs(h, true, a, st));
+    // (concurrent classes: on the last side stream, beside the tiled ones; it shares
+    // no row of theta, m, v or d_E with them, and the step count that it reads is
+    // advanced after the join)
+    const bool apart = h->side && P.nsmall && !P.classes.empty();
+    std::unique_lock<std::mutex> lk(g_side_mu, std::defer_lock);
+    hipStream_t small_st = st;
+    if (apart) {
+        lk.lock();
+        small_st = h->side->s[NSIDE - 1];
+        HIP_TRY(hipEventRecord(h->side->fork, st));
+        HIP_TRY(hipStreamWaitEvent(small_st, h->side->fork, 0));
     }
-    if (!P.only_small) {
-        ProfScope ps("angle_prep", st, angle_bytes(P, p));
-        HIP_TRY(launch_angle_prep(h->ws, h->d_subs, P.B, p, d_theta, d_theta + BP, st));
+    auto steps = [&]() -> qaoa_status_t {
+        if (P.nsmall) {
+            ProfScope ps("small", small_st, iters * small_bytes(P, p, true));
+            HIP_TRY(small_subgraphs(h, true, a, small_st));
+        }
+        if (!P.only_small) {
+            ProfScope ps("angle_prep", st, angle_bytes(P, p));
+            HIP_TRY(launch_angle_prep(h->ws, h->d_subs, P.B, p, d_theta, d_theta + BP, st));
+        }
+        for (int it = 0; it < iters && !P.only_small; ++it) {
+            qaoa_status_t e = enqueue_grad_passes(h, p, a, apart ? NSIDE - 1 : NSIDE, st);
+            if (e != QAOA_OK) return e;
+            ProfScope ps("reduce_adam", st,
+                         8.0 * P.total_tiles * (1.0 + p * (MAX_GROUPS + 1.0)) + 7.0 * 8.0 * 2.0 * BP +
+                             angle_bytes(P, p));
+            HIP_TRY(launch_reduce_adam(h->ws, h->d_subs, P.B, p, h->part, d_theta, d_m, d_v, d_step, it, lr, beta1,
+                                       beta2, eps, d_E, st));
+        }
+        return QAOA_OK;
+    };
+    s = steps();
+    if (apart) {  // also after an error
+        const hipError_t e = hipEventRecord(h->side->join[NSIDE - 1], small_st);
+        const hipError_t f = e == hipSuccess ? hipStreamWaitEvent(st, h->side->join[NSIDE - 1], 0) : e;
+        lk.unlock();
+        if (s == QAOA_OK && f != hipSuccess)
+            s = fail(QAOA_ERR_HIP, "join of the small subgraphs: %s", hipGetErrorString(f));
     }
-    for (int it = 0; it < iters && !P.only_small; ++it) {
-        s = enqueue_grad_passes(h, p, a, st);
-        if (s != QAOA_OK) return s;
-        ProfScope ps("reduce_adam", st,
-                     8.0 * P.total_tiles * (1.0 + p * (MAX_GROUPS + 1.0)) + 7.0 * 8.0 * 2.0 * BP + angle_bytes(P, p));
-        HIP_TRY(launch_reduce_adam(h->ws, h->d_subs, P.B, p, h->part, d_theta, d_m, d_v, d_step, it, lr, beta1,
-                                   beta2, eps, d_E, st));
-    }
+    if (s != QAOA_OK) return s;
     HIP_TRY(launch_step_advance(d_step, iters, st));
     h->state_valid = false;
     h->e_valid = true;
