@@ -201,7 +201,7 @@ struct Plan {
              o_pgb = 0,
              o_pgg = 0, o_keys = 0, total = 0;
     int nsmall = 0;
-    int small_n = 0, small_len = 0;  // largest qubit count and phase table of the small ones
+    int small_n = 0, small_len[3] = {};  // largest qubit count of the small ones, largest phase table by small_waves
     bool only_small = false;         // every subgraph is run by the small-subgraph kernel
     // host images of the metadata regions
     std::vector<int2> work_all;
@@ -478,7 +478,8 @@ qaoa_status_t make_plan(int32_t B, const int32_t* nq, const int64_t* eoff, const
     P.only_small = P.nsmall == B;
     for (int b : P.small) {
         P.small_n = std::max(P.small_n, (int)P.subs[b].n);
-        P.small_len = std::max(P.small_len, (int)P.subs[b].lut_len);
+        int& len = P.small_len[small_waves(P.subs[b].n)];
+        len = std::max(len, (int)P.subs[b].lut_len);
     }
 
     // regions
@@ -912,7 +913,7 @@ extern "C" qaoa_status_t qaoa_apply_layers(qaoa_batch_t h, int32_t p, const doub
     s = for_each_class(h, p, st, true, NSIDE, [&](int k, hipStream_t cs) -> qaoa_status_t {
         if (k < 0) {
             ProfScope ps("small", cs, small_bytes(P, p, false));
-            HIP_TRY(small_subgraphs(h, false, SmallArgs{p, P.B, 0, 0, 0, d_gamma, d_beta}, cs));
+            HIP_TRY(small_subgraphs(h, false, SmallArgs{p, P.B, 0, 0, d_gamma, d_beta}, cs));
             return QAOA_OK;
         }
         const auto& c = P.classes[k];
@@ -1051,7 +1052,7 @@ extern "C" qaoa_status_t qaoa_expectation_grad(qaoa_batch_t h, int32_t p, const 
         ProfScope ps("angle_prep", st, angle_bytes(P, p));
         HIP_TRY(launch_angle_prep(h->ws, h->d_subs, P.B, p, d_gamma, d_beta, st));
     }
-    SmallArgs a{p, P.B, 0, 0, 0, d_gamma, d_beta};
+    SmallArgs a{p, P.B, 0, 0, d_gamma, d_beta};
     if (P.only_small) {  // one tile per subgraph: nothing to reduce
         a.E = d_E;
         a.dgamma = d_dgamma;

@@ -190,9 +190,9 @@ hipError_t launch_bwd_mixed(uint8_t* ws, const SubDesc* subs, const int2* work, 
 // ---- launchers (small.hip) ----
 // Arguments of the whole-state kernel: angles [B*p]; outputs that may be NULL;
 // with iters > 0 theta, m, v [2*B*p] and the Adam constants (then gamma and
-// beta are not read). The lut fields are the launcher's.
+// beta are not read). lut_at is the launcher's.
 struct SmallArgs {
-    int32_t p, B, iters, lut_cap;
+    int32_t p, B, iters;
     uint32_t lut_at;
     const double *gamma, *beta;
     double *E, *dgamma, *dbeta;
@@ -200,8 +200,10 @@ struct SmallArgs {
     const int32_t* step;
     double lr, b1, b2, eps;
 };
-hipError_t launch_small(uint8_t* ws, const SubDesc* subs, const int32_t* list, int nlist, int max_n, int max_len,
-                        bool grad, SmallArgs A, Partials part, hipStream_t s);
+// the kernel's number of waves for n qubits, as an index: 1, 4, 8
+inline int small_waves(int n) { return n <= 10 ? 0 : n <= 12 ? 1 : 2; }
+hipError_t launch_small(uint8_t* ws, const SubDesc* subs, const int32_t* list, int nlist, int max_n,
+                        const int (&max_len)[3], bool grad, SmallArgs A, Partials part, hipStream_t s);
 // ---- launchers (wide.hip) ----
 // chain: 3: group 0; 7..12: a strided group of that many qubits
 hipError_t launch_fwd_wide(uint8_t* ws, const SubDesc* subs, const int2* work, int nwork, int chain,

@@ -28,6 +28,8 @@
 //
 // The optimiser runs all its steps in one launch: subgraphs are independent,
 // so theta, the moments and the tables never leave the CU between steps.
+#include <algorithm>
+
 #include "angles.h"
 #include "lane.h"
 
@@ -37,6 +39,18 @@ namespace {
 
 constexpr int ST = 512;  // threads at most
 constexpr int STEPS = 64;  // steps whose bias corrections are computed at a time
+// A phase table of more than PART_MIN entries per thread, or tables of more than
+// LUT_CAP entries over all layers, are kept as parts: e^{-i gamma c} is the product (in
+// FP64, as the parts are) of e^{-i gamma (c mod 32)} and e^{-i gamma 32 (c / 32)}, taken
+// for each amplitude when it is used: one sine and cosine an entry made a table of
+// 2000 entries the longest part of a call. Before / with parts, weight sum 2000:
+// forward, one subgraph of 10 qubits, p = 3 59.9 / 8.9 us, p = 8 154 / 17.9; 2048 of
+// them, p = 8 593 / 47.1; gradient of one of 13 qubits, weight sum 300, p = 32 (a
+// table of 4096 entries at most in LDS, the rest in the workspace) 209 / 217. At weight
+// sum 300 and 10 qubits p = 3 forward 11.4 / 7.8, gradient 19.1 / 16.9, of 2048 28.5 / 32.3.
+constexpr int PART_LO = 32, PART_MIN = 2, LUT_CAP = 4096;
+__host__ __device__ inline bool in_parts(int len, int p, int threads) { return len > PART_MIN * threads || p * len > LUT_CAP; }
+__host__ __device__ inline int part_count(int len) { return PART_LO + (len - 1) / PART_LO + 1; }
 
 template <int X>
 constexpr int log2c()
@@ -228,8 +242,9 @@ struct SmallShared {
     double k1[STEPS], k2[STEPS];  // Adam's bias corrections of the next steps
 };
 
-// W waves of R registers per lane; GRAD: gradient (and optimiser) or forward.
-template <int W, int R, bool GRAD>
+// W waves of R registers per lane; GRAD: gradient (and optimiser) or forward;
+// LONG: some subgraph of the launch may have its phase tables in parts.
+template <int W, int R, bool GRAD, bool LONG>
 __device__ __forceinline__ void run(uint8_t* ws, const SubDesc* sd, int b, const SmallArgs& A, Partials part,
                                     float2* dyn, SmallShared& S)
 {
@@ -241,7 +256,9 @@ __device__ __forceinline__ void run(uint8_t* ws, const SubDesc* sd, int b, const
     const int nl = n - 1 < 6 ? n - 1 : 6;
     float2* buf = dyn;                                    // W > 1: two exchange buffers
     float2* lut = dyn + A.lut_at;                         // phase tables
-    const bool all = p * len <= A.lut_cap;                // every layer's table at once
+    double2* part_of = (double2*)lut;                     // or their parts
+    const bool parts = LONG && in_parts(len, p, (int)T);
+    const int per = parts ? part_count(len) : len;        // entries per layer
     // the lane of the complement (index bits 0..5 flipped) of this one
     const uint32_t rest = (dim - 1u) & 63u;
     const int lflip = (int)(row_lanes(rest & 15u) | (rest & 48u));
@@ -296,24 +313,27 @@ __device__ __forceinline__ void run(uint8_t* ws, const SubDesc* sd, int b, const
     for (int it = 0; it < (opt ? A.iters : 1); ++it) {
         auto gamma_of = [&](int l) { return opt ? S.angle[l] : gm[l]; };
         auto beta_of = [&](int l) { return opt ? S.angle[p + l] : bt[l]; };
-        // phase tables (where those of all layers do not fit in LDS, they wait in
-        // the workspace) and rotation parameters, one sine and cosine each
-        float2* tables = all ? lut : (float2*)(ws + sd->lut);
-        for (int i = (int)tid; i < p * len + p; i += T) {
-            const int l = i / len;
+        // phase tables, or their parts, and rotation parameters, one sine and cosine
+        // each
+        for (int i = (int)tid; i < p * per + p; i += T) {
+            const int l = i / per;
             const bool phase = l < p;
+            int c = i % per;
+            if (LONG && parts && c >= PART_LO) c = (c - PART_LO) * PART_LO;
             double sn, cs;
-            sincos(phase ? gamma_of(l) * (double)(i % len) : beta_of(i - p * len), &sn, &cs);
-            if (phase) {
-                tables[i] = make_float2((float)cs, (float)-sn);
+            sincos(phase ? gamma_of(l) * (double)c : beta_of(i - p * per), &sn, &cs);
+            if (LONG && parts && phase) {
+                part_of[i] = make_double2(cs, -sn);
+            } else if (phase) {
+                lut[i] = make_float2((float)cs, (float)-sn);
             } else {
                 // e^{-i beta X} = f (I - i t X) X^flip as in rx_coef
                 const bool tanm = fabs(cs) >= fabs(sn);
-                S.rx[i - p * len] = make_float2((float)(tanm ? sn / cs : -cs / sn),
+                S.rx[i - p * per] = make_float2((float)(tanm ? sn / cs : -cs / sn),
                                                 (float)(tanm ? cs * cs : sn * sn));
                 double fr, fi;
                 cpow_d(tanm ? cs : 0.0, tanm ? 0.0 : -sn, n, fr, fi);
-                S.F[i - p * len] = make_float2((float)fr, (float)fi);
+                S.F[i - p * per] = make_float2((float)fr, (float)fi);
             }
         }
         if (opt && it % STEPS == 0)
@@ -323,23 +343,29 @@ __device__ __forceinline__ void run(uint8_t* ws, const SubDesc* sd, int b, const
                 S.k2[i] = 1.0 - pow(A.b2, t);
             }
         __syncthreads();
-        for (int i = (int)tid; i < p * len; i += T) tables[i] = cmulf(tables[i], S.F[i / len]);
-        __syncthreads();
-        // layer l's table, with f^n
-        auto table = [&](int l) -> const float2* {
-            if (all) return lut + l * len;
-            sync<W>();
-            for (int i = (int)tid; i < len; i += T) lut[i] = tables[l * len + i];
-            sync<W>();
-            return lut;
+        if (!LONG || !parts) {
+#pragma unroll 1
+            for (int i = (int)tid; i < p * len; i += T) lut[i] = cmulf(lut[i], S.F[i / len]);
+            __syncthreads();
+        }
+        // phase at cut value c with f^n: L = layer l's table, P its parts
+        auto phase_of = [&](const float2* L, const double2* P, float2 F, uint32_t c) -> float2 {
+            if (!LONG || !parts) return L[c];
+            __builtin_amdgcn_sched_barrier(0);  // one amplitude at a time: registers are short
+            const double2 a = P[c % PART_LO], b = P[PART_LO + c / PART_LO];
+            const double x = a.x * b.x - a.y * b.y, y = a.x * b.y + a.y * b.x, fr = F.x, fi = F.y;
+            return make_float2((float)(x * fr - y * fi), (float)(x * fi + y * fr));
         };
         alt = 0;
+#pragma clang loop unroll(disable)
         for (int l = 0; l < p; ++l) {
-            const float2* L = table(l);
+            const float2* L = lut + l * len;
+            const double2* P = part_of + l * per;
+            const float2 F = LONG ? S.F[l] : make_float2(1.f, 0.f);
             const float t = S.rx[l].x;
 #pragma unroll
             for (int r = 0; r < R; ++r) {
-                const float2 f = L[cut(r, alt)];
+                const float2 f = phase_of(L, P, F, cut(r, alt));
                 if (l == 0) v[r] = index(r, 0) < dim ? make_float2(amp * f.x, amp * f.y) : make_float2(0.f, 0.f);
                 else v[r] = cmulf(v[r], f);
             }
@@ -381,6 +407,7 @@ __device__ __forceinline__ void run(uint8_t* ws, const SubDesc* sd, int b, const
                 const float c = (float)cut(r, alt);
                 la[r] = make_float2(c * v[r].x, c * v[r].y);
             }
+#pragma clang loop unroll(disable)
             for (int l = p - 1; l >= 0; --l) {
                 Back s{-S.rx[l].x, S.rx[l].y, 1.f, 0.0};
                 back(v, la, nl, s);
@@ -437,10 +464,11 @@ __device__ __forceinline__ void run(uint8_t* ws, const SubDesc* sd, int b, const
                     S.sb[l][wv] = xb;
                 }
                 if (l > 0) {
-                    const float2* L = table(l);
+                    const float2* L = lut + l * len;
+                    const double2* P = part_of + l * per;
 #pragma unroll
                     for (int r = 0; r < R; ++r) {  // conj(f^n) undoes f^n and the phase of this layer
-                        float2 f = L[cut(r, alt)];
+                        float2 f = phase_of(L, P, F, cut(r, alt));
                         f.y = -f.y;
                         v[r] = cmulf(v[r], f);
                         la[r] = cmulf(la[r], f);
@@ -500,22 +528,22 @@ __device__ __forceinline__ void run(uint8_t* ws, const SubDesc* sd, int b, const
 
 }  // namespace
 
-template <bool GRAD>
+template <bool GRAD, bool LONG>
 __global__ __launch_bounds__(ST) __attribute__((amdgpu_waves_per_eu(4))) void k_small(uint8_t* ws, const SubDesc* subs, const int32_t* list, SmallArgs A,
                                               Partials part)
 {
-    extern __shared__ float2 dyn[];
+    extern __shared__ __align__(16) float2 dyn[];
     __shared__ SmallShared S;
     const int b = list[blockIdx.x];
     const SubDesc* sd = subs + b;
     switch (sd->n) {
-    case 13: run<8, 8, GRAD>(ws, sd, b, A, part, dyn, S); break;
-    case 12: run<4, 8, GRAD>(ws, sd, b, A, part, dyn, S); break;
-    case 11: run<4, 4, GRAD>(ws, sd, b, A, part, dyn, S); break;
-    case 10: run<1, 8, GRAD>(ws, sd, b, A, part, dyn, S); break;
-    case 9: run<1, 4, GRAD>(ws, sd, b, A, part, dyn, S); break;
-    case 8: run<1, 2, GRAD>(ws, sd, b, A, part, dyn, S); break;
-    default: run<1, 1, GRAD>(ws, sd, b, A, part, dyn, S); break;
+    case 13: run<8, 8, GRAD, LONG>(ws, sd, b, A, part, dyn, S); break;
+    case 12: run<4, 8, GRAD, LONG>(ws, sd, b, A, part, dyn, S); break;
+    case 11: run<4, 4, GRAD, LONG>(ws, sd, b, A, part, dyn, S); break;
+    case 10: run<1, 8, GRAD, LONG>(ws, sd, b, A, part, dyn, S); break;
+    case 9: run<1, 4, GRAD, LONG>(ws, sd, b, A, part, dyn, S); break;
+    case 8: run<1, 2, GRAD, LONG>(ws, sd, b, A, part, dyn, S); break;
+    default: run<1, 1, GRAD, LONG>(ws, sd, b, A, part, dyn, S); break;
     }
 }
 
@@ -536,7 +564,7 @@ __device__ inline void rx_pair(float2& a, float2& b, float c, float s)
 __global__ __launch_bounds__(THREADS) void k_small_layer(uint8_t* ws, const SubDesc* subs, const int32_t* list,
                                                         SmallArgs A, Partials part)
 {
-    extern __shared__ float2 dyn[];
+    extern __shared__ __align__(16) float2 dyn[];
     __shared__ double red[THREADS / 64];
     __shared__ double s_angle[2];  // gamma, beta
     const uint32_t tid = threadIdx.x;
@@ -646,25 +674,28 @@ __global__ __launch_bounds__(THREADS) void k_small_layer(uint8_t* ws, const SubD
     }
 }
 
-// max_n, max_len: the list's largest qubit count and phase table. The tables
-// of all layers are kept where they fit 4096 entries, else one at a time.
-hipError_t launch_small(uint8_t* ws, const SubDesc* subs, const int32_t* list, int nlist, int max_n, int max_len,
-                        bool grad, SmallArgs A, Partials part, hipStream_t s)
+// max_n, max_len: the list's largest qubit count, and phase tables by waves (small_waves)
+hipError_t launch_small(uint8_t* ws, const SubDesc* subs, const int32_t* list, int nlist, int max_n,
+                        const int (&max_len)[3], bool grad, SmallArgs A, Partials part, hipStream_t s)
 {
     if (nlist <= 0) return hipSuccess;
+    const int len = std::max(max_len[0], std::max(max_len[1], max_len[2]));
     if (grad && A.p == 1) {
         A.lut_at = 1u << (max_n - 1);
-        hipLaunchKernelGGL(k_small_layer, dim3(nlist), dim3(THREADS), (2 * A.lut_at + max_len) * sizeof(float2), s, ws,
+        hipLaunchKernelGGL(k_small_layer, dim3(nlist), dim3(THREADS), (2 * A.lut_at + len) * sizeof(float2), s, ws,
                            subs, list, A, part);
         return hipGetLastError();
     }
     A.lut_at = max_n >= 11 ? 2u << (max_n - 1) : 0u;
-    A.lut_cap = A.p * max_len < 4096 ? A.p * max_len : 4096;
-    if (A.lut_cap < max_len) A.lut_cap = max_len;
-    const size_t lds = (size_t)(A.lut_at + A.lut_cap) * sizeof(float2);
+    bool parts = false;
+    for (int k = 0; k < 3; ++k) parts |= in_parts(max_len[k], A.p, 64 << (k ? k + 1 : 0));
+    size_t lds = std::min(A.p * len, LUT_CAP) * sizeof(float2);
+    if (parts) lds = std::max(lds, A.p * part_count(len) * sizeof(double2));
+    lds += A.lut_at * sizeof(float2);
     const int threads = max_n <= 10 ? 64 : max_n <= 12 ? 256 : ST;
-    if (grad) hipLaunchKernelGGL(k_small<true>, dim3(nlist), dim3(threads), lds, s, ws, subs, list, A, part);
-    else hipLaunchKernelGGL(k_small<false>, dim3(nlist), dim3(threads), lds, s, ws, subs, list, A, part);
+    auto* k = grad ? (parts ? k_small<true, true> : k_small<true, false>)
+                   : (parts ? k_small<false, true> : k_small<false, false>);
+    hipLaunchKernelGGL(k, dim3(nlist), dim3(threads), lds, s, ws, subs, list, A, part);
     return hipGetLastError();
 }
 
