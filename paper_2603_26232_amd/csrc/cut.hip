@@ -11,8 +11,9 @@ namespace pq {
 // (one assignment each read 160 MB of edges at 20,000 edges and 1024 assignments,
 // and two words of the assignment for each edge). It first lays the assignments
 // out in LDS as one byte per vertex, bit g for assignment g: an edge is then two
-// byte reads and an exclusive or. More vertices than LDS_VERTICES are looked up
-// in the packed words instead.
+// byte reads and an exclusive or. More vertices than LDS_VERTICES, or more than a
+// workgroup's edges repay, are looked up in the packed words instead, one or two
+// assignments a workgroup (the rows of more do not fit the L1 cache).
 //
 // G is the largest of 8, 4, 2, 1 that leaves a workgroup per CU. If there are
 // fewer than that even with one each and the edges are many, `splits` workgroups
@@ -29,6 +30,7 @@ namespace pq {
 constexpr int CUT_THREADS = 1024;
 constexpr int CUT_FEW_EDGES = 4096;  // fewer: workgroups of a quarter of the threads
 constexpr int CUT_CUS = 256;
+constexpr int CUT_L1_BYTES = 32 * 1024;
 constexpr int LDS_VERTICES = 60 * 1024;
 constexpr int EDGES_PER_SPLIT = 8192;
 
@@ -85,6 +87,7 @@ __global__ __launch_bounds__(T) void k_maxcut(int32_t nV, int64_t nE, const int3
             }
 #pragma unroll
             for (int k = 0; k < 4; ++k) {
+                if (!LDS && e + k * T >= e1) continue;  // (no words to look up)
                 if ((uint32_t)p[k] >= (uint32_t)nV || (uint32_t)q[k] >= (uint32_t)nV) {
                     bad = true;
                     continue;
@@ -132,47 +135,97 @@ __global__ __launch_bounds__(THREADS) void k_maxcut_check(int32_t nV, int64_t nE
 }
 
 template <int G, int T>
-static void launch_maxcut_gt(int64_t grid, bool lds, int32_t nV, int64_t nE, const int32_t* u, const int32_t* v,
+static void launch_maxcut_gt(int64_t grid, int32_t nV, int64_t nE, const int32_t* u, const int32_t* v,
                              const int32_t* w, int64_t A, const uint32_t* assign, int splits, int64_t* cut,
                              hipStream_t s)
 {
-    auto* k = lds ? (w ? k_maxcut<G, T, true, true> : k_maxcut<G, T, true, false>)
-                  : (w ? k_maxcut<G, T, false, true> : k_maxcut<G, T, false, false>);
-    hipLaunchKernelGGL(k, dim3((unsigned)grid), dim3(T), lds ? (size_t)nV : 0, s, nV, nE, u, v, w, A, assign, splits,
+    auto* k = w ? k_maxcut<G, T, true, true> : k_maxcut<G, T, true, false>;
+    hipLaunchKernelGGL(k, dim3((unsigned)grid), dim3(T), (size_t)nV, s, nV, nE, u, v, w, A, assign, splits,
                        (nE + splits - 1) / splits, cut);
 }
 
 template <int G>
-static void launch_maxcut_g(int64_t grid, bool lds, int32_t nV, int64_t nE, const int32_t* u, const int32_t* v,
+static void launch_maxcut_g(bool few, int64_t grid, int32_t nV, int64_t nE, const int32_t* u, const int32_t* v,
                             const int32_t* w, int64_t A, const uint32_t* assign, int splits, int64_t* cut,
                             hipStream_t s)
 {
-    auto* f = nE < CUT_FEW_EDGES ? launch_maxcut_gt<G, CUT_THREADS / 4> : launch_maxcut_gt<G, CUT_THREADS>;
-    f(grid, lds, nV, nE, u, v, w, A, assign, splits, cut, s);
+    auto* f = few ? launch_maxcut_gt<G, CUT_THREADS / 4> : launch_maxcut_gt<G, CUT_THREADS>;
+    f(grid, nV, nE, u, v, w, A, assign, splits, cut, s);
+}
+
+// in the packed words
+template <int G, int T>
+static void launch_maxcut_words(int64_t grid, int32_t nV, int64_t nE, const int32_t* u, const int32_t* v,
+                                const int32_t* w, int64_t A, const uint32_t* assign, int splits, int64_t* cut,
+                                hipStream_t s)
+{
+    auto* k = w ? k_maxcut<G, T, false, true> : k_maxcut<G, T, false, false>;
+    hipLaunchKernelGGL(k, dim3((unsigned)grid), dim3(T), 0, s, nV, nE, u, v, w, A, assign, splits,
+                       (nE + splits - 1) / splits, cut);
+}
+
+// How a call is split: G assignments a workgroup, `splits` workgroups for the same
+// ones, `few` edges (256 threads), assignments laid out in LDS or not.
+//
+// Laying out takes nV G bits a workgroup and repays from about nV / 2 edges on, with
+// 1024 threads and at most two assignments from nV / 4. In us, LDS / words: 60,000
+// vertices, 5000 assignments, 3000 edges 467 / 41, 21,000 317 / 229, 30,000 333 / 326,
+// 45,000 349 / 481; 1000 assignments, 3000 edges 49 / 10, 12,000 26 / 31, 30,000 33 / 72;
+// 2000 vertices, 5000 assignments, 400 edges 13.5 / 10.2, 1000 13.7 / 12.2, 1500 14.6 /
+// 15.9; 60,000 vertices, one assignment, 300,000 edges (8192 a workgroup) 17.7 / 14.8.
+// Words, one / two / eight assignments a workgroup: 100,000 vertices, 200,000 edges,
+// 5000 assignments 2279 / 2150 / 4133 us; 2,000,000 edges, 1000 assignments 5382 / 4365 /
+// -; 1,000,000 vertices, as many edges, 300 assignments 3386 / 4463 / 7718.
+struct CutShape {
+    int G, splits;
+    bool few, lds;
+    int64_t groups;
+};
+static CutShape cut_shape(int32_t nV, int64_t nE, int64_t A)
+{
+    CutShape c;
+    c.G = 8;
+    while (c.G > 1 && A < (int64_t)c.G * CUT_CUS) c.G >>= 1;
+    c.few = nE < CUT_FEW_EDGES;
+    c.lds = nV <= LDS_VERTICES;
+    auto split = [&]() {
+        c.groups = (A + c.G - 1) / c.G;
+        c.splits = 1;
+        while (c.groups * c.splits * 2 <= CUT_CUS && nE >= (int64_t)c.splits * 2 * EDGES_PER_SPLIT) c.splits *= 2;
+    };
+    split();
+    if (c.lds) c.lds = (!c.few && c.G <= 2 ? 4 : 2) * ((nE + c.splits - 1) / c.splits) >= nV;
+    if (!c.lds) {
+        const bool two = c.G >= 2 && !c.few && nV <= 8 * CUT_L1_BYTES / 2;
+        c.G = two ? 2 : 1;
+        split();
+    }
+    return c;
 }
 
 hipError_t launch_maxcut_eval(int32_t nV, int64_t nE, const int32_t* u, const int32_t* v, const int32_t* w,
                               int64_t A, const uint32_t* assign, int64_t* cut, hipStream_t s)
 {
     if (A <= 0) return hipSuccess;
-    int G = 8;
-    while (G > 1 && A < (int64_t)G * CUT_CUS) G >>= 1;
-    const int64_t groups = (A + G - 1) / G;
-    int splits = 1;
-    while (groups * splits * 2 <= CUT_CUS && nE >= (int64_t)splits * 2 * EDGES_PER_SPLIT) splits *= 2;
-    const bool lds = nV <= LDS_VERTICES;
-    const int64_t grid = groups < 65536 ? groups * splits : 65536;  // splits > 1 only with few groups
-    if (splits > 1)
+    const CutShape c = cut_shape(nV, nE, A);
+    const int64_t grid = c.groups < 65536 ? c.groups * c.splits : 65536;  // splits > 1 only with few groups
+    if (c.splits > 1)
         hipLaunchKernelGGL(k_maxcut_clear, dim3((unsigned)((A + THREADS - 1) / THREADS)), dim3(THREADS), 0, s, A, cut);
-    if (G == 8)
-        launch_maxcut_g<8>(grid, lds, nV, nE, u, v, w, A, assign, splits, cut, s);
-    else if (G == 4)
-        launch_maxcut_g<4>(grid, lds, nV, nE, u, v, w, A, assign, splits, cut, s);
-    else if (G == 2)
-        launch_maxcut_g<2>(grid, lds, nV, nE, u, v, w, A, assign, splits, cut, s);
+    if (!c.lds && c.few)
+        launch_maxcut_words<1, CUT_THREADS / 4>(grid, nV, nE, u, v, w, A, assign, c.splits, cut, s);
+    else if (!c.lds && c.G == 2)
+        launch_maxcut_words<2, CUT_THREADS>(grid, nV, nE, u, v, w, A, assign, c.splits, cut, s);
+    else if (!c.lds)
+        launch_maxcut_words<1, CUT_THREADS>(grid, nV, nE, u, v, w, A, assign, c.splits, cut, s);
+    else if (c.G == 8)
+        launch_maxcut_g<8>(c.few, grid, nV, nE, u, v, w, A, assign, c.splits, cut, s);
+    else if (c.G == 4)
+        launch_maxcut_g<4>(c.few, grid, nV, nE, u, v, w, A, assign, c.splits, cut, s);
+    else if (c.G == 2)
+        launch_maxcut_g<2>(c.few, grid, nV, nE, u, v, w, A, assign, c.splits, cut, s);
     else
-        launch_maxcut_g<1>(grid, lds, nV, nE, u, v, w, A, assign, splits, cut, s);
-    if (splits > 1) {
+        launch_maxcut_g<1>(c.few, grid, nV, nE, u, v, w, A, assign, c.splits, cut, s);
+    if (c.splits > 1) {
         const int64_t blocks = (nE + 8 * THREADS - 1) / (8 * THREADS);
         hipLaunchKernelGGL(k_maxcut_check, dim3((unsigned)(blocks < CUT_CUS ? blocks : CUT_CUS)), dim3(THREADS), 0, s, nV, nE,
                            u, v, A, cut);
