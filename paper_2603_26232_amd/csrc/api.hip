@@ -470,10 +470,16 @@ qaoa_status_t make_plan(int32_t B, const int32_t* nq, const int64_t* eoff, const
             P.classes[ci].tab_bytes += (double)d.ntiles * TILE * d.tabw;
         }
     }
-    for (int b = 0; b < B; ++b)
-        if (P.subs[b].ngroups == 1 && !P.subs[b].skip) P.small.push_back(b);
     // the longest first
-    std::stable_sort(P.small.begin(), P.small.end(), [&](int a, int c) { return P.subs[a].n > P.subs[c].n; });
+    {
+        int at[SMALL_MAX_N + 2] = {};  // at[n]: subgraphs of more than n qubits, then the next slot of n
+        for (const SubDesc& d : P.subs)
+            if (d.ngroups == 1 && !d.skip)
+                for (int n = 0; n < d.n; ++n) ++at[n];
+        P.small.resize(at[0]);
+        for (int b = 0; b < B; ++b)
+            if (P.subs[b].ngroups == 1 && !P.subs[b].skip) P.small[at[P.subs[b].n]++] = b;
+    }
     P.nsmall = (int)P.small.size();
     P.only_small = P.nsmall == B;
     for (int b : P.small) {
