@@ -235,19 +235,21 @@ hipError_t launch_maxcut_eval(int32_t nV, int64_t nE, const int32_t* u, const in
 
 // Adam (Kingma and Ba 2015) in FP64; sign = +1 ascends (the QAOA objective
 // is maximised), -1 descends. The step counter lives in device memory so a
-// captured graph can replay the step. One thread per parameter; up to one
-// workgroup's worth advances the counter itself, more leave it to a second
-// kernel, since every workgroup reads it. (One workgroup for all of the 19,590
-// parameters of the angle predictor took 71 us of FP64 divisions and roots.)
-constexpr int ADAM_THREADS = 256;
+// captured graph can replay the step. One thread per parameter; one workgroup (up to
+// 1024 parameters) advances the counter itself, more leave it to a second kernel,
+// since every workgroup reads it. One workgroup / several and the second kernel, us: 300
+// parameters 4.2 / 6.4, 1024 5.8 / 6.4, 2000 (two a thread) 9.1 / 6.4, the 19,590 of the
+// angle predictor 71 / 6.4.
+constexpr int ADAM_THREADS = 256, ADAM_ALONE = 1024;
 
-__global__ __launch_bounds__(ADAM_THREADS) void k_adam(int32_t count, double* theta, const double* grad, double* m,
-                                                      double* v, int32_t* step, int advance, double lr, double b1,
-                                                      double b2, double eps, double sign)
+template <int T>
+__global__ __launch_bounds__(T) void k_adam(int32_t count, double* theta, const double* grad, double* m, double* v,
+                                           int32_t* step, int advance, double lr, double b1, double b2, double eps,
+                                           double sign)
 {
     const int32_t t = *step + 1;
     const double c1 = 1.0 - pow(b1, (double)t), c2 = 1.0 - pow(b2, (double)t);
-    const int32_t i = blockIdx.x * ADAM_THREADS + threadIdx.x;
+    const int32_t i = blockIdx.x * T + threadIdx.x;
     if (i < count) {
         double th = theta[i], mi = m[i], vi = v[i];
         adam_update(th, mi, vi, grad[i], c1, c2, lr, b1, b2, eps, sign);
@@ -264,9 +266,13 @@ hipError_t launch_adam(int32_t count, double* theta, const double* grad, double*
                        double lr, double b1, double b2, double eps, double sign, hipStream_t s)
 {
     const int blocks = count / ADAM_THREADS + (count % ADAM_THREADS != 0);
-    const int alone = blocks == 1;
-    hipLaunchKernelGGL(k_adam, dim3(blocks), dim3(ADAM_THREADS), 0, s, count, theta, grad, m, v, step, alone, lr, b1,
-                       b2, eps, sign);
+    const int alone = count <= ADAM_ALONE;
+    if (alone && blocks > 1)
+        hipLaunchKernelGGL(k_adam<ADAM_ALONE>, dim3(1), dim3(ADAM_ALONE), 0, s, count, theta, grad, m, v, step, 1, lr,
+                           b1, b2, eps, sign);
+    else
+        hipLaunchKernelGGL(k_adam<ADAM_THREADS>, dim3(blocks), dim3(ADAM_THREADS), 0, s, count, theta, grad, m, v, step,
+                           alone, lr, b1, b2, eps, sign);
     const hipError_t e = hipGetLastError();
     return e != hipSuccess || alone ? e : launch_step_advance(step, 1, s);
 }
