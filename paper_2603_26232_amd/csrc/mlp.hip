@@ -22,7 +22,8 @@ __host__ __device__ inline int64_t mlp_off_b3(const MlpDims& d) { return mlp_off
 __host__ __device__ int64_t mlp_nparams(const MlpDims& d) { return mlp_off_b3(d) + d.out; }
 int64_t mlp_num_params(const MlpDims& d) { return mlp_nparams(d); }
 
-// Forward and error kernels: a workgroup takes as many samples as its 1024
+// Forward and error kernels of many samples (of few, k_mlp_fwd_sample and
+// k_mlp_delta_sample below): a workgroup takes as many samples as its 1024
 // threads can share (one per thread and unit), so every weight, read as FP64 and
 // rounded to FP32 once per workgroup into LDS, serves all of them, along rows.
 // (One workgroup per sample, each lane reading its own row, touched 64 cache
@@ -207,6 +208,84 @@ __global__ __launch_bounds__(MLP_THREADS) void k_mlp_delta(int B, MlpDims d, int
     });
 }
 
+// The same, a workgroup per sample and a thread per unit, for few samples: nothing is
+// staged, so the first products need not wait for a whole layer's weights. Every output
+// is the same chain of fused multiply-adds as above, bit for bit. Together / a sample
+// each, us, forward: 18-128-6 (both hidden layers of 128) 1 sample 13.0 / 7.8, 256 13.5 /
+// 8.6, 384 13.5 / 11.9, 64-128-64 384 15.2 / 16.3, 64-256-64 256 28.5 / 26.1, 384 28.7 /
+// 43.4, 18-64-6 1024 10.7 / 7.9, 2048 10.8 / 12.6, 5-32-2
+// 2048 9.1 / 6.1, 4096 9.2 / 9.8, 4-16-2 4096 8.4 / 5.9; backward: 64-256-64 1 31.4 / 20.2, 512
+// 43.4 / 37.2, 768 51.9 / 54.5, 18-200-6 512 30.9 / 27.1, 768 36.1 / 39.2, 18-64-6 2048
+// 41.3 / 40.1, 4096 74.8 / 80.4.
+inline bool mlp_fwd_each(int B, const MlpDims& d)
+{
+    return B <= (d.H > 64 ? 256 : d.H > 32 ? 1024 : d.H > 24 ? 3072 : 4096);
+}
+inline bool mlp_delta_each(int B, const MlpDims& d) { return B <= (d.H > 64 ? 512 : 2048); }
+
+__global__ __launch_bounds__(MLP_MAX_H) void k_mlp_fwd_sample(MlpDims d, const double* P, const float* X, float* Y,
+                                                             float* act)
+{
+    __shared__ float xs[MLP_MAX_IN], h1[MLP_MAX_H], h2[MLP_MAX_H];
+    const int s = blockIdx.x, i = threadIdx.x;
+    // unit i of a layer of N over K inputs
+    auto unit = [&](int K, const double* W, const double* b, const float* src) {
+        float a = (float)b[i];
+        for (int j = 0; j < K; ++j) a = fmaf((float)W[(size_t)i * K + j], src[j], a);
+        return a;
+    };
+    if (i < d.in) xs[i] = X[(size_t)s * d.in + i];
+    __syncthreads();
+    if (i < d.H) {
+        const float a = unit(d.in, P, P + mlp_off_b1(d), xs);
+        h1[i] = a > 0.f ? a : 0.f;
+        act[(size_t)s * 2 * d.H + i] = h1[i];
+    }
+    __syncthreads();
+    if (i < d.H) {
+        const float a = unit(d.H, P + mlp_off_W2(d), P + mlp_off_b2(d), h1);
+        h2[i] = a > 0.f ? a : 0.f;
+        act[(size_t)s * 2 * d.H + d.H + i] = h2[i];
+    }
+    __syncthreads();
+    if (i < d.out) Y[(size_t)s * d.out + i] = unit(d.H, P + mlp_off_W3(d), P + mlp_off_b3(d), h2);
+}
+
+__global__ __launch_bounds__(MLP_MAX_H) void k_mlp_delta_sample(int B, MlpDims d, const double* P, const float* Y,
+                                                               const float* act, const float* T, float* delta,
+                                                               double* sq)
+{
+    __shared__ float d3[MLP_MAX_OUT], d2[MLP_MAX_H], r[MLP_MAX_OUT];
+    const int s = blockIdx.x, i = threadIdx.x;
+    const double *W2 = P + mlp_off_W2(d), *W3 = P + mlp_off_W3(d);
+    const float scale = 1.0f / ((float)B * (float)d.out);
+    const float *a1 = act + (size_t)s * 2 * d.H, *a2 = a1 + d.H;
+    float* dl = delta + (size_t)s * (2 * d.H + d.out);
+    if (i < d.out) {
+        r[i] = Y[(size_t)s * d.out + i] - T[(size_t)s * d.out + i];
+        d3[i] = 2.f * r[i] * scale;
+        dl[2 * d.H + i] = d3[i];
+    }
+    __syncthreads();
+    if (i < d.H) {
+        float a = 0.f;
+        for (int o = 0; o < d.out; ++o) a = fmaf((float)W3[(size_t)o * d.H + i], d3[o], a);
+        d2[i] = a2[i] > 0.f ? a : 0.f;
+        dl[d.H + i] = d2[i];
+    }
+    __syncthreads();
+    if (i < d.H) {
+        float a = 0.f;
+        for (int k = 0; k < d.H; ++k) a = fmaf((float)W2[(size_t)k * d.H + i], d2[k], a);
+        dl[i] = a1[i] > 0.f ? a : 0.f;
+    }
+    if (i == 0) {
+        double a = 0.0;
+        for (int o = 0; o < d.out; ++o) a += (double)r[o] * (double)r[o];
+        sq[s] = a;
+    }
+}
+
 // Weight gradients and the loss. A wave owns a 4 x 8 tile of one layer's (error
 // row, input column) sums, the bias being one more column whose input is 1. Its
 // lanes take every 64th sample (products rounded to FP32, summed in FP64), three
@@ -371,6 +450,11 @@ hipError_t launch_keep_better(int B, int p, const double* E_alt, const double* t
 hipError_t launch_mlp_forward(int B, MlpDims d, const double* P, const float* X, float* Y, float* act, hipStream_t s)
 {
     const int S = mlp_samples(d.H), big = d.H > d.out ? d.H : d.out;
+    if (mlp_fwd_each(B, d)) {
+        const int units = d.in > big ? d.in : big;
+        hipLaunchKernelGGL(k_mlp_fwd_sample, dim3(B), dim3((units + 63) / 64 * 64), 0, s, d, P, X, Y, act);
+        return hipGetLastError();
+    }
     const size_t lds = sizeof(float) * ((size_t)big * mlp_row(big) +
                                         (size_t)S * (mlp_pad(d.in) + 2 * mlp_pad(d.H)));
     hipLaunchKernelGGL(k_mlp_fwd, dim3((B + S - 1) / S), dim3(MLP_THREADS), lds, s, B, d, S, P, X, Y, act);
@@ -385,7 +469,13 @@ hipError_t launch_mlp_backward(int B, MlpDims d, const double* P, const float* X
     sq = (double*)(((uintptr_t)sq + 7) & ~(uintptr_t)7);
     const int S = mlp_samples(d.H);
     const size_t lds = sizeof(float) * ((size_t)d.H * mlp_row(d.H) + (size_t)S * (mlp_pad(d.out) + mlp_pad(d.H)));
-    hipLaunchKernelGGL(k_mlp_delta, dim3((B + S - 1) / S), dim3(MLP_THREADS), lds, s, B, d, S, P, Y, act, T, delta, sq);
+    if (mlp_delta_each(B, d)) {
+        const int units = d.H > d.out ? d.H : d.out;
+        hipLaunchKernelGGL(k_mlp_delta_sample, dim3(B), dim3((units + 63) / 64 * 64), 0, s, B, d, P, Y, act, T, delta, sq);
+    } else {
+        hipLaunchKernelGGL(k_mlp_delta, dim3((B + S - 1) / S), dim3(MLP_THREADS), lds, s, B, d, S, P, Y, act, T, delta,
+                           sq);
+    }
     const int tiles = wg_tiles(d.H, d.in + 1) + wg_tiles(d.H, d.H + 1) + wg_tiles(d.out, d.H + 1);
     hipLaunchKernelGGL(k_mlp_wgrad, dim3((tiles + WG_WAVES - 1) / WG_WAVES + 1), dim3(64 * WG_WAVES), 0, s, B, d, X, act, delta, sq, G, loss);
     return hipGetLastError();
