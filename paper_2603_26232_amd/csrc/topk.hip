@@ -38,8 +38,11 @@
 // A selection counts keys in 256 bins over the 8 octaves of probability below
 // the largest one (1/32 octave each: most keys of a state spread over them, so
 // the LDS atomics do not meet in one bin), then over the bin that holds the k-th,
-// until a bin boundary is the answer; if fewer than k keys are in that window, it
-// starts over the whole range.
+// until a bin boundary is the answer or the bin holds at most 256 keys, which are
+// then ranked against each other (equal probabilities differ in the string only, six
+// more rounds of bins: four 20-qubit states of graphs with three edges, k = 1, 24 / 15
+// us); if fewer than k keys are in the window, it starts over the
+// whole range.
 // Canonical mode takes only z with bit 0 clear (pi(z) = pi(~z)).
 //
 // Bound: the 8 bytes per stored amplitude that stage 1 reads. Measured on 8704
@@ -126,8 +129,9 @@ struct SelState {
     int hist[256];
     int wsum[4];
     uint32_t wmax[16];
-    int bin, excl, h, total, count;
+    int bin, excl, h, total, count, few;
     uint64_t out[MAX_K];
+    uint64_t cand[256], answer;  // keys of the k-th one's bin
 };
 
 __device__ inline uint32_t wave_max(uint32_t x)
@@ -174,6 +178,7 @@ __device__ uint64_t select_smallest(SelState& S, const Each& each, int q, uint32
     for (bool first = true;; first = false) {
         __syncthreads();  // the last round's results have been read
         if (t < 256) S.hist[t] = 0;
+        if (t == 0) S.few = 0;
         __syncthreads();
         each([&](uint64_t key) {
             if (key >= lo && key <= hi) atomicAdd(&S.hist[(int)((hi - key) >> shift)], 1);
@@ -210,8 +215,23 @@ __device__ uint64_t select_smallest(SelState& S, const Each& each, int q, uint32
         const int excl = S.excl;
         const uint64_t top_of = hi - (b << shift);
         const uint64_t low_of = top_of - lo >= (1ull << shift) ? top_of - (1ull << shift) + 1ull : lo;
-        if (excl + S.h == q) return low_of;
+        const int held = S.h;
+        if (excl + held == q) return low_of;
         q -= excl;
+        if (held <= 256) {
+            each([&](uint64_t key) {
+                if (key >= low_of && key <= top_of) S.cand[atomicAdd(&S.few, 1)] = key;
+            });
+            __syncthreads();
+            if (t < held) {
+                const uint64_t mine = S.cand[t];
+                int above = 0;
+                for (int i = 0; i < held; ++i) above += S.cand[i] > mine;
+                if (above == q - 1) S.answer = mine;
+            }
+            __syncthreads();
+            return S.answer;
+        }
         hi = top_of;
         lo = low_of;
         shift = shift >= 8 ? shift - 8 : 0;
