@@ -375,11 +375,13 @@ qaoa_status_t qaoa_state_offset(qaoa_batch_t h, int32_t b, size_t* out_offset);
  * 0..10 and the top qubit, 4096-amplitude tiles) and strided groups of at most
  * 8 of the qubits 11..n-2, one HBM pass per group and layer (Sec. 2.2's mixer
  * is a product over qubits, so any grouping gives the same state). Without a
- * split named here, batches large enough take 16384-amplitude tiles (13 low
- * qubits and the top one, strided groups of at most 12) for subgraphs where
- * that saves a group: 21..26, 29 and 30 qubits, in gradient batches up to 25
- * qubits and 29, 30, and only where the weight sum is at most 1.5 n and
- * max_p is more than 1.
+ * split named here, subgraphs of 21..26, 29 and 30 qubits, where that saves a
+ * group, take 16384-amplitude tiles (13 low qubits and the top one, strided
+ * groups of at most 12) if the batch has at least 128 of those tiles (all but a
+ * batch whose only such subgraph has 21 qubits) and no matrix-core mixer mode.
+ * In batches with QAOA_FLAG_GRADIENT this holds up to 25 qubits and for 29 and
+ * 30, where max_p is more than 1 and the subgraph's weight sum at most 1.5 n.
+ * The two tile sizes give the same results to rounding, not to the bit.
  * sizes[0..count) are the strided group sizes in qubit order for subgraphs
  * with n qubits (each 1..8, at most 3 groups, adding up to n - 12); count = 0
  * restores the default (fewest groups, sizes as even as possible). Batches
@@ -387,6 +389,11 @@ qaoa_status_t qaoa_state_offset(qaoa_batch_t h, int32_t b, size_t* out_offset);
  * 14..30, count > 3 or a size outside 1..8; QAOA_ERR_INVALID_ARG if the sizes
  * do not add up to n - 12. */
 qaoa_status_t qaoa_tune_group_split(int32_t n, int32_t count, const int32_t* sizes);
+
+/* The same for the subgraphs with n qubits that run on 4096-amplitude tiles
+ * without a split named by qaoa_tune_group_split, leaving the choice of the
+ * tiles to the library. Arguments, default and errors as there. */
+qaoa_status_t qaoa_tune_narrow_split(int32_t n, int32_t count, const int32_t* sizes);
 
 /* Text of a status code (static storage). */
 const char* qaoa_status_string(qaoa_status_t s);

@@ -88,6 +88,7 @@ def lib() -> ct.CDLL:
             "qaoa_profile_read": [ct.c_char_p, _vp, _vp, _vp],
             "qaoa_profile_select": [ct.c_char_p],
             "qaoa_tune_group_split": [_i32, _i32, _vp],
+            "qaoa_tune_narrow_split": [_i32, _i32, _vp],
         }
         for name, args in sig.items():
             if not hasattr(L, name):
@@ -265,11 +266,21 @@ def qaoa_profile_enable(on: int) -> None:
     _call("qaoa_profile_enable", int(on))
 
 
+def _tune_split(fn: str, n: int, sizes) -> None:
+    arr = np.ascontiguousarray(sizes if sizes else [0], dtype=np.int32)
+    _call(fn, int(n), len(sizes) if sizes else 0, arr.ctypes.data_as(ct.c_void_p))
+
+
 def qaoa_tune_group_split(n: int, sizes) -> None:
     """Strided group sizes for n-qubit subgraphs of batches created from now
-    on (empty / None = default split)."""
-    arr = np.ascontiguousarray(sizes if sizes else [0], dtype=np.int32)
-    _call("qaoa_tune_group_split", int(n), len(sizes) if sizes else 0, arr.ctypes.data_as(ct.c_void_p))
+    on (empty / None = default split); a named split also keeps them on
+    4096-amplitude tiles."""
+    _tune_split("qaoa_tune_group_split", n, sizes)
+
+
+def qaoa_tune_narrow_split(n: int, sizes) -> None:
+    """The same for those that run on 4096-amplitude tiles anyway."""
+    _tune_split("qaoa_tune_narrow_split", n, sizes)
 
 
 def qaoa_profile_select(kernel) -> None:

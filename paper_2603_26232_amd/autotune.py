@@ -10,10 +10,18 @@ bits are real qubits and how long the contiguous rows of a strided tile are
 candidate splits (fewest groups, every ordered composition of n - 12 into
 parts of at most 8) on a batch of random graphs with n qubits, one optimiser
 evaluation (forward pass + adjoint sweep) or one forward evaluation per
-repetition, and keeps the fastest. A named split also keeps a subgraph on
-4096-amplitude tiles; the split None is the library's own choice, which takes
-wider tiles where those save a group, and is timed beside the named ones. The
-table is saved as JSON and applied with `apply()` before batches are created.
+repetition, and keeps the fastest.
+
+The library takes wider tiles for some subgraphs of a size and 4096-amplitude ones
+for others (dense gradients), and a split named for the size keeps them all on
+4096-amplitude tiles. So each size is timed on dense graphs (density 0.15 or, where
+that leaves the weight sum at 1.5 n or below, a little above it), for the split of
+4096-amplitude tiles, and on sparse ones (at most 1.5 n edges) with that split named
+and without. Where the library's own choice is the faster of the two, or is not timed
+by this kind of evaluation (gradients of 26 qubits have 4096-amplitude tiles, their
+forward evaluations wide ones), the table holds no named split ("split": null), and the
+tuned one applies to 4096-amplitude tiles alone ("split_4096_tiles"). The table is
+saved as JSON and applied with `apply()` before batches are created.
 
 Run: python -m paper_2603_26232_amd.autotune --n 21 22 ... --out FILE
 """
@@ -54,17 +62,28 @@ def default_split(n: int):
     return [R // G1 + (1 if g < R % G1 else 0) for g in range(G1)]
 
 
-def time_split(n, split, p=3, gradient=True, amps=1 << 24, reps=5, seed=0):
-    """Device milliseconds per evaluation and per 2^20 amplitudes."""
-    B = max(1, amps >> n)
+def _graphs(n, B, dense, seed):
     edges = []
     for b in range(B):
-        g = synth.erdos_renyi(n, 0.1, seed + b)
-        edges.append((g.u, g.v, g.w))
+        g = synth.erdos_renyi(n, 0.15, seed + b)
+        limit = 3 * n // 2
+        if dense and g.num_edges <= limit:
+            g = synth.erdos_renyi(n, 0.2, seed + b)
+        m = max(limit + 1, g.num_edges) if dense else limit
+        pick = np.sort(np.random.default_rng(seed + b).permutation(g.num_edges)[:m])
+        edges.append((g.u[pick], g.v[pick], g.w[pick]))
+        assert (g.w[pick].sum() > limit) == dense
+    return edges
+
+
+def time_split(n, split, p=3, gradient=True, amps=1 << 24, reps=5, seed=0, dense=False):
+    """Device milliseconds per evaluation and per 2^20 amplitudes (the least of
+    three times `reps` evaluations)."""
+    B = max(1, amps >> n)
     gamma, beta = synth.uniform_angles(seed + 999, p, batch=B)
     _abi.qaoa_tune_group_split(n, split)
     try:
-        bt = QaoaBatch([n] * B, edges, max_p=p, max_k=8, gradient=gradient)
+        bt = QaoaBatch([n] * B, _graphs(n, B, dense, seed), max_p=p, max_k=8, gradient=gradient)
     finally:
         _abi.qaoa_tune_group_split(n, None)
     g = torch.as_tensor(gamma, device="cuda")
@@ -79,40 +98,51 @@ def time_split(n, split, p=3, gradient=True, amps=1 << 24, reps=5, seed=0):
 
     once()
     torch.cuda.synchronize()
-    ev = [torch.cuda.Event(enable_timing=True) for _ in range(2)]
-    ev[0].record()
-    for _ in range(reps):
-        once()
-    ev[1].record()
-    torch.cuda.synchronize()
-    ms = ev[0].elapsed_time(ev[1]) / reps
+    ms = []
+    for _ in range(3):
+        ev = [torch.cuda.Event(enable_timing=True) for _ in range(2)]
+        ev[0].record()
+        for _ in range(reps):
+            once()
+        ev[1].record()
+        torch.cuda.synchronize()
+        ms.append(ev[0].elapsed_time(ev[1]) / reps)
     bt.close()
-    return ms, ms / (B * (1 << n) / (1 << 20))
+    return min(ms), min(ms) / (B * (1 << n) / (1 << 20))
 
 
 def tune(ns, p=3, gradient=True, log=print):
+    reset(ns)
     table = {}
     for n in ns:
         cands = candidates(n)
         if len(cands) <= 1:
             continue
-        res = []
-        for sp in cands + [None]:
-            ms, per = time_split(n, sp, p=p, gradient=gradient)
-            res.append((per, sp, ms))
-            log(f"autotune: n={n} split {sp}: {ms:.3f} ms per evaluation ({per:.4f} ms per 2^20 amplitudes)")
-        res.sort(key=lambda r: r[0])
+
+        def timed(sp, dense):
+            ms, per = time_split(n, sp, p=p, gradient=gradient, dense=dense)
+            kind = "dense" if dense else "sparse"
+            log(f"autotune: n={n} split {sp}, {kind}: {ms:.3f} ms per evaluation ({per:.4f} ms per 2^20 amplitudes)")
+            return {"split": sp, "graphs": kind, "ms_per_mamp": per}
+
+        res = sorted((timed(sp, True) for sp in cands), key=lambda r: r["ms_per_mamp"])
         best = res[0]
-        dflt = next(r for r in res if r[1] == default_split(n))
-        table[str(n)] = {"split": best[1], "ms_per_mamp": best[0], "default_split": dflt[1],
-                         "default_ms_per_mamp": dflt[0],
-                         "all": [{"split": r[1], "ms_per_mamp": r[0]} for r in res]}
-        log(f"autotune: n={n}: best {best[1]} ({best[0]:.4f}), default {dflt[1]} ({dflt[0]:.4f})")
+        dflt = next(r for r in res if r["split"] == default_split(n))
+        named, own = timed(best["split"], False), timed(None, False)
+        wide = n in (21, 22, 23, 24, 25, 26, 29, 30)  # of some evaluations
+        keep = not wide or (own["ms_per_mamp"] > named["ms_per_mamp"] and not (gradient and n == 26))
+        table[str(n)] = {"split": best["split"] if keep else None, "split_4096_tiles": best["split"],
+                         "ms_per_mamp": (named if keep else own)["ms_per_mamp"],
+                         "ms_per_mamp_4096_tiles": best["ms_per_mamp"], "default_split": dflt["split"],
+                         "default_ms_per_mamp": dflt["ms_per_mamp"], "all": res + [named, own]}
+        log(f"autotune: n={n}: 4096-amplitude tiles {best['split']} ({best['ms_per_mamp']:.4f}), default {dflt['split']} "
+            f"({dflt['ms_per_mamp']:.4f}); sparse {named['ms_per_mamp']:.4f}, library's choice {own['ms_per_mamp']:.4f}")
     return table
 
 
 def apply(path: str = DEFAULT_TABLE) -> dict:
-    """Load a tuning table and set it in the library; returns {n: split}."""
+    """Load a tuning table and set it in the library; returns {n: named split}
+    (None: the library's choice of tiles)."""
     if not os.path.exists(path):
         return {}
     with open(path) as f:
@@ -120,6 +150,7 @@ def apply(path: str = DEFAULT_TABLE) -> dict:
     out = {}
     for n, e in data.get("entries", {}).items():
         _abi.qaoa_tune_group_split(int(n), e["split"])
+        _abi.qaoa_tune_narrow_split(int(n), e.get("split_4096_tiles"))
         out[int(n)] = e["split"]
     return out
 
@@ -127,6 +158,7 @@ def apply(path: str = DEFAULT_TABLE) -> dict:
 def reset(ns=range(14, 31)):
     for n in ns:
         _abi.qaoa_tune_group_split(n, None)
+        _abi.qaoa_tune_narrow_split(n, None)
 
 
 def main():

@@ -287,12 +287,18 @@ int groups_for(int n)
 // Tuned sizes of the strided qubit groups per qubit count (empty = even
 // split into the fewest groups); read when a batch is planned.
 std::mutex g_split_mu;
-std::vector<int> g_split[QAOA_MAX_QUBITS + 1];
+std::vector<int> g_split[QAOA_MAX_QUBITS + 1];   // named: it also keeps the 4096-amplitude tiles
+std::vector<int> g_narrow[QAOA_MAX_QUBITS + 1];  // of subgraphs that have those anyway
 
 std::vector<int> tuned_split(int n)
 {
     std::lock_guard<std::mutex> lk(g_split_mu);
     return g_split[n];
+}
+std::vector<int> narrow_split(int n)
+{
+    std::lock_guard<std::mutex> lk(g_split_mu);
+    return g_split[n].empty() ? g_narrow[n] : g_split[n];
 }
 
 std::vector<int> even_split(int rest, int parts)
@@ -401,7 +407,7 @@ qaoa_status_t make_plan(int32_t B, const int32_t* nq, const int64_t* eoff, const
             d.gsize[0] = d.n <= SMALL_MAX_N ? d.n : d.wide ? WIDE_BITS : TILE_BITS;
             d.ngroups = 1;
             if (d.n <= SMALL_MAX_N) continue;
-            std::vector<int> split = tuned_split(d.n);
+            std::vector<int> split = narrow_split(d.n);
             if (d.wide) split = even_split(d.n - WIDE_BITS, wide_groups_for(d.n) - 1);
             else if (split.empty()) split = even_split(d.n - TILE_BITS, groups_for(d.n) - 1);
             int q = d.gsize[0] - 1;
@@ -644,7 +650,7 @@ double small_bytes(const Plan& P, int p, bool grad)
 
 }  // namespace
 
-extern "C" qaoa_status_t qaoa_tune_group_split(int32_t n, int32_t count, const int32_t* sizes)
+static qaoa_status_t set_split(std::vector<int>* table, int32_t n, int32_t count, const int32_t* sizes)
 {
     if (n <= SMALL_MAX_N || n > QAOA_MAX_QUBITS)
         return fail(QAOA_ERR_OUT_OF_RANGE, "n = %d outside %d..%d", n, SMALL_MAX_N + 1, QAOA_MAX_QUBITS);
@@ -662,8 +668,18 @@ extern "C" qaoa_status_t qaoa_tune_group_split(int32_t n, int32_t count, const i
     if (count > 0 && sum != n - TILE_BITS)
         return fail(QAOA_ERR_INVALID_ARG, "group sizes add up to %d, not n - %d = %d", sum, TILE_BITS, n - TILE_BITS);
     std::lock_guard<std::mutex> lk(g_split_mu);
-    g_split[n] = v;
+    table[n] = v;
     return ok();
+}
+
+extern "C" qaoa_status_t qaoa_tune_group_split(int32_t n, int32_t count, const int32_t* sizes)
+{
+    return set_split(g_split, n, count, sizes);
+}
+
+extern "C" qaoa_status_t qaoa_tune_narrow_split(int32_t n, int32_t count, const int32_t* sizes)
+{
+    return set_split(g_narrow, n, count, sizes);
 }
 
 // ---------------------------------------------------------------------------
