@@ -1,4 +1,5 @@
-// Rotations and inner products across the lanes of a wave, on DPP operands.
+// Rotations, inner products, sums and extremes across the lanes of a wave, on DPP
+// operands.
 //
 // The lanes of a row of 16 hold four index bits; the lane number is the XOR of
 // the masks 1, 2, 7, 15 of the bits that are set, so that a bit's partner lane
@@ -13,6 +14,11 @@
 #include "common.h"
 
 namespace pq {
+
+__device__ inline float2 cmul(float2 a, float2 b)
+{
+    return make_float2(a.x * b.x - a.y * b.y, a.x * b.y + a.y * b.x);
+}
 
 __host__ __device__ constexpr uint32_t row_lanes(uint32_t bits)
 {
@@ -166,6 +172,30 @@ __device__ inline double wave_total(double x)
     x += across<2>(x);
     x += across<3>(x);
     return halves_sum<32>(halves_sum<16>(x));
+}
+
+// the wave's largest / smallest value, by lane permutations that need no LDS
+template <typename F>
+__device__ inline uint32_t wave_fold(uint32_t x, F pick)
+{
+    x = pick(x, __float_as_uint(across<0>(__uint_as_float(x))));
+    x = pick(x, __float_as_uint(across<1>(__uint_as_float(x))));
+    x = pick(x, __float_as_uint(across<2>(__uint_as_float(x))));
+    x = pick(x, __float_as_uint(across<3>(__uint_as_float(x))));
+    float a = __uint_as_float(x), c = a;
+    swap_halves<16>(a, c);
+    x = pick(__float_as_uint(a), __float_as_uint(c));
+    a = c = __uint_as_float(x);
+    swap_halves<32>(a, c);
+    return pick(__float_as_uint(a), __float_as_uint(c));
+}
+__device__ inline uint32_t wave_max(uint32_t x)
+{
+    return wave_fold(x, [](uint32_t a, uint32_t c) { return a > c ? a : c; });
+}
+__device__ inline uint32_t wave_min(uint32_t x)
+{
+    return wave_fold(x, [](uint32_t a, uint32_t c) { return a < c ? a : c; });
 }
 
 }  // namespace pq

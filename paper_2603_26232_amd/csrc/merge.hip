@@ -124,29 +124,6 @@ __device__ inline int32_t wave_sum(int32_t x)
     for (int o = 32; o > 0; o >>= 1) x += __shfl_xor(x, o, 64);
     return x;
 }
-// the wave's largest / smallest value, by lane permutations that need no LDS
-template <typename F>
-__device__ inline uint32_t wave_fold(uint32_t x, F pick)
-{
-    x = pick(x, __float_as_uint(across<0>(__uint_as_float(x))));
-    x = pick(x, __float_as_uint(across<1>(__uint_as_float(x))));
-    x = pick(x, __float_as_uint(across<2>(__uint_as_float(x))));
-    x = pick(x, __float_as_uint(across<3>(__uint_as_float(x))));
-    float a = __uint_as_float(x), c = a;
-    swap_halves<16>(a, c);
-    x = pick(__float_as_uint(a), __float_as_uint(c));
-    a = c = __uint_as_float(x);
-    swap_halves<32>(a, c);
-    return pick(__float_as_uint(a), __float_as_uint(c));
-}
-__device__ inline uint32_t wave_max(uint32_t x)
-{
-    return wave_fold(x, [](uint32_t a, uint32_t c) { return a > c ? a : c; });
-}
-__device__ inline uint32_t wave_min(uint32_t x)
-{
-    return wave_fold(x, [](uint32_t a, uint32_t c) { return a < c ? a : c; });
-}
 // exclusive prefix of the per-wave values slots[0..NW) at wave wv, and their
 // total (lanes 0..NW-1 read one slot each)
 template <int NW>

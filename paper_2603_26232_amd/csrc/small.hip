@@ -170,11 +170,6 @@ __device__ inline void rotate(float2 (&v)[R], float t, int nl)
     if constexpr (K > 2) rx_reg<2>(v, t);
 }
 
-__device__ inline float2 cmulf(float2 a, float2 b)
-{
-    return make_float2(a.x * b.x - a.y * b.y, a.x * b.y + a.y * b.x);
-}
-
 // One bit of the adjoint sweep: the beta term on states scaled by |f|^-done,
 // w = |f|^(2 done), then the inverse rotation of both.
 struct Back {
@@ -345,7 +340,7 @@ __device__ __forceinline__ void run(uint8_t* ws, const SubDesc* sd, int b, const
         __syncthreads();
         if (!LONG || !parts) {
 #pragma unroll 1
-            for (int i = (int)tid; i < p * len; i += T) lut[i] = cmulf(lut[i], S.F[i / len]);
+            for (int i = (int)tid; i < p * len; i += T) lut[i] = cmul(lut[i], S.F[i / len]);
             __syncthreads();
         }
         // phase at cut value c with f^n: L = layer l's table, P its parts
@@ -367,7 +362,7 @@ __device__ __forceinline__ void run(uint8_t* ws, const SubDesc* sd, int b, const
             for (int r = 0; r < R; ++r) {
                 const float2 f = phase_of(L, P, F, cut(r, alt));
                 if (l == 0) v[r] = index(r, 0) < dim ? make_float2(amp * f.x, amp * f.y) : make_float2(0.f, 0.f);
-                else v[r] = cmulf(v[r], f);
+                else v[r] = cmul(v[r], f);
             }
             rotate(v, t, nl);
             if constexpr (W > 1) {
@@ -470,8 +465,8 @@ __device__ __forceinline__ void run(uint8_t* ws, const SubDesc* sd, int b, const
                     for (int r = 0; r < R; ++r) {  // conj(f^n) undoes f^n and the phase of this layer
                         float2 f = phase_of(L, P, F, cut(r, alt));
                         f.y = -f.y;
-                        v[r] = cmulf(v[r], f);
-                        la[r] = cmulf(la[r], f);
+                        v[r] = cmul(v[r], f);
+                        la[r] = cmul(la[r], f);
                     }
                 }
             }
@@ -597,7 +592,7 @@ __global__ __launch_bounds__(THREADS) void k_small_layer(uint8_t* ws, const SubD
         const float2 cs = make_float2((float)co, (float)sn);
         for (uint32_t z = tid; z < dim; z += THREADS) ps[z] = make_float2(a0, 0.f);
         __syncthreads();
-        for (uint32_t z = tid; z < dim; z += THREADS) ps[z] = cmulf(ps[z], lut[cut(z)]);
+        for (uint32_t z = tid; z < dim; z += THREADS) ps[z] = cmul(ps[z], lut[cut(z)]);
         for (int j = 0; j < n - 1; ++j) {
             __syncthreads();
             for (uint32_t i = tid; i < half; i += THREADS) {
@@ -607,7 +602,7 @@ __global__ __launch_bounds__(THREADS) void k_small_layer(uint8_t* ws, const SubD
         }
         __syncthreads();
         for (uint32_t i = tid; i < half; i += THREADS) rx_pair(ps[i], ps[i ^ comp], cs.x, cs.y);
-        if (dim == 1 && tid == 0) ps[0] = cmulf(ps[0], make_float2(cs.x, -cs.y));
+        if (dim == 1 && tid == 0) ps[0] = cmul(ps[0], make_float2(cs.x, -cs.y));
         __syncthreads();
         double e = 0.0;
         for (uint32_t z = tid; z < dim; z += THREADS) {
@@ -625,8 +620,8 @@ __global__ __launch_bounds__(THREADS) void k_small_layer(uint8_t* ws, const SubD
             if (j == n - 1 && dim == 1) {
                 if (tid == 0) {
                     a += la[0].x * ps[0].y - la[0].y * ps[0].x;
-                    ps[0] = cmulf(ps[0], make_float2(cs.x, cs.y));
-                    la[0] = cmulf(la[0], make_float2(cs.x, cs.y));
+                    ps[0] = cmul(ps[0], make_float2(cs.x, cs.y));
+                    la[0] = cmul(la[0], make_float2(cs.x, cs.y));
                 }
             } else {
                 for (uint32_t i = tid; i < half; i += THREADS) {

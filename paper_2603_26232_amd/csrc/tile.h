@@ -80,11 +80,6 @@ __device__ inline void rx_tan(float2& a, float2& b, float t)
     b = nb;
 }
 
-__device__ inline float2 cmul(float2 a, float2 b)
-{
-    return make_float2(a.x * b.x - a.y * b.y, a.x * b.y + a.y * b.x);
-}
-
 // Per-layer rotation parameters (built in FP64 by the angle-prep kernel):
 // e^{-i beta X} = f (I - i t X) X^flip per qubit.
 struct RxC {

@@ -137,27 +137,6 @@ struct SelState {
     uint64_t cand[256], answer;  // keys of the k-th one's bin
 };
 
-__device__ inline uint32_t wave_max(uint32_t x)
-{
-    auto take = [&](float y) {
-        const uint32_t u = __float_as_uint(y);
-        x = u > x ? u : x;
-    };
-    take(across<0>(__uint_as_float(x)));
-    take(across<1>(__uint_as_float(x)));
-    take(across<2>(__uint_as_float(x)));
-    take(across<3>(__uint_as_float(x)));
-    float a = __uint_as_float(x), b = a;
-    swap_halves<16>(a, b);
-    take(a);
-    take(b);
-    a = b = __uint_as_float(x);
-    swap_halves<32>(a, b);
-    take(a);
-    take(b);
-    return x;
-}
-
 // the largest value over the block's waves
 __device__ inline uint32_t block_max(SelState& S, uint32_t x)
 {
