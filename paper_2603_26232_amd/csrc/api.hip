@@ -313,18 +313,29 @@ std::vector<int> even_split(int rest, int parts)
 // of 4). Measured over 2^28 amplitudes at p = 3, 4096-amplitude against wide
 // tiles: forward 2.67 -> 1.59 ms at 21 qubits, 2.70 -> 1.66 at 24, 2.81 -> 1.95
 // at 25 (64-byte rows), 2.79 -> 2.15 at 26 (pairs; one state 0.63 -> 0.49); gradient 5.94 -> 4.37,
-// 6.06 -> 4.68, 6.26 -> 5.10 and 6.21 -> 6.30 ms.
+// 6.06 -> 4.68, 6.26 -> 5.10 and 6.21 -> 6.30 ms; one gradient of 29 qubits 17.8 -> 14.9,
+// of 30 36.5 -> 30.4 ms (sparse graphs, tuned 4096-amplitude splits).
 int wide_groups_for(int n) { return 1 + (n - WIDE_BITS + WIDE_GROUP_MAX - 1) / WIDE_GROUP_MAX; }
 bool wide_saves(int n) { return n > SMALL_MAX_N + 2 && wide_groups_for(n) < groups_for(n); }
 
 // Exceptions. 26 qubits: the 32-byte rows take back the gradient's gain (the
-// forward passes have tiles in pairs for them). Gradients of denser graphs: at generic angles dE/dgamma
-// is small beside the C(z)-weighted terms that cancel in it (10^-5 and less of
-// them at 21 qubits and half of all edges), so another order of the roundings
-// moves its leading digits without being more or less exact; those subgraphs
-// keep the tiles, and the bits, that they have. So do gradients of one layer, where
-// the usual starting angle beta = pi/8 is a stationary point of every triangle-free
-// subgraph and Adam blows dE/dbeta's rounding noise up to its step size.
+// forward passes have tiles in pairs for them).
+//
+// Gradients of denser graphs: at generic angles dE/dgamma is small beside the
+// C(z)-weighted terms that cancel in it, so another order of the roundings moves its
+// leading digits without being more or less exact; those subgraphs keep the tiles,
+// and the bits, that they have. The line is the weight sum of 1.5 n unit edges, up to
+// which the relative error of dE/dgamma against FP64 is that of the amplitudes: 0.3 to
+// 0.9e-6 on either tile (21 and 24 qubits, p = 2 and 4, geometric means). At 2 n edges it
+// is 0.6 to 2e-6, at 3 n 1.4 to 4e-6, at half of all pairs 0.6 to 3e-5, with weights of
+// 1..9 up to 1e-4, single ones 1e-3; wide tiles / 4096-amplitude ones differ by factors
+// between 0.4 and 2.7 there, without a trend. (dE/dbeta stays at 0.2 to 3e-6.)
+//
+// Batches made for one layer: the usual starting angle beta = pi/8 is a stationary point
+// of every triangle-free subgraph, and Adam blows dE/dbeta's rounding noise up to its
+// step size. (The tables' order is fixed when the batch is made, so this goes by max_p:
+// a call of one layer on a batch made for more runs that batch's tiles. The kernels of
+// small subgraphs have no such order and go by the call's p.)
 bool wide_allowed(const SubDesc& d, bool grad, int64_t wsum, int max_p)
 {
     if (d.skip || !wide_saves(d.n) || !tuned_split(d.n).empty()) return false;

@@ -26,10 +26,10 @@
 // bytes): group 0 middle forward 557 us (5.1 TB/s), 11-qubit middle forward
 // 790 us (3.6 TB/s: a copy of 64-byte rows reaches 3.6), group 0 middle
 // backward 1.50 ms (2.8 TB/s), 11-qubit middle backward 1.48 ms (2.8 TB/s).
-// The forward passes are bound by memory. The backward ones issue 6,370 (group
-// 0) and 4,810 vector instructions per wave, 0.57 of the time at the vector
-// units' rate, and their loads and stores do not overlap that: at 256 registers
-// a lane, one workgroup fills the CU. On 4096-amplitude tiles the two passes
+// The forward passes are bound by memory. The backward ones issue 6,400 (group
+// 0) and 4,830 vector instructions per wave, 0.57 of the time at the vector
+// units' rate, and their loads and stores do not overlap that: at 210 to 226
+// registers a lane, one workgroup fills the CU. On 4096-amplitude tiles the two passes
 // that each of these replaces take 5.9 + 4.5 and 4.9 + 4.5 ns per 1000
 // amplitudes, against 8.9 and 8.8.
 //
